@@ -29,11 +29,20 @@
 // ranking key follows the exact integer window statistics, and the winner's
 // NCC is recomputed in exact integer arithmetic from the staged operands.
 //
-// Data flow of one workgroup (one selected block):
-//  * the block's clipped window is staged in LDS as fp16 (v - c), rows padded
-//    so every base's reads stay inside, and T - c goes to a zero-bordered
-//    fp16 table from which each wavefront builds its Toeplitz B operands once
-//    (they stay in registers for the whole block);
+// Data flow of one workgroup (one selected block).  What bounds it is latency:
+// 5508 blocks of the 256x256x124 workload (b = 7, W = 10) pass two at a time
+// through each of 256 CUs, and a wavefront used to spend 72,000 cycles on a
+// block, of which the products and their ranking were 18,600 (cycle stamps
+// per phase).  So the phases are arranged to wait for memory once:
+//  * every load of the block (its voxels, then the window's 16-byte row
+//    chunks, at most KREG per thread) is issued at the start, into registers;
+//  * while the window's loads return, the block's sums give its centre and
+//    T - c goes to four zero-bordered fp16 tables (one per x offset, so that
+//    the reads are aligned), from which each wavefront builds its Toeplitz B
+//    operands once (they stay in registers for the whole block);
+//  * the window's value range then gives its centre, and the window is written
+//    to LDS once, as fp16 (v - c), over the tables, two rows interleaved so
+//    that an A operand is one 16-byte read;
 //  * each wavefront sweeps the window planes for a tile of 16 bases: the A
 //    operand loaded for plane p feeds the accumulators of every displacement
 //    plane dz = p - s that uses it (s = 0..b-1), a ring of b accumulator
@@ -42,13 +51,18 @@
 //    its slot reused;
 //  * bases cover the valid (dx, dy) range in steps of 4; the displacement
 //    planes are split into phases so that tiles = ceil(bases * phases / 16)
-//    balance over the workgroup's wavefronts;
+//    balance over the workgroup's wavefronts; a table in LDS, filled while the
+//    loads are in flight, says which base and phase a tile's row is;
 //  * argmax: largest key, smallest shift index among equal keys, reduced over
-//    lanes, wavefronts and the workgroup.
+//    lanes (by DPP moves), wavefronts and the workgroup.
 //
-// One 256-thread workgroup per selected block, two co-resident per CU: the
-// staging and ranking latencies of one are hidden behind the matrix work of
-// the other.
+// One 256-thread workgroup per selected block, two co-resident per CU up to
+// b = 7: the latencies of one are hidden behind the matrix work of the other.
+// Measured against the earlier form (window staged raw in two rounds, centred
+// in place, operands from one table by 2-byte reads, 64-bit record addresses,
+// shuffle reductions): the search takes 0.178 ms instead of 0.356 on
+// 256x256x124 (b = 7, W = 10, 5508 blocks), 42.0 instead of 57.1 ms on 512x512x256
+// (b = 9, W = 12, 357,035 blocks); the keys and the winners are the same bits.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -56,6 +70,8 @@
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
+#include <type_traits>
 
 #include "nrr_internal.h"
 
@@ -66,24 +82,28 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));  // volume rows
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef short i16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 half4u __attribute__((ext_vector_type(4), aligned(2)));
 
 constexpr int OFF = 3;  // zero border of the T table (offsets 0..3)
 
-// Compile-time sizes of the K layout for block edge B.
+// Compile-time sizes of the K layout for block edge B, and of the block
+// tables the B operands are read from: four copies of T - c (offset a's
+// values moved right by a columns, so that every operand half is an aligned
+// 8-byte read), each with OFF zero rows above.
 template <int B>
 struct KGeo {
     static constexpr int GX = (B + 3 + 3) / 4;   // x' groups of 4 (x' extent B + 3)
     static constexpr int GYP = (B + 3 + 1) / 2;  // y' row pairs (y' extent B + 3)
     static constexpr int NG = GX * GYP;          // k-groups of 8 per block plane
     static constexpr int NQ = (NG + 3) / 4;      // 32-wide K chunks per block plane
-    static constexpr int TXW = 4 * GX + 4;       // T table row width (halves)
+    static constexpr int TXW = 4 * GX;           // T table row width (halves)
     static constexpr int TYW = 2 * GYP + OFF;    // T table rows per plane
-    static constexpr int TT_HALVES = B * TYW * TXW;
-    static constexpr int TT_BYTES = (TT_HALVES * 2 + 15) & ~15;
+    static constexpr int TCOPY = B * TYW * TXW;  // halves per copy
+    static constexpr int T_BYTES = (4 * TCOPY * 2 + 15) & ~15;
 };
 
 struct MfParams {
@@ -94,8 +114,11 @@ struct MfParams {
     int64_t first;  // first block of this launch
     int w;
     const StatU16 *stats;
+    int64_t nstat;  // records of the table
     int ox, oy;
-    int rp, pl;  // LDS window row and plane pitch (halves)
+    int rp;        // LDS window row pitch (halves)
+    int tab_off;   // LDS byte offset of the tile-row table
+    int tz[2];     // phase length of an unclipped window, x parity shift 0 / 1
     int32_t *disp;
     float *ncc;
     float *conf;
@@ -123,33 +146,59 @@ __device__ inline void put(const MfParams &p, int64_t blk, int dx, int dy, int d
     p.conf[blk] = v > 0.0f ? v : 0.0f;
 }
 
+// Wavefront reductions by data-parallel-primitive moves (row shifts, then
+// row broadcasts): lane 63 ends with the result of all 64 lanes.  A step
+// costs a few cycles; a shuffle goes through LDS and waits ~100.
+template <int CTRL>
+__device__ inline int dpp(int old, int v) {
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xf, 0xf, false);
+}
+template <typename F>
+__device__ inline void dpp_steps(F &&f) {
+    f(std::integral_constant<int, 0x111>());  // row_shr:1
+    f(std::integral_constant<int, 0x112>());
+    f(std::integral_constant<int, 0x114>());
+    f(std::integral_constant<int, 0x118>());
+    f(std::integral_constant<int, 0x142>());  // row_bcast:15
+    f(std::integral_constant<int, 0x143>());  // row_bcast:31
+}
+__device__ inline int wave_sum(int v) {  // 32-bit sums, wrapping
+    dpp_steps([&](auto c) { v += dpp<decltype(c)::value>(0, v); });
+    return v;
+}
+__device__ inline u16x2 wave_min(u16x2 v) {
+    dpp_steps([&](auto c) {
+        const int o = dpp<decltype(c)::value>(-1, __builtin_bit_cast(int, v));
+        v = __builtin_elementwise_min(v, __builtin_bit_cast(u16x2, o));
+    });
+    return v;
+}
+__device__ inline void wave_best(float &bk, int &bi) {
+    dpp_steps([&](auto c) {
+        constexpr int C = decltype(c)::value;
+        const float ok = __int_as_float(dpp<C>(__float_as_int(bk), __float_as_int(bk)));
+        const int oi = dpp<C>(bi, bi);
+        keep_best(bk, bi, ok, oi);
+    });
+}
+
 constexpr int MAX_NW = 4;  // wavefronts per workgroup
 struct MfSmall {
-    long long red[MAX_NW * 4];
-    int mm[MAX_NW * 4];
+    int sum[MAX_NW][3];
+    uint32_t mm[MAX_NW];  // block value range: min | (4095 - max) << 16
+    uint32_t wm[MAX_NW];  // window value range, the same
     float key[MAX_NW];
     int idx[MAX_NW];
 };
 
-// Tile decomposition of one block's displacements: bases every 4 voxels in x
-// and y; the displacement planes in `nph` phases of `tz` planes each, tz a
-// multiple of the block edge so the sweep's ramps fall on whole unrolled
-// blocks of steps (planes past the valid range are computed and masked).
-struct Tiling {
-    int nbx, nby, nxy, nph, tz, nrows, ntiles;
-};
-
-__device__ inline Tiling make_tiling(int dxn, int dyn, int dzn, int b, int nq, int nw) {
-    Tiling t;
-    t.nbx = (dxn + 3) / 4;
-    t.nby = (dyn + 3) / 4;
-    t.nxy = t.nbx * t.nby;
-    // fewest wavefront rounds of (MFMAs of a tile + per-step overhead)
+// Fewest wavefront rounds of (MFMAs of a tile + per-step overhead): phase
+// length tz (a multiple of b) for bases nxy and dzn displacement planes.
+__host__ __device__ inline int best_phase(int nxy, int dzn, int b, int nq, int nw) {
     int best = b;
     float bc = 3.0e38f;
     for (int tz = b; tz < dzn + b; tz += b) {
         const int ph = (dzn + tz - 1) / tz;
-        const int tiles = (t.nxy * ph + 15) / 16;
+        const int tiles = (nxy * ph + 15) / 16;
         const int rounds = (tiles + nw - 1) / nw;
         const float c = rounds * ((float)tz * b * nq + 3.0f * (tz + b - 1));
         if (c < bc) {
@@ -157,30 +206,38 @@ __device__ inline Tiling make_tiling(int dxn, int dyn, int dzn, int b, int nq, i
             best = tz;
         }
     }
-    t.tz = best;
-    t.nph = (dzn + best - 1) / best;
-    t.nrows = t.nxy * t.nph;
-    t.ntiles = (t.nrows + 15) / 16;
-    return t;
+    return best;
 }
 
 // Search geometry of one block: valid displacement range per axis (the
 // displaced block inside the volume), the window origin, and the staged
 // region.  Rows are staged from the even element at or before the window's
-// first column (4-byte aligned copies; volumes with an even row length), so
-// window column x sits at LDS column x + px; the tiles' x bases are LDS
-// columns 4i (8-byte aligned operand reads).
+// first column (volumes with an even row length), so window column x sits at
+// LDS column x + px; the tiles' x bases are LDS columns 4i.
+//
+// Tile decomposition of the displacements: bases every 4 voxels in x and y
+// (nbx x nby of them); the displacement planes in `nph` phases of `tz` planes
+// each, tz a multiple of the block edge so the sweep's ramps fall on whole
+// unrolled blocks of steps (planes past the valid range are computed and
+// masked).  A tile is 16 rows (base, phase).
+//
+// LDS layout of the window: rows two by two (the two window rows a K group
+// of 8 reads are always an even row and the next), 4 columns of the upper
+// row then the same 4 of the lower, so an A operand is one aligned 16-byte
+// read.
 struct BGeo {
     int cx, cy, cz;
     bool inside;
     int lox, loy, loz, dxn, dyn, dzn;
     int wx0, wy0, wz0, ex, ey, ez, px;
-    int rpb, pyb, cpr;  // LDS columns read, staged rows per plane, 8-column chunks per row
-    Tiling tl;
+    int nbx, nby, cpr;  // bases per axis, 8-column chunks per staged row
+    int eyp;            // staged rows per plane (even; a row past the window repeats the last)
+    int rp2, pl;        // LDS pitch of a row pair and of a plane (halves)
+    int tz, nph, nrows, ntiles;
 };
 
 template <int B>
-__device__ inline BGeo block_geo(const MfParams &p, int64_t blk, int nw) {
+__device__ inline BGeo block_geo(const MfParams &p, int64_t blk) {
     using G = KGeo<B>;
     constexpr int H = (B - 1) / 2;
     BGeo g;
@@ -202,44 +259,43 @@ __device__ inline BGeo block_geo(const MfParams &p, int64_t blk, int nw) {
     g.ey = g.dyn + B - 1;
     g.ez = g.dzn + B - 1;
     g.px = (p.nx & 1) == 0 ? (g.wx0 & 1) : 0;
-    g.tl = make_tiling(g.dxn + g.px, g.dyn, g.dzn, B, G::NQ, nw);
-    g.rpb = 4 * (g.tl.nbx - 1) + 4 * G::GX;
-    g.pyb = 4 * (g.tl.nby - 1) + 2 * G::GYP;
-    g.cpr = (g.rpb + 7) / 8;
+    g.nbx = (g.dxn + g.px + 3) / 4;
+    g.nby = (g.dyn + 3) / 4;
+    g.cpr = (4 * (g.nbx - 1) + 4 * G::GX + 7) / 8;
+    g.eyp = (g.ey + 1) & ~1;
+    g.rp2 = 2 * p.rp;
+    g.pl = (g.eyp / 2) * g.rp2;
     return g;
 }
 
-// Global element of LDS column 8 xc, row y, plane z of the staged region
-// (rows past the window repeat its last row).
-__device__ inline int64_t stage_elem(const MfParams &p, const BGeo &g, int z, int y, int xc) {
-    return ((int64_t)(g.wz0 + z) * p.ny + (g.wy0 + min(y, g.ey - 1))) * p.nx + g.wx0 - g.px +
-           8 * xc;
+template <int B, int NW>
+__device__ inline void block_tiles(const MfParams &p, BGeo &g) {
+    const int d = 2 * p.w + 1, nxy = g.nbx * g.nby;
+    g.tz = g.dxn == d && g.dyn == d && g.dzn == d ? p.tz[g.px]
+                                                  : best_phase(nxy, g.dzn, B, KGeo<B>::NQ, NW);
+    g.nph = (g.dzn + g.tz - 1) / g.tz;
+    g.nrows = nxy * g.nph;
+    g.ntiles = (g.nrows + 15) / 16;
 }
 
-// The 16 bytes (8 voxels) of one staged chunk through registers: a 16-byte
-// load where it lies inside the volume, else clamped words (the volume's
-// last voxels) or, for odd row lengths, voxel by voxel clamped into the
-// window's row.
-__device__ inline u32x4 load_chunk(const MfParams &p, const BGeo &g, int64_t e, int xc) {
-    const int64_t vol_end = (int64_t)p.nx * p.ny * p.nz - 1;
-    if ((p.nx & 1) == 0 && e + 7 <= vol_end) return *reinterpret_cast<const u32x4 *>(p.flt + e);
-    uint32_t t[4];
-    if ((p.nx & 1) == 0) {
-        const int64_t last_pair = (vol_end - 1) & ~(int64_t)1;
+// Tile rows as packed table entries: x base index, y base index, phase, and
+// whether the row exists (rows past the last repeat row 0, masked).
+__device__ inline uint32_t row_entry(const BGeo &g, int r) {
+    const bool real = r < g.nrows;
+    const int rr = real ? r : 0, nxy = g.nbx * g.nby;
+    const int ph = rr / nxy, xy = rr - ph * nxy, yi = xy / g.nbx, xi = xy - yi * g.nbx;
+    return (uint32_t)xi | (uint32_t)yi << 8 | (uint32_t)ph << 16 | (real ? 1u << 24 : 0u);
+}
+
+// The chunk 8 columns wide that starts `sh` voxels after the 16 bytes v, the
+// volume's last: voxels past the end repeat the last pair.
+__device__ inline u32x4 shift_chunk(u32x4 v, int sh) {
+    const uint32_t h[4] = {v[0] >> 16 | v[1] << 16, v[1] >> 16 | v[2] << 16,
+                           v[2] >> 16 | v[3] << 16, v[3] >> 16 | (v[3] & 0xffff0000u)};
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            t[j] = *reinterpret_cast<const uint32_t *>(p.flt + min(e + 2 * j, last_pair));
-    } else {
-        const uint16_t *r = p.flt + (e - 8 * xc);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int x0 = min(8 * xc + 2 * j, g.ex - 1), x1 = min(8 * xc + 2 * j + 1, g.ex - 1);
-            t[j] = (uint32_t)r[x0] | ((uint32_t)r[x1] << 16);
-        }
-    }
-    u32x4 v;
-    __builtin_memcpy(&v, t, 16);
-    return v;
+    for (int j = 0; j < 4; ++j) v[j] = sh & 1 ? h[j] : v[j];
+    v = sh & 2 ? u32x4{v[1], v[2], v[3], v[3]} : v;
+    return sh & 4 ? u32x4{v[2], v[3], v[3], v[3]} : v;
 }
 
 // One unrolled block of B sweep steps t0 .. t0 + B - 1 (t0 a multiple of B):
@@ -279,22 +335,23 @@ __device__ __attribute__((always_inline)) inline void sweep_block(
 }
 
 // Toeplitz B operands of this lane for every block plane and K chunk, from
-// the zero-bordered table of T - c.
+// the zero-bordered copies of T - c: column (oa, ob) reads copy oa, ob rows
+// up.
 template <int B>
 __device__ __attribute__((always_inline)) inline void build_bop(
     const _Float16 *tt, int lane, half8 (&bop)[B][KGeo<B>::NQ]) {
     using G = KGeo<B>;
-    const int grp = lane >> 4, oa = lane & 3, ob = (lane >> 2) & 3;  // column: offset (oa, ob)
+    const int grp = lane >> 4, oa = lane & 3, ob = (lane >> 2) & 3;
 #pragma unroll
     for (int q = 0; q < G::NQ; ++q) {
         const int g = 4 * q + grp;
         const bool real = g < G::NG;
         const int gx = real ? g % G::GX : 0, gy = real ? g / G::GX : 0;
+        const _Float16 *tr = tt + oa * G::TCOPY + (2 * gy - ob + OFF) * G::TXW + 4 * gx;
 #pragma unroll
         for (int s = 0; s < B; ++s) {
-            const _Float16 *tr = tt + (s * G::TYW + 2 * gy - ob + OFF) * G::TXW + 4 * gx - oa + OFF;
-            const half4u lo = *reinterpret_cast<const half4u *>(tr);
-            const half4u hi = *reinterpret_cast<const half4u *>(tr + G::TXW);
+            const half4 lo = *reinterpret_cast<const half4 *>(tr + s * G::TYW * G::TXW);
+            const half4 hi = *reinterpret_cast<const half4 *>(tr + (s * G::TYW + 1) * G::TXW);
             const half8 v = half8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
             bop[s][q] = real ? v : half8{};
         }
@@ -302,58 +359,77 @@ __device__ __attribute__((always_inline)) inline void build_bop(
 }
 
 // This wavefront's tiles of the block's search over the centred window
-// `win` (row pitch rp, plane pitch pl halves): keeps the lane's best (key,
-// shift index).  key = (N C - S_T S_F) * rsqrt(N varF), with S_T = sum (T -
-// c_T) and S_F = sum (F - c_F) = s + N (2048 - c_F) (the table's s sums
-// F - 2048): S_T S_F = S_T s + S_T N (2048 - c_F), both terms in FP32 from
-// exact integers (relative error 2^-24 of terms at most |S_T| N 2048).
-template <int B, int NW, bool SURF>
+// `win`: keeps the lane's best (key, shift index).  key = (N C - S_T S_F) *
+// rsqrt(N varF), with S_T = sum (T - c_T) and S_F = sum (F - c_F) = s + N
+// (2048 - c_F) (the table's s sums F - 2048): S_T S_F = S_T s + S_T N (2048 -
+// c_F), both terms in FP32 from exact integers (relative error 2^-24 of
+// terms at most |S_T| N 2048).
+//
+// WIDE: volumes whose window spans more than 2 GiB of records; the records
+// are read through 64-bit addresses, clamped into the valid range.  Else
+// through a buffer descriptor of the table from the window's corner on: one
+// 32-bit offset per row, the plane added by the scalar offset, and reads past
+// the table's end (planes that are masked) return 0 by the descriptor's own
+// range check.
+template <int B, int NW, bool SURF, bool WIDE>
 __device__ __attribute__((always_inline)) inline void sweep_tiles(
-    const MfParams &p, const BGeo &g, int64_t blk, const _Float16 *win, int rp, int pl,
+    const MfParams &p, const BGeo &g, int64_t blk, const _Float16 *win, const uint32_t *rowtab,
     const half8 (&bop)[B][KGeo<B>::NQ], long long sTc, float inv_vt, int cf, int wave, int lane,
     float &bk, int &bi) {
     using G = KGeo<B>;
     constexpr int N = B * B * B, NQ = G::NQ;
-    const Tiling &tl = g.tl;
     const int n16 = lane & 15, grp = lane >> 4;
     const int oa = n16 & 3, ob = n16 >> 2;
     const float fN = (float)N, fST = (float)sTc;
     const float fshift = (float)(sTc * (long long)N * (2048 - cf));
     const int side = 2 * p.w + 1, side2 = side * side;
     const int plane_rec = p.oy * p.ox;
-    for (int tile = wave; tile < tl.ntiles; tile += NW) {
-        // the lane's A row (base of row n16)
-        int aoff[NQ], aph;
-        {
-            const int r = 16 * tile + n16, rr = r < tl.nrows ? r : 0;
-            const int xy = rr % tl.nxy, ph = rr / tl.nxy;
-            const int bx = 4 * (xy % tl.nbx), by = 4 * (xy / tl.nbx);
-            aph = ph * tl.tz;
+    const int64_t corner = ((int64_t)g.wz0 * p.oy + g.wy0) * p.ox + g.wx0;
+    const StatU16 *srec = p.stats + corner;
+    const int64_t left = (p.nstat - corner) * (int64_t)sizeof(StatU16);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<StatU16 *>(srec), 0, (int)(left < 0xffffffffll ? left : 0xffffffffll),
+        0x00020000);
+    int kq[NQ];  // this lane's K group of each chunk, from its row's base
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int gg = 4 * q + grp < G::NG ? 4 * q + grp : 0;
-                aoff[q] = (by + 2 * (gg / G::GX)) * rp + bx + 4 * (gg % G::GX);
-            }
+    for (int q = 0; q < NQ; ++q) {
+        const int gg = 4 * q + grp < G::NG ? 4 * q + grp : 0;
+        kq[q] = (gg / G::GX) * g.rp2 + (gg % G::GX) * 8;
+    }
+    for (int tile = wave; tile < g.ntiles; tile += NW) {
+        // the lane's A row (base of row n16): window halves at abase + kq,
+        // plane aph + t, which advances while t < alim
+        int abase, alim;
+        {
+            const uint32_t e = rowtab[16 * tile + n16];
+            const int aph = (int)(e >> 16 & 0xff) * g.tz;
+            abase = min(aph, g.ez - 1) * g.pl + (int)(e >> 8 & 0xff) * 2 * g.rp2 +
+                    (int)(e & 0xff) * 8;
+            alim = g.ez - 1 - aph;
         }
         // the lane's four output rows: displacement (odx, ody) relative to the
-        // valid range's corner, plane offset oph; records at orec + dz planes
-        // ranking of plane tau: valid while tau < lim (lim = -1 for rows
-        // outside the valid range), shift index oidx + tau side^2; records
-        // of plane min(tau + oph, dzn - 1) at rcur, which advances by a plane
-        // while tau < lim3 = dzn - 1 - oph
-        int rcur[4], lim[4], lim3[4], oidx[4];
+        // valid range's corner, plane offset oph.  Plane tau is ranked while
+        // tau < lim (lim = -1 for rows outside the valid range), shift index
+        // oidx + tau side^2; its record is at roff + tau planes (WIDE: at
+        // rcur, which advances by a plane while tau < lim3 = dzn - 1 - oph)
+        int lim[4], lim3[4], oidx[4];
+        uint32_t roff[4];
+        int64_t rcur[4];
+        const uint4 ent = *reinterpret_cast<const uint4 *>(rowtab + 16 * tile + 4 * grp);
+        const uint32_t ents[4] = {ent.x, ent.y, ent.z, ent.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int r = 16 * tile + 4 * grp + i;
-            bool orow = r < tl.nrows;
-            const int rr = orow ? r : 0;
-            const int xy = rr % tl.nxy, ph = rr / tl.nxy;
-            const int odx = 4 * (xy % tl.nbx) + oa - g.px;
-            const int ody = 4 * (xy / tl.nbx) + ob;
-            const int oph = ph * tl.tz;
-            orow = orow && odx >= 0 && odx < g.dxn && ody < g.dyn;
-            rcur[i] = (g.wz0 * p.oy + (g.wy0 + min(ody, g.dyn - 1))) * p.ox +
-                      (g.wx0 + min(max(odx, 0), g.dxn - 1)) + min(oph, g.dzn - 1) * plane_rec;
+            const uint32_t e = ents[i];
+            const int odx = 4 * (int)(e & 0xff) + oa - g.px;
+            const int ody = 4 * (int)(e >> 8 & 0xff) + ob;
+            const int oph = (int)(e >> 16 & 0xff) * g.tz;
+            const bool orow = (e >> 24) && odx >= 0 && odx < g.dxn && ody < g.dyn;
+            const int cell = min(ody, g.dyn - 1) * p.ox + min(max(odx, 0), g.dxn - 1);
+            if constexpr (WIDE)
+                rcur[i] = (int64_t)cell + (int64_t)min(oph, g.dzn - 1) * plane_rec;
+            else
+                roff[i] = (uint32_t)(cell + min(oph, g.dzn - 1) * plane_rec) *
+                          (uint32_t)sizeof(StatU16);
             lim[i] = orow ? g.dzn - oph : -1;
             lim3[i] = g.dzn - 1 - oph;
             oidx[i] = (g.loz + oph + p.w) * side2 + (g.loy + ody + p.w) * side +
@@ -364,36 +440,43 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
         for (int k = 0; k < B; ++k) acc[k] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
         // A operand of plane t + phase (clamped: planes past the window feed
         // only displacements that are masked out)
-        auto load_a = [&](int t, half8 (&aop)[NQ]) {
-            const int pz = min(t + aph, g.ez - 1);
+        auto read_a = [&](half8 (&aop)[NQ]) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const _Float16 *ap = win + pz * pl + aoff[q];
-                const half4 lo = *reinterpret_cast<const half4 *>(ap);
-                const half4 hi = *reinterpret_cast<const half4 *>(ap + rp);
-                aop[q] = half8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            }
+            for (int q = 0; q < NQ; ++q)
+                aop[q] = *reinterpret_cast<const half8 *>(win + abase + kq[q]);
+        };
+        auto load_a = [&](int t, half8 (&aop)[NQ]) {
+            abase += t <= alim ? g.pl : 0;
+            read_a(aop);
         };
         // statistics records of the four output rows, loaded one displacement
-        // plane ahead of their ranking (clamped into the valid range, so every
-        // load is in bounds; invalid ones are masked)
+        // plane ahead of their ranking
         StatU16 rec0[4];
         auto fetch = [&](int tau, StatU16 (&rec)[4]) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                rec[i] = p.stats[rcur[i]];
-                rcur[i] += tau < lim3[i] ? plane_rec : 0;
+                if constexpr (WIDE) {
+                    rec[i] = srec[rcur[i]];
+                    rcur[i] += tau < lim3[i] ? plane_rec : 0;
+                } else {
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(
+                        rsrc, (int)roff[i], tau * plane_rec * (int)sizeof(StatU16), 0);
+                    rec[i].s = (int)v[0];
+                    rec[i].r = __uint_as_float(v[1]);
+                }
             }
         };
-        // best key of each output row in this tile and its plane (byte i of
-        // rtp; 0xff: none; planes < 255, see mf_plan).  Along a row the shift
-        // index grows with tau, so a strict comparison keeps the smallest
-        // index among equal keys; rows are merged with the full rule after
-        // the tile.
+        // best key of each output row in this tile and its plane (-1: none).
+        // Along a row the shift index grows with tau, so a strict comparison
+        // keeps the smallest index among equal keys; rows are merged with the
+        // full rule after the tile.
         float rk[4];
-        uint32_t rtp = 0xffffffffu;
+        int rt[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rk[i] = -INFINITY;
+        for (int i = 0; i < 4; ++i) {
+            rk[i] = -INFINITY;
+            rt[i] = -1;
+        }
         // ranking of displacement plane tau, then the records of tau + 1
         auto rank = [&](const float4v &c4, int tau) {
 #pragma unroll
@@ -403,7 +486,7 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
                 const float key = cov * rec0[i].r;
                 const bool take = (tau < lim[i]) & (key > rk[i]);
                 rk[i] = take ? key : rk[i];
-                rtp = take ? (rtp & ~(0xffu << (8 * i))) | ((uint32_t)tau << (8 * i)) : rtp;
+                rt[i] = take ? tau : rt[i];
                 if constexpr (SURF)  // NCC = key / sqrt(N varT)
                     if (tau < lim[i]) p.surface[blk * side2 * side + oidx[i] + tau * side2] =
                         key * inv_vt;
@@ -412,126 +495,13 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
         };
         fetch(0, rec0);
         half8 aop[NQ];
-        load_a(0, aop);
+        read_a(aop);
         sweep_block<B, NQ, 0>(0, acc, bop, aop, load_a, rank);
-        for (int t0 = B; t0 < tl.tz; t0 += B) sweep_block<B, NQ, 1>(t0, acc, bop, aop, load_a, rank);
-        sweep_block<B, NQ, 2>(tl.tz, acc, bop, aop, load_a, rank);
+        for (int t0 = B; t0 < g.tz; t0 += B) sweep_block<B, NQ, 1>(t0, acc, bop, aop, load_a, rank);
+        sweep_block<B, NQ, 2>(g.tz, acc, bop, aop, load_a, rank);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int rt = (rtp >> (8 * i)) & 0xff;
-            if (rt != 0xff) keep_best(bk, bi, rk[i], oidx[i] + rt * side2);
-        }
-    }
-}
-
-// Workgroup argmax of the lanes' (key, index), then the exact NCC at the
-// winner from the staged integers (F - c_F in the window, T - c_T in the
-// table; the NCC does not depend on either constant), written by thread 0.  Every
-// thread of the workgroup calls it; it ends with a barrier.
-template <int B, int NW>
-__device__ __attribute__((always_inline)) inline void finish_block(
-    const MfParams &p, const BGeo &g, int64_t blk, const _Float16 *win, int rp, int pl,
-    const _Float16 *tt, long long st, long long stt, int c, float bk, int bi, MfSmall &sm,
-    int tid) {  // c: the block's constant c_T
-    using G = KGeo<B>;
-    constexpr int N = B * B * B, NT = 64 * NW;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ok = __shfl_xor(bk, off);
-        const int oi = __shfl_xor(bi, off);
-        keep_best(bk, bi, ok, oi);
-    }
-    if (lane == 0) {
-        sm.key[wave] = bk;
-        sm.idx[wave] = bi;
-    }
-    __syncthreads();
-    bk = sm.key[0];
-    bi = sm.idx[0];
-#pragma unroll
-    for (int i = 1; i < NW; ++i) keep_best(bk, bi, sm.key[i], sm.idx[i]);
-    if (bi == INT_MAX) {  // no finite key (cannot happen for 12-bit data)
-        if (tid == 0) put(p, blk, 0, 0, 0, NAN);
-        __syncthreads();
-        return;
-    }
-    const int side = 2 * p.w + 1;
-    const int ddx = bi % side - p.w, ddy = (bi / side) % side - p.w, ddz = bi / (side * side) - p.w;
-    const int rx = ddx - g.lox + g.px, ry = ddy - g.loy, rz = ddz - g.loz;
-    long long sf = 0, sff = 0, stf = 0;
-    for (int o = tid; o < N; o += NT) {
-        const int oz = o / (B * B), oy = (o / B) % B, ox = o % B;
-        const long long f = (long long)(float)win[(rz + oz) * pl + (ry + oy) * rp + rx + ox];
-        const long long tv = (long long)(float)tt[(oz * G::TYW + oy + OFF) * G::TXW + ox + OFF];
-        sf += f;
-        sff += f * f;
-        stf += tv * f;
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        sf += __shfl_xor(sf, off);
-        sff += __shfl_xor(sff, off);
-        stf += __shfl_xor(stf, off);
-    }
-    __syncthreads();  // sm reused
-    if (lane == 0) {
-        sm.red[wave * 4] = sf;
-        sm.red[wave * 4 + 1] = sff;
-        sm.red[wave * 4 + 2] = stf;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        sf = sff = stf = 0;
-        for (int i = 0; i < NW; ++i) {
-            sf += sm.red[i * 4];
-            sff += sm.red[i * 4 + 1];
-            stf += sm.red[i * 4 + 2];
-        }
-        const long long sTc = st - (long long)N * c;                       // sum (T - c)
-        const long long tc2 = stt - 2ll * c * st + (long long)N * c * c;  // sum (T - c)^2
-        const long long vt = (long long)N * tc2 - sTc * sTc;
-        const long long vf = (long long)N * sff - sf * sf;
-        const long long cv = (long long)N * stf - sTc * sf;
-        const double v = (vt > 0 && vf > 0) ? (double)cv / sqrt((double)vt * (double)vf) : 0.0;
-        put(p, blk, ddx, ddy, ddz, (float)v);
-    }
-    __syncthreads();
-}
-
-// Workgroup reduction of the block sums and the value ranges (block: tmin,
-// tmax; window: vmin, vmax); every thread returns the totals.
-template <int NW>
-__device__ inline void reduce_block(long long &st, long long &stt, int &tmin, int &tmax,
-                                    int &vmin, int &vmax, MfSmall &sm, int tid) {
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int off = 32; off > 0; off >>= 1) {
-        st += __shfl_xor(st, off);
-        stt += __shfl_xor(stt, off);
-        tmin = min(tmin, __shfl_xor(tmin, off));
-        tmax = max(tmax, __shfl_xor(tmax, off));
-        vmin = min(vmin, __shfl_xor(vmin, off));
-        vmax = max(vmax, __shfl_xor(vmax, off));
-    }
-    if (lane == 0) {
-        sm.red[wave * 4] = st;
-        sm.red[wave * 4 + 1] = stt;
-        sm.mm[wave * 4] = tmin;
-        sm.mm[wave * 4 + 1] = tmax;
-        sm.mm[wave * 4 + 2] = vmin;
-        sm.mm[wave * 4 + 3] = vmax;
-    }
-    __syncthreads();
-    st = 0;
-    stt = 0;
-    tmin = vmin = 4095;
-    tmax = vmax = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        st += sm.red[i * 4];
-        stt += sm.red[i * 4 + 1];
-        tmin = min(tmin, sm.mm[i * 4]);
-        tmax = max(tmax, sm.mm[i * 4 + 1]);
-        vmin = min(vmin, sm.mm[i * 4 + 2]);
-        vmax = max(vmax, sm.mm[i * 4 + 3]);
+        for (int i = 0; i < 4; ++i)
+            if (rt[i] >= 0) keep_best(bk, bi, rk[i], oidx[i] + rt[i] * side2);
     }
 }
 
@@ -559,135 +529,300 @@ __device__ inline u32x4 centre_chunk(u32x4 v, i16x2 c2) {
 // register file of one.
 constexpr int PB_NW = 4;
 
-template <int B, bool SURF>
-__global__ __launch_bounds__(64 * PB_NW, B <= 7 ? 2 : 1) void k_match_mfma(MfParams p) {
+template <int B, bool SURF, bool WIDE>
+__global__ __launch_bounds__(64 * PB_NW, B == 3 ? 4 : B == 5 ? 3 : B == 7 ? 2 : 1) void k_match_mfma(MfParams p) {
     using G = KGeo<B>;
     constexpr int H = (B - 1) / 2, N = B * B * B, NQ = G::NQ, NT = 64 * PB_NW;
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ MfSmall sm;
-    _Float16 *tt = reinterpret_cast<_Float16 *>(lds);  // [B][TYW][TXW]
-    _Float16 *win = reinterpret_cast<_Float16 *>(lds + G::TT_BYTES);
+    _Float16 *tt = reinterpret_cast<_Float16 *>(lds);  // [4][B][TYW][TXW], until the operands are built
+    _Float16 *win = reinterpret_cast<_Float16 *>(lds);  // the window, after that
+    uint32_t *rowtab = reinterpret_cast<uint32_t *>(lds + p.tab_off);
 
     const int64_t blk = p.first + xcd_order(blockIdx.x, gridDim.x);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const BGeo g = block_geo<B>(p, blk, PB_NW);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    BGeo g = block_geo<B>(p, blk);
     if (!g.inside) {
         if (tid == 0) put(p, blk, 0, 0, 0, NAN);
         return;
     }
-    const int rp = p.rp, pl = p.pl;
-    const int nchunk = g.ez * g.pyb * g.cpr;
 
-    // ---- pass 1: window as raw 12-bit values, block sums, value range.  The
-    // block's voxels (at most 3 per thread for edges up to 9) are loaded with
-    // the first round of window rows and kept in registers for pass 2.
-    for (int i = tid; i < G::TT_HALVES; i += NT) tt[i] = (_Float16)0.0f;
+    // ---- loads of the block's voxels (at most 3 per thread for edges up to
+    // 9) and of the window's rows, all in flight together; the block tables
+    // and operands are built while the window's loads return
     constexpr int TPT = (N + NT - 1) / NT;  // block voxels per thread
     int tv[TPT];
-#pragma unroll
-    for (int k = 0; k < TPT; ++k) {
-        const int o = min(tid + k * NT, N - 1);
-        const int oz = o / (B * B), oy = (o / B) % B, ox = o % B;
-        tv[k] = p.ref[((int64_t)(g.cz - H + oz) * p.ny + (g.cy - H + oy)) * p.nx + (g.cx - H + ox)];
-    }
-    // The range that clamps the window's centre covers every staged voxel: the
-    // window and the few neighbouring voxels its padded rows pick up.
-    u16x2 mn2 = {4095, 4095}, mx2 = {0, 0};
     {
-        // chunk coordinates advance by NT chunks per step (no divisions)
-        const int sx = NT % g.cpr, sr = NT / g.cpr;
-        int xc = tid % g.cpr, y = tid / g.cpr, z = 0;
-        while (y >= g.pyb) {
-            y -= g.pyb;
-            ++z;
-        }
-        constexpr int UNR = 8;
-        for (int c0 = tid; c0 < nchunk; c0 += NT * UNR) {
-            u32x4 w[UNR];
-            int off[UNR];
-            bool live[UNR];
+        const uint16_t *rb =
+            p.ref + ((int64_t)(g.cz - H) * p.ny + (g.cy - H)) * p.nx + (g.cx - H);
+        const int64_t rplane = (int64_t)p.ny * p.nx;
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                live[u] = c0 + u * NT < nchunk;
-                const int zz = live[u] ? z : 0;
-                off[u] = zz * pl + y * rp + 8 * xc;
-                w[u] = load_chunk(p, g, stage_elem(p, g, zz, y, xc), xc);
-                xc += sx;
-                y += sr;
-                if (xc >= g.cpr) {
-                    xc -= g.cpr;
-                    ++y;
-                }
-                while (y >= g.pyb) {
-                    y -= g.pyb;
-                    ++z;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                if (!live[u]) continue;
-                u16x2 h[4];
-                __builtin_memcpy(h, &w[u], 16);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    mn2 = __builtin_elementwise_min(mn2, h[j]);
-                    mx2 = __builtin_elementwise_max(mx2, h[j]);
-                }
-                *reinterpret_cast<u32x4 *>(win + off[u]) = w[u];
-            }
+        for (int k = 0; k < TPT; ++k) {
+            const int o = min(tid + k * NT, N - 1);
+            const int oz = o / (B * B), oy = (o / B) % B, ox = o % B;
+            tv[k] = rb[oz * rplane + (int64_t)oy * p.nx + ox];
         }
     }
-    int vmin = min((int)mn2[0], (int)mn2[1]), vmax = max((int)mx2[0], (int)mx2[1]);
-    int tmin = 4095, tmax = 0;
-    long long st = 0, stt = 0;
+    // Thread t copies chunk column xc of every R-th row of the window (rows
+    // (z, y) in order, R even: an LDS row pair per two rows), so its addresses
+    // advance by additions.  Threads and steps past the last row repeat it.
+    // Rows beyond KREG steps (half windows above 13 or so) are read again
+    // when their centre is known.
+    constexpr int KREG = B == 3 ? 8 : B == 5 ? 16 : B == 7 ? 20 : 32;
+    const int R = (NT / g.cpr) & ~1, rows = g.ez * g.eyp;
+    const int kn = (rows + R - 1) / R;
+    const int xc = tid % g.cpr;
+    const uint16_t *wb = p.flt + ((int64_t)g.wz0 * p.ny + g.wy0) * p.nx + g.wx0 - g.px;
+    using Off = typename std::conditional<WIDE, int64_t, uint32_t>::type;
+    const Off nx_ = (Off)p.nx, nxy_ = (Off)p.nx * (Off)p.ny;
+    // A chunk that would run past the volume's last voxel is read 8 voxels
+    // before the end and moved into place when it is used (`edge`, uniform:
+    // the window has such chunks).
+    const int64_t tail = (int64_t)p.nx * p.ny * p.nz - 8 - (wb - p.flt);
+    const bool edge =
+        (int64_t)(g.ez - 1) * p.ny * p.nx + (int64_t)(g.ey - 1) * p.nx + 8 * (g.cpr - 1) > tail;
+    const Off tail_ = edge ? (Off)tail : std::numeric_limits<Off>::max();
+    const Off last = (Off)(g.ez - 1) * nxy_ + (Off)(g.ey - 1) * nx_ + (Off)(8 * xc);
+    struct Walk {
+        int r, z, y;
+    };
+    const int rz = R / g.eyp, ry = R - rz * g.eyp;
+    auto walk_start = [&]() {
+        Walk s;
+        s.r = tid / g.cpr;
+        if (s.r >= R) s.r = rows;  // idle thread: repeats the last row
+        s.z = s.r / g.eyp;
+        s.y = s.r - s.z * g.eyp;
+        return s;
+    };
+    auto walk_next = [&](Walk &s) {
+        s.r += R;
+        s.z += rz;
+        s.y += ry;
+        const bool wrap = s.y >= g.eyp;
+        s.y -= wrap ? g.eyp : 0;
+        s.z += wrap ? 1 : 0;
+    };
+    auto walk_elem = [&](const Walk &s) {
+        return s.r < rows ? (Off)s.z * nxy_ + (Off)min(s.y, g.ey - 1) * nx_ + (Off)(8 * xc) : last;
+    };
+    auto walk_load = [&](const Walk &s) {
+        const u32x4u v = *reinterpret_cast<const u32x4u *>(wb + min(walk_elem(s), tail_));
+        u32x4 o;
+        __builtin_memcpy(&o, &v, 16);
+        return o;
+    };
+    const bool odd = (p.nx & 1) != 0;
+    auto walk_fix = [&](u32x4 v, const Walk &s) {  // the chunk of an `edge` window
+        const int64_t sh = (int64_t)walk_elem(s) - tail;
+        return sh > 0 ? shift_chunk(v, (int)min(sh, (int64_t)(odd ? 7 : 6))) : v;
+    };
+    u32x4 w[KREG];
+    Walk at = walk_start();
+#pragma unroll
+    for (int k4 = 0; k4 < KREG; k4 += 4)
+        if (k4 < kn) {
+#pragma unroll
+            for (int k = k4; k < k4 + 4; ++k) {
+                w[k] = walk_load(at);
+                walk_next(at);
+            }
+        }
+
+    // ---- tile rows, zeroed block tables
+    block_tiles<B, PB_NW>(p, g);
+    for (int r = tid; r < 16 * g.ntiles; r += NT) rowtab[r] = row_entry(g, r);
+    for (int i = tid; i < G::T_BYTES / 16; i += NT)
+        *reinterpret_cast<u32x4 *>(lds + 16 * i) = u32x4{0, 0, 0, 0};
+
+    // ---- block sums and value range (per wavefront at most 192 values: the
+    // squares sum below 2^32), then c_T
+    uint32_t ws = 0, wss = 0;
+    u16x2 mm = {4095, 4095};
 #pragma unroll
     for (int k = 0; k < TPT; ++k) {
-        if (tid + k * NT >= N) continue;
-        st += tv[k];
-        stt += (long long)tv[k] * tv[k];
-        tmin = min(tmin, tv[k]);
-        tmax = max(tmax, tv[k]);
+        const bool real = tid + k * NT < N;
+        const uint32_t v = real ? (uint32_t)tv[k] : 0u;
+        ws += v;
+        wss += v * v;
+        const u16x2 m = {(uint16_t)tv[k], (uint16_t)(4095 - tv[k])};
+        if (real) mm = __builtin_elementwise_min(mm, m);
     }
-    reduce_block<PB_NW>(st, stt, tmin, tmax, vmin, vmax, sm, tid);
+    ws = (uint32_t)wave_sum((int)ws);
+    wss = (uint32_t)wave_sum((int)wss);
+    mm = wave_min(mm);
+    if (lane == 63) {
+        sm.sum[wave][0] = (int)ws;
+        sm.sum[wave][1] = (int)wss;
+        sm.mm[wave] = __builtin_bit_cast(uint32_t, mm);
+    }
+    __syncthreads();  // sums; the zeroed tables
+    long long st = 0, stt = 0;
+    mm = u16x2{4095, 4095};
+#pragma unroll
+    for (int i = 0; i < PB_NW; ++i) {
+        st += (uint32_t)sm.sum[i][0];
+        stt += (uint32_t)sm.sum[i][1];
+        mm = __builtin_elementwise_min(mm, __builtin_bit_cast(u16x2, sm.mm[i]));
+    }
     if ((long long)N * stt - st * st == 0) {  // flat block: every NCC is 0
         if (tid == 0) put(p, blk, g.lox, g.loy, g.loz, 0.0f);
         return;
     }
-    const int c = centre(st, N, tmin, tmax);    // c_T
-    const int cf = centre(st, N, vmin, vmax);  // c_F
-
-    // ---- pass 2: centre the staged planes in place (whole planes, padding
-    // included: those halves are never read) on c_F, and the bordered table
-    // of T - c_T
-    {
-        const i16x2 c2 = {(short)cf, (short)cf};
-        const int nq = g.ez * pl / 8;  // pl is a multiple of 8 halves
-        for (int i = tid; i < nq; i += NT) {
-            u32x4 *a = reinterpret_cast<u32x4 *>(win + 8 * i);
-            *a = centre_chunk(*a, c2);
-        }
-    }
+    const int c = centre(st, N, mm[0], 4095 - mm[1]);  // c_T
 #pragma unroll
     for (int k = 0; k < TPT; ++k) {
         const int o = tid + k * NT;
         if (o >= N) continue;
         const int oz = o / (B * B), oy = (o / B) % B, ox = o % B;
-        tt[(oz * G::TYW + oy + OFF) * G::TXW + ox + OFF] = (_Float16)(float)(tv[k] - c);
+        const _Float16 v = (_Float16)(float)(tv[k] - c);
+        _Float16 *d = tt + (oz * G::TYW + oy + OFF) * G::TXW + ox;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) d[a * G::TCOPY + a] = v;
+    }
+    __syncthreads();
+    half8 bop[B][NQ];
+    build_bop<B>(tt, lane, bop);
+
+    // ---- value range of the staged voxels, then c_F.  The range covers the
+    // window and, for even row lengths, the few neighbouring voxels its
+    // padded rows pick up.
+    u16x2 mn2 = {0xffff, 0xffff}, mx2 = {0, 0};
+    uint32_t keep[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+    if (odd) {  // only the window's own columns
+        const int nv = g.ex - 8 * xc;  // this thread's columns inside it
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            keep[j] = (2 * j < nv ? 0xffffu : 0u) | (2 * j + 1 < nv ? 0xffff0000u : 0u);
+    }
+    auto range = [&](const u32x4 &v) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            mn2 = __builtin_elementwise_min(mn2, __builtin_bit_cast(u16x2, v[j] | ~keep[j]));
+            mx2 = __builtin_elementwise_max(mx2, __builtin_bit_cast(u16x2, v[j] & keep[j]));
+        }
+    };
+    const Walk rest = at;
+    if (edge) {
+        Walk s = walk_start();
+#pragma unroll
+        for (int k = 0; k < KREG; ++k, walk_next(s)) w[k] = walk_fix(w[k], s);
+    }
+    auto reload = [&]() {
+        u32x4 v = walk_load(at);
+        if (edge) v = walk_fix(v, at);
+        return v;
+    };
+#pragma unroll
+    for (int k4 = 0; k4 < KREG; k4 += 4)
+        if (k4 < kn) {
+#pragma unroll
+            for (int k = k4; k < k4 + 4; ++k) range(w[k]);
+        }
+    for (int k = KREG; k < kn; ++k, walk_next(at)) range(reload());
+    const int vmn = min((int)mn2[0], (int)mn2[1]), vmx = max((int)mx2[0], (int)mx2[1]);
+    mm = wave_min(u16x2{(uint16_t)min(vmn, 4095), (uint16_t)(4095 - vmx)});
+    if (lane == 63) sm.wm[wave] = __builtin_bit_cast(uint32_t, mm);
+    __syncthreads();  // every wavefront's operands are built: the window takes the tables' place
+    mm = u16x2{4095, 4095};
+#pragma unroll
+    for (int i = 0; i < PB_NW; ++i)
+        mm = __builtin_elementwise_min(mm, __builtin_bit_cast(u16x2, sm.wm[i]));
+    const int cf = centre(st, N, mm[0], 4095 - mm[1]);  // c_F
+
+    // ---- the window as fp16 (v - c_F); a pair of rows past the last plane,
+    // which the lowest bases read against zeros, is cleared
+    {
+        const i16x2 c2 = {(short)cf, (short)cf};
+        const int end = ((rows - 1) >> 1) * g.rp2 + 4 + 16 * xc;  // the last row's (rows is even)
+        auto store = [&](const u32x4 &v, int r) {
+            const u32x4 h = centre_chunk(v, c2);
+            _Float16 *d = win + (r < rows ? (r >> 1) * g.rp2 + (r & 1) * 4 + 16 * xc : end);
+            *reinterpret_cast<u32x2 *>(d) = u32x2{h[0], h[1]};
+            *reinterpret_cast<u32x2 *>(d + 8) = u32x2{h[2], h[3]};
+        };
+        int r = tid / g.cpr;
+        if (r >= R) r = rows;
+#pragma unroll
+        for (int k4 = 0; k4 < KREG; k4 += 4)
+            if (k4 < kn) {
+#pragma unroll
+                for (int k = k4; k < k4 + 4; ++k, r += R) store(w[k], r);
+            }
+        at = rest;
+        for (int k = KREG; k < kn; ++k, walk_next(at)) store(reload(), at.r);
+        for (int i = tid; i < g.rp2 / 8; i += NT)
+            *reinterpret_cast<u32x4 *>(win + (rows >> 1) * g.rp2 + 8 * i) = u32x4{0, 0, 0, 0};
     }
     __syncthreads();
 
-    half8 bop[B][NQ];
-    build_bop<B>(tt, lane, bop);
     float bk = -INFINITY;
     int bi = INT_MAX;
-    const long long sTc = st - (long long)N * c;
+    const long long sTc = st - (long long)N * c;                      // sum (T - c)
+    const long long tc2 = stt - 2ll * c * st + (long long)N * c * c;  // sum (T - c)^2
+    const long long vt = (long long)N * tc2 - sTc * sTc;
     float inv_vt = 0.0f;
-    if constexpr (SURF) {  // 1 / sqrt(N sum (T - c)^2 - (sum (T - c))^2), exact integers
-        const long long tc2 = stt - 2ll * c * st + (long long)N * c * c;
-        inv_vt = (float)(1.0 / sqrt((double)((long long)N * tc2 - sTc * sTc)));
+    if constexpr (SURF) inv_vt = (float)(1.0 / sqrt((double)vt));
+    sweep_tiles<B, PB_NW, SURF, WIDE>(p, g, blk, win, rowtab, bop, sTc, inv_vt, cf, wave, lane, bk,
+                                      bi);
+
+    // ---- workgroup argmax, then the exact NCC at the winner from the staged
+    // integers (F - c_F in the window, T - c_T from the registers; the NCC
+    // does not depend on either constant), written by thread 0
+    wave_best(bk, bi);
+    if (lane == 63) {
+        sm.key[wave] = bk;
+        sm.idx[wave] = bi;
     }
-    sweep_tiles<B, PB_NW, SURF>(p, g, blk, win, rp, pl, bop, sTc, inv_vt, cf, wave, lane, bk, bi);
-    finish_block<B, PB_NW>(p, g, blk, win, rp, pl, tt, st, stt, c, bk, bi, sm, tid);
+    __syncthreads();
+    bk = sm.key[0];
+    bi = sm.idx[0];
+#pragma unroll
+    for (int i = 1; i < PB_NW; ++i) keep_best(bk, bi, sm.key[i], sm.idx[i]);
+    if (bi == INT_MAX) {  // no finite key (cannot happen for 12-bit data)
+        if (tid == 0) put(p, blk, 0, 0, 0, NAN);
+        return;
+    }
+    const int side = 2 * p.w + 1;
+    const int ddx = bi % side - p.w, ddy = (bi / side) % side - p.w, ddz = bi / (side * side) - p.w;
+    const int rx = ddx - g.lox + g.px, ryo = ddy - g.loy, rzo = ddz - g.loz;
+    // 32-bit sums per wavefront: at most 192 values of magnitude up to 2^22
+    int sf = 0, sff = 0, stf = 0;
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) {
+        const int o = tid + k * NT;
+        if (o >= N) continue;
+        const int oz = o / (B * B), oy = (o / B) % B, ox = o % B;
+        const int y = ryo + oy, x = rx + ox;
+        const int f = (int)(float)win[(rzo + oz) * g.pl + (y >> 1) * g.rp2 + (x >> 2) * 8 +
+                                      (y & 1) * 4 + (x & 3)];
+        sf += f;
+        sff += f * f;
+        stf += (tv[k] - c) * f;
+    }
+    sf = wave_sum(sf);
+    sff = wave_sum(sff);
+    stf = wave_sum(stf);
+    if (lane == 63) {
+        sm.sum[wave][0] = sf;
+        sm.sum[wave][1] = sff;
+        sm.sum[wave][2] = stf;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        long long tf = 0, tff = 0, ttf = 0;
+#pragma unroll
+        for (int i = 0; i < PB_NW; ++i) {
+            tf += sm.sum[i][0];
+            tff += sm.sum[i][1];
+            ttf += sm.sum[i][2];
+        }
+        const long long vf = (long long)N * tff - tf * tf;
+        const long long cv = (long long)N * ttf - sTc * tf;
+        const double v = (vt > 0 && vf > 0) ? (double)cv / sqrt((double)vt * (double)vf) : 0.0;
+        put(p, blk, ddx, ddy, ddz, (float)v);
+    }
 }
 
 // ------------------------------------------------------------------- host
@@ -695,11 +830,13 @@ typedef void (*mf_kernel_t)(MfParams);
 
 struct MfVariant {
     int b;
-    mf_kernel_t fn, surf;
-    int tt_bytes;
+    mf_kernel_t fn, wide, surf;
+    int nq, t_bytes;
 };
 
-#define MFV(B) {B, k_match_mfma<B, false>, k_match_mfma<B, true>, KGeo<B>::TT_BYTES}
+#define MFV(B)                                                                                  \
+    {B, k_match_mfma<B, false, false>, k_match_mfma<B, false, true>, k_match_mfma<B, true, true>, \
+     KGeo<B>::NQ, KGeo<B>::T_BYTES}
 const MfVariant kMfVariants[] = {MFV(3), MFV(5), MFV(7), MFV(9)};
 #undef MFV
 
@@ -709,10 +846,11 @@ const MfVariant *mf_variant(int b) {
     return nullptr;
 }
 
-// LDS sizes for the unclipped window of (b, w): rows padded so that rows
-// four apart (the bases' y step) start on different banks.
+// LDS sizes for the unclipped window of (b, w): the window (or, before it,
+// the block tables) and the tile-row table; clipped windows need no more.
 struct MfPlan {
-    int rp, pl;  // row and plane pitch (halves)
+    int rp;       // row pitch (halves)
+    int tab_off;  // byte offset of the tile-row table
     size_t lds;
 };
 
@@ -721,18 +859,18 @@ bool mf_plan(int b, int w, size_t limit, MfPlan *out) {
     if (!v) return false;
     const int d = 2 * w + 1;
     const int nbx = (d + 1 + 3) / 4, nby = (d + 3) / 4;  // x: one column of parity shift
-    const int gx = (b + 6) / 4, gyp = (b + 4) / 2;
+    const int gx = (b + 6) / 4;
     int rp = (4 * (nbx - 1) + 4 * gx + 7) / 8 * 8;  // whole 8-column chunks
     while (((rp * 8) % 256) < 48 || ((rp * 8) % 256) > 208) rp += 8;
-    const int py = 4 * (nby - 1) + 2 * gyp;
-    int pl = py * rp;
-    if (((pl * 2) % 256) == 0) pl += 8;
-    const int planes = d + b - 1;
-    if (planes >= 255) return false;  // the ranking keeps plane numbers in bytes
-    const size_t lds = (size_t)v->tt_bytes + (size_t)planes * pl * 2;
+    const int planes = d + b - 1;  // also the window's rows per plane, odd
+    if (planes >= 255) return false;  // tile rows keep base and phase numbers in bytes
+    const size_t win = (size_t)(planes * (planes + 1) + 2) * rp * 2;
+    const size_t tab = win > (size_t)v->t_bytes ? win : (size_t)v->t_bytes;
+    const size_t nrows = (size_t)nbx * nby * ((d + b - 1) / b);
+    const size_t lds = tab + (nrows + 15) / 16 * 16 * 4;
     if (lds + sizeof(MfSmall) > limit) return false;
     out->rp = rp;
-    out->pl = pl;
+    out->tab_off = (int)tab;
     out->lds = lds;
     return true;
 }
@@ -765,15 +903,22 @@ hipError_t launch_match_mfma(const MatchArgs &a, hipStream_t stream, float *surf
     p.first = 0;
     p.w = a.window;
     p.stats = static_cast<const StatU16 *>(a.stats);
+    p.nstat = (int64_t)a.ox * a.oy * (a.nz - a.block + 1);
     p.ox = a.ox;
     p.oy = a.oy;
     p.rp = pl.rp;
-    p.pl = pl.pl;
+    p.tab_off = pl.tab_off;
+    const int d = 2 * a.window + 1;
+    for (int px = 0; px < 2; ++px)
+        p.tz[px] = best_phase((d + px + 3) / 4 * ((d + 3) / 4), d, a.block, v->nq, PB_NW);
     p.disp = a.disp;
     p.ncc = a.ncc;
     p.conf = a.conf;
     p.surface = surface;
-    const mf_kernel_t fn = surface ? v->surf : v->fn;
+    // 32-bit record offsets reach the window's planes (and the masked ones
+    // past it) unless the volume's planes are very large
+    const bool wide = (int64_t)a.nx * a.ny * 8 * (2 * d + 2 * a.block) >= (1ll << 31);
+    const mf_kernel_t fn = surface ? v->surf : wide ? v->wide : v->fn;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds);
     if (e != hipSuccess) return e;
