@@ -60,9 +60,12 @@
 // b = 7: the latencies of one are hidden behind the matrix work of the other.
 // Measured against the earlier form (window staged raw in two rounds, centred
 // in place, operands from one table by 2-byte reads, 64-bit record addresses,
-// shuffle reductions): the search takes 0.178 ms instead of 0.356 on
-// 256x256x124 (b = 7, W = 10, 5508 blocks), 42.0 instead of 57.1 ms on 512x512x256
+// shuffle reductions): the search takes 0.160 ms instead of 0.356 on
+// 256x256x124 (b = 7, W = 10, 5508 blocks), 30.8 instead of 57.1 ms on 512x512x256
 // (b = 9, W = 12, 357,035 blocks); the keys and the winners are the same bits.
+// Of the 0.160 ms, 0.08 are the phases around the sweep (a variant without it),
+// 0.05 the matrix instructions; at b = 9 (one wavefront per SIMD) the sweep's
+// products and ranking add up.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -72,6 +75,7 @@
 #include <cstring>
 #include <limits>
 #include <type_traits>
+#include <utility>
 
 #include "nrr_internal.h"
 
@@ -116,7 +120,7 @@ struct MfParams {
     const StatU16 *stats;
     int64_t nstat;  // records of the table
     int ox, oy;
-    int rp;        // LDS window row pitch (halves)
+    int rp2;       // LDS pitch of a pair of window rows (halves)
     int tab_off;   // LDS byte offset of the tile-row table
     int tz[2];     // phase length of an unclipped window, x parity shift 0 / 1
     int32_t *disp;
@@ -263,7 +267,7 @@ __device__ inline BGeo block_geo(const MfParams &p, int64_t blk) {
     g.nby = (g.dyn + 3) / 4;
     g.cpr = (4 * (g.nbx - 1) + 4 * G::GX + 7) / 8;
     g.eyp = (g.ey + 1) & ~1;
-    g.rp2 = 2 * p.rp;
+    g.rp2 = p.rp2;
     g.pl = (g.eyp / 2) * g.rp2;
     return g;
 }
@@ -278,12 +282,19 @@ __device__ inline void block_tiles(const MfParams &p, BGeo &g) {
     g.ntiles = (g.nrows + 15) / 16;
 }
 
+// a / b for 0 <= a < 65536, b > 0: (a + 1/2) / b is at least 1 / (2 b) away
+// from the next integer, beyond the rounding of the reciprocal.
+__device__ inline int quotient(int a, int b) {
+    return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
+}
+
 // Tile rows as packed table entries: x base index, y base index, phase, and
 // whether the row exists (rows past the last repeat row 0, masked).
 __device__ inline uint32_t row_entry(const BGeo &g, int r) {
     const bool real = r < g.nrows;
     const int rr = real ? r : 0, nxy = g.nbx * g.nby;
-    const int ph = rr / nxy, xy = rr - ph * nxy, yi = xy / g.nbx, xi = xy - yi * g.nbx;
+    const int ph = quotient(rr, nxy), xy = rr - ph * nxy;
+    const int yi = quotient(xy, g.nbx), xi = xy - yi * g.nbx;
     return (uint32_t)xi | (uint32_t)yi << 8 | (uint32_t)ph << 16 | (real ? 1u << 24 : 0u);
 }
 
@@ -298,6 +309,17 @@ __device__ inline u32x4 shift_chunk(u32x4 v, int sh) {
     return sh & 4 ? u32x4{v[2], v[3], v[3], v[3]} : v;
 }
 
+// f(0) .. f(N - 1) with the index as a compile-time constant.
+template <typename F, int... I>
+__device__ __attribute__((always_inline)) inline void static_for_seq(
+    F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ __attribute__((always_inline)) inline void static_for(F &&f) {
+    static_for_seq(f, std::make_integer_sequence<int, N>());
+}
+
 // One unrolled block of B sweep steps t0 .. t0 + B - 1 (t0 a multiple of B):
 // MODE 0 is the first block (plane s of the block only reaches displacement
 // planes tau = t - s >= 0), MODE 1 a full block, MODE 2 the last one (B - 1
@@ -308,8 +330,8 @@ __device__ __attribute__((always_inline)) inline void sweep_block(
     int t0, float4v (&acc)[B], const half8 (&bop)[B][NQ], half8 (&aop)[NQ], LoadA load_a,
     Rank rank) {
     constexpr int STEPS = MODE == 2 ? B - 1 : B;
-#pragma unroll
-    for (int u = 0; u < STEPS; ++u) {
+    static_for<STEPS>([&](auto uc) {
+        constexpr int u = decltype(uc)::value;
         const int t = t0 + u;
         // consecutive products feed different accumulators, and the plane
         // completed by this step (block plane B - 1) is fed first in each
@@ -328,10 +350,10 @@ __device__ __attribute__((always_inline)) inline void sweep_block(
         // the next plane's operand replaces this one (its reads are issued
         // behind the products above and complete while the ranking runs)
         load_a(t + 1, aop);
-        const int fs = (u + 1) % B;
-        if (MODE != 0 || u == B - 1) rank(acc[fs], t - (B - 1));
+        constexpr int fs = (u + 1) % B;
+        if (MODE != 0 || u == B - 1) rank(acc[fs], t - (B - 1), std::integral_constant<int, fs>());
         acc[fs] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-    }
+    });
 }
 
 // Toeplitz B operands of this lane for every block plane and K chunk, from
@@ -346,14 +368,15 @@ __device__ __attribute__((always_inline)) inline void build_bop(
     for (int q = 0; q < G::NQ; ++q) {
         const int g = 4 * q + grp;
         const bool real = g < G::NG;
-        const int gx = real ? g % G::GX : 0, gy = real ? g / G::GX : 0;
-        const _Float16 *tr = tt + oa * G::TCOPY + (2 * gy - ob + OFF) * G::TXW + 4 * gx;
+        // groups past the last read two of the zero rows
+        const int gx = g % G::GX, gy = g / G::GX;
+        const _Float16 *tr =
+            tt + oa * G::TCOPY + (real ? (2 * gy - ob + OFF) * G::TXW + 4 * gx : 0);
 #pragma unroll
         for (int s = 0; s < B; ++s) {
             const half4 lo = *reinterpret_cast<const half4 *>(tr + s * G::TYW * G::TXW);
             const half4 hi = *reinterpret_cast<const half4 *>(tr + (s * G::TYW + 1) * G::TXW);
-            const half8 v = half8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            bop[s][q] = real ? v : half8{};
+            bop[s][q] = half8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         }
     }
 }
@@ -449,10 +472,15 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
             abase += t <= alim ? g.pl : 0;
             read_a(aop);
         };
-        // statistics records of the four output rows, loaded one displacement
-        // plane ahead of their ranking
-        StatU16 rec0[4];
-        auto fetch = [&](int tau, StatU16 (&rec)[4]) {
+        // statistics records of the four output rows, loaded AHEAD displacement
+        // planes before their ranking, in a ring indexed like the accumulators
+        // (AHEAD of its B slots are live)
+        // (a record's round trip is longer than a step: one plane ahead left the
+        // ramps waiting, 42.4 against 32.6 ms on the dense workload; at b = 7 the
+        // registers allow three)
+        constexpr int AHEAD = B == 7 ? 3 : B;
+        StatU16 rec[B][4];
+        auto fetch = [&](int tau, StatU16 (&rec)[4]) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if constexpr (WIDE) {
@@ -477,8 +505,10 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
             rk[i] = -INFINITY;
             rt[i] = -1;
         }
-        // ranking of displacement plane tau, then the records of tau + 1
-        auto rank = [&](const float4v &c4, int tau) {
+        // ranking of displacement plane tau, then the records of tau + AHEAD
+        auto rank = [&](const float4v &c4, int tau, auto slot) __attribute__((always_inline)) {
+            constexpr int S = decltype(slot)::value;
+            const StatU16(&rec0)[4] = rec[S];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float sts = __builtin_fmaf(fST, (float)rec0[i].s, fshift);
@@ -491,9 +521,9 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
                     if (tau < lim[i]) p.surface[blk * side2 * side + oidx[i] + tau * side2] =
                         key * inv_vt;
             }
-            fetch(tau + 1, rec0);
+            fetch(tau + AHEAD, rec[(S + AHEAD) % B]);
         };
-        fetch(0, rec0);
+        static_for<AHEAD>([&](auto k) { fetch(decltype(k)::value, rec[decltype(k)::value]); });
         half8 aop[NQ];
         read_a(aop);
         sweep_block<B, NQ, 0>(0, acc, bop, aop, load_a, rank);
@@ -508,8 +538,10 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
 // A centre: the block's rounded mean, clamped so every |v - c| <= 2048 over
 // the values of range [vmin, vmax] (12-bit values: the interval is never
 // empty).
-__device__ inline int centre(long long st, int n, int vmin, int vmax) {
-    return min(max((int)llrint((double)st / (double)n), vmax - 2048), vmin + 2048);
+template <int N>
+__device__ inline int centre(uint32_t st, int vmin, int vmax) {
+    static_assert(N % 2 == 1, "an odd count: the mean is never half way between integers");
+    return min(max((int)((2 * st + N) / (2 * N)), vmax - 2048), vmin + 2048);
 }
 
 // 16 bytes of raw 12-bit voxels -> fp16 (v - c), exact for |v - c| <= 2048.
@@ -567,64 +599,65 @@ __global__ __launch_bounds__(64 * PB_NW, B == 3 ? 4 : B == 5 ? 3 : B == 7 ? 2 : 
     // Thread t copies chunk column xc of every R-th row of the window (rows
     // (z, y) in order, R even: an LDS row pair per two rows), so its addresses
     // advance by additions.  Threads and steps past the last row repeat it.
-    // Rows beyond KREG steps (half windows above 13 or so) are read again
-    // when their centre is known.
+    // Steps beyond KREG (half windows above 12 or so) are read again when
+    // their centre is known.
     constexpr int KREG = B == 3 ? 8 : B == 5 ? 16 : B == 7 ? 20 : 32;
+    using Off = typename std::conditional<WIDE, int64_t, uint32_t>::type;
+    const bool odd = (p.nx & 1) != 0;
     const int R = (NT / g.cpr) & ~1, rows = g.ez * g.eyp;
     const int kn = (rows + R - 1) / R;
-    const int xc = tid % g.cpr;
-    const uint16_t *wb = p.flt + ((int64_t)g.wz0 * p.ny + g.wy0) * p.nx + g.wx0 - g.px;
-    using Off = typename std::conditional<WIDE, int64_t, uint32_t>::type;
+    const int rz = R / g.eyp, ry = R - rz * g.eyp;
+    const int xc = tid - quotient(tid, g.cpr) * g.cpr;
     const Off nx_ = (Off)p.nx, nxy_ = (Off)p.nx * (Off)p.ny;
+    const Off inc = (Off)rz * nxy_ + (Off)ry * nx_, wrap = nxy_ - (Off)g.eyp * nx_;
+    const Off last = (Off)(g.ez - 1) * nxy_ + (Off)(g.ey - 1) * nx_ + (Off)(8 * xc);
+    const uint16_t *wb = p.flt + ((int64_t)g.wz0 * p.ny + g.wy0) * p.nx + g.wx0 - g.px;
     // A chunk that would run past the volume's last voxel is read 8 voxels
     // before the end and moved into place when it is used (`edge`, uniform:
     // the window has such chunks).
-    const int64_t tail = (int64_t)p.nx * p.ny * p.nz - 8 - (wb - p.flt);
+    const int64_t end = (int64_t)p.nx * p.ny * p.nz - 8 - (wb - p.flt);
     const bool edge =
-        (int64_t)(g.ez - 1) * p.ny * p.nx + (int64_t)(g.ey - 1) * p.nx + 8 * (g.cpr - 1) > tail;
-    const Off tail_ = edge ? (Off)tail : std::numeric_limits<Off>::max();
-    const Off last = (Off)(g.ez - 1) * nxy_ + (Off)(g.ey - 1) * nx_ + (Off)(8 * xc);
+        ((int64_t)(g.ez - 1) * p.ny + (g.ey - 1)) * p.nx + 8 * (g.cpr - 1) > end;
+    const Off tail = edge ? (Off)end : std::numeric_limits<Off>::max();
     struct Walk {
-        int r, z, y;
+        int r, y;  // row, and its row in its plane
+        Off e;     // its chunk's first voxel, from wb
     };
-    const int rz = R / g.eyp, ry = R - rz * g.eyp;
     auto walk_start = [&]() {
-        Walk s;
-        s.r = tid / g.cpr;
-        if (s.r >= R) s.r = rows;  // idle thread: repeats the last row
-        s.z = s.r / g.eyp;
-        s.y = s.r - s.z * g.eyp;
-        return s;
+        Walk a;
+        a.r = quotient(tid, g.cpr);
+        if (a.r >= R) a.r = rows;  // idle thread: repeats the last row
+        const int z = quotient(a.r, g.eyp);
+        a.y = a.r - z * g.eyp;
+        a.e = (Off)z * nxy_ + (Off)a.y * nx_ + (Off)(8 * xc);
+        return a;
     };
-    auto walk_next = [&](Walk &s) {
-        s.r += R;
-        s.z += rz;
-        s.y += ry;
-        const bool wrap = s.y >= g.eyp;
-        s.y -= wrap ? g.eyp : 0;
-        s.z += wrap ? 1 : 0;
+    auto walk_next = [&](Walk &a) {
+        a.r += R;
+        a.y += ry;
+        const bool over = a.y >= g.eyp;
+        a.y -= over ? g.eyp : 0;
+        a.e += inc + (over ? wrap : (Off)0);
     };
-    auto walk_elem = [&](const Walk &s) {
-        return s.r < rows ? (Off)s.z * nxy_ + (Off)min(s.y, g.ey - 1) * nx_ + (Off)(8 * xc) : last;
+    auto walk_elem = [&](const Walk &a) {
+        const Off e = a.e - (a.y >= g.ey ? nx_ : (Off)0);  // the padding row repeats the last
+        return a.r < rows ? e : last;
     };
-    auto walk_load = [&](const Walk &s) {
-        const u32x4u v = *reinterpret_cast<const u32x4u *>(wb + min(walk_elem(s), tail_));
-        u32x4 o;
-        __builtin_memcpy(&o, &v, 16);
-        return o;
+    auto walk_load = [&](const Walk &a) {
+        return __builtin_bit_cast(
+            u32x4, *reinterpret_cast<const u32x4u *>(wb + min(walk_elem(a), tail)));
     };
-    const bool odd = (p.nx & 1) != 0;
-    auto walk_fix = [&](u32x4 v, const Walk &s) {  // the chunk of an `edge` window
-        const int64_t sh = (int64_t)walk_elem(s) - tail;
+    auto walk_fix = [&](u32x4 v, const Walk &a) {  // the chunk of an `edge` window
+        const int64_t sh = (int64_t)walk_elem(a) - end;
         return sh > 0 ? shift_chunk(v, (int)min(sh, (int64_t)(odd ? 7 : 6))) : v;
     };
     u32x4 w[KREG];
     Walk at = walk_start();
 #pragma unroll
-    for (int k4 = 0; k4 < KREG; k4 += 4)
-        if (k4 < kn) {
+    for (int k2 = 0; k2 < KREG; k2 += 2)
+        if (k2 < kn) {
 #pragma unroll
-            for (int k = k4; k < k4 + 4; ++k) {
+            for (int k = k2; k < k2 + 2; ++k) {
                 w[k] = walk_load(at);
                 walk_next(at);
             }
@@ -632,7 +665,11 @@ __global__ __launch_bounds__(64 * PB_NW, B == 3 ? 4 : B == 5 ? 3 : B == 7 ? 2 : 
 
     // ---- tile rows, zeroed block tables
     block_tiles<B, PB_NW>(p, g);
-    for (int r = tid; r < 16 * g.ntiles; r += NT) rowtab[r] = row_entry(g, r);
+    // row r of a tile takes base 4 (r mod 4) + r / 4 of its 16: a lane group's
+    // i-th output rows are then four x-neighbouring bases, whose records are
+    // 128 contiguous bytes per y
+    for (int r = tid; r < 16 * g.ntiles; r += NT)
+        rowtab[r] = row_entry(g, (r & ~15) | (r & 3) << 2 | (r >> 2 & 3));
     for (int i = tid; i < G::T_BYTES / 16; i += NT)
         *reinterpret_cast<u32x4 *>(lds + 16 * i) = u32x4{0, 0, 0, 0};
 
@@ -670,7 +707,7 @@ __global__ __launch_bounds__(64 * PB_NW, B == 3 ? 4 : B == 5 ? 3 : B == 7 ? 2 : 
         if (tid == 0) put(p, blk, g.lox, g.loy, g.loz, 0.0f);
         return;
     }
-    const int c = centre(st, N, mm[0], 4095 - mm[1]);  // c_T
+    const int c = centre<N>((uint32_t)st, mm[0], 4095 - mm[1]);  // c_T
 #pragma unroll
     for (int k = 0; k < TPT; ++k) {
         const int o = tid + k * NT;
@@ -687,40 +724,49 @@ __global__ __launch_bounds__(64 * PB_NW, B == 3 ? 4 : B == 5 ? 3 : B == 7 ? 2 : 
 
     // ---- value range of the staged voxels, then c_F.  The range covers the
     // window and, for even row lengths, the few neighbouring voxels its
-    // padded rows pick up.
+    // padded rows pick up (odd row lengths: only the window's own columns).
     u16x2 mn2 = {0xffff, 0xffff}, mx2 = {0, 0};
-    uint32_t keep[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-    if (odd) {  // only the window's own columns
-        const int nv = g.ex - 8 * xc;  // this thread's columns inside it
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            keep[j] = (2 * j < nv ? 0xffffu : 0u) | (2 * j + 1 < nv ? 0xffff0000u : 0u);
-    }
-    auto range = [&](const u32x4 &v) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            mn2 = __builtin_elementwise_min(mn2, __builtin_bit_cast(u16x2, v[j] | ~keep[j]));
-            mx2 = __builtin_elementwise_max(mx2, __builtin_bit_cast(u16x2, v[j] & keep[j]));
-        }
-    };
     const Walk rest = at;
     if (edge) {
         Walk s = walk_start();
 #pragma unroll
-        for (int k = 0; k < KREG; ++k, walk_next(s)) w[k] = walk_fix(w[k], s);
+        for (int k = 0; k < KREG; ++k, walk_next(s))
+            if (k < kn) w[k] = walk_fix(w[k], s);
     }
     auto reload = [&]() {
         u32x4 v = walk_load(at);
         if (edge) v = walk_fix(v, at);
         return v;
     };
+    auto ranges = [&](auto &&use) {
 #pragma unroll
-    for (int k4 = 0; k4 < KREG; k4 += 4)
-        if (k4 < kn) {
+        for (int k = 0; k < KREG; ++k)
+            if (k < kn) use(w[k]);
+        for (int k = KREG; k < kn; ++k, walk_next(at)) use(reload());
+    };
+    if (odd) {
+        const int nv = g.ex - 8 * xc;  // this thread's columns inside the window
+        uint32_t keep[4];
 #pragma unroll
-            for (int k = k4; k < k4 + 4; ++k) range(w[k]);
-        }
-    for (int k = KREG; k < kn; ++k, walk_next(at)) range(reload());
+        for (int j = 0; j < 4; ++j)
+            keep[j] = (2 * j < nv ? 0xffffu : 0u) | (2 * j + 1 < nv ? 0xffff0000u : 0u);
+        ranges([&](const u32x4 &v) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                mn2 = __builtin_elementwise_min(mn2, __builtin_bit_cast(u16x2, v[j] | ~keep[j]));
+                mx2 = __builtin_elementwise_max(mx2, __builtin_bit_cast(u16x2, v[j] & keep[j]));
+            }
+        });
+    } else {
+        ranges([&](const u32x4 &v) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t x = v[j];  // a bit cast of the element itself reads element 0
+                mn2 = __builtin_elementwise_min(mn2, __builtin_bit_cast(u16x2, x));
+                mx2 = __builtin_elementwise_max(mx2, __builtin_bit_cast(u16x2, x));
+            }
+        });
+    }
     const int vmn = min((int)mn2[0], (int)mn2[1]), vmx = max((int)mx2[0], (int)mx2[1]);
     mm = wave_min(u16x2{(uint16_t)min(vmn, 4095), (uint16_t)(4095 - vmx)});
     if (lane == 63) sm.wm[wave] = __builtin_bit_cast(uint32_t, mm);
@@ -729,31 +775,29 @@ __global__ __launch_bounds__(64 * PB_NW, B == 3 ? 4 : B == 5 ? 3 : B == 7 ? 2 : 
 #pragma unroll
     for (int i = 0; i < PB_NW; ++i)
         mm = __builtin_elementwise_min(mm, __builtin_bit_cast(u16x2, sm.wm[i]));
-    const int cf = centre(st, N, mm[0], 4095 - mm[1]);  // c_F
+    const int cf = centre<N>((uint32_t)st, mm[0], 4095 - mm[1]);  // c_F
 
     // ---- the window as fp16 (v - c_F); a pair of rows past the last plane,
     // which the lowest bases read against zeros, is cleared
     {
         const i16x2 c2 = {(short)cf, (short)cf};
-        const int end = ((rows - 1) >> 1) * g.rp2 + 4 + 16 * xc;  // the last row's (rows is even)
-        auto store = [&](const u32x4 &v, int r) {
+        auto store = [&](const u32x4 &v, int r, int d) {
             const u32x4 h = centre_chunk(v, c2);
-            _Float16 *d = win + (r < rows ? (r >> 1) * g.rp2 + (r & 1) * 4 + 16 * xc : end);
-            *reinterpret_cast<u32x2 *>(d) = u32x2{h[0], h[1]};
-            *reinterpret_cast<u32x2 *>(d + 8) = u32x2{h[2], h[3]};
+            _Float16 *q = win + (r < rows ? d : (rows / 2 - 1) * g.rp2 + 4 + 16 * xc);
+            *reinterpret_cast<u32x2 *>(q) = u32x2{h[0], h[1]};
+            *reinterpret_cast<u32x2 *>(q + 8) = u32x2{h[2], h[3]};
         };
-        int r = tid / g.cpr;
+        const int step = (R >> 1) * g.rp2;
+        int r = quotient(tid, g.cpr);
+        int d = (r >> 1) * g.rp2 + (r & 1) * 4 + 16 * xc;
         if (r >= R) r = rows;
 #pragma unroll
-        for (int k4 = 0; k4 < KREG; k4 += 4)
-            if (k4 < kn) {
-#pragma unroll
-                for (int k = k4; k < k4 + 4; ++k, r += R) store(w[k], r);
-            }
+        for (int k = 0; k < KREG; ++k, r += R, d += step)
+            if (k < kn) store(w[k], r, d);
         at = rest;
-        for (int k = KREG; k < kn; ++k, walk_next(at)) store(reload(), at.r);
+        for (int k = KREG; k < kn; ++k, walk_next(at), d += step) store(reload(), at.r, d);
         for (int i = tid; i < g.rp2 / 8; i += NT)
-            *reinterpret_cast<u32x4 *>(win + (rows >> 1) * g.rp2 + 8 * i) = u32x4{0, 0, 0, 0};
+            *reinterpret_cast<u32x4 *>(win + g.ez * g.pl + 8 * i) = u32x4{0, 0, 0, 0};
     }
     __syncthreads();
 
@@ -849,7 +893,7 @@ const MfVariant *mf_variant(int b) {
 // LDS sizes for the unclipped window of (b, w): the window (or, before it,
 // the block tables) and the tile-row table; clipped windows need no more.
 struct MfPlan {
-    int rp;       // row pitch (halves)
+    int rp2;      // pitch of a pair of rows (halves)
     int tab_off;  // byte offset of the tile-row table
     size_t lds;
 };
@@ -860,16 +904,16 @@ bool mf_plan(int b, int w, size_t limit, MfPlan *out) {
     const int d = 2 * w + 1;
     const int nbx = (d + 1 + 3) / 4, nby = (d + 3) / 4;  // x: one column of parity shift
     const int gx = (b + 6) / 4;
-    int rp = (4 * (nbx - 1) + 4 * gx + 7) / 8 * 8;  // whole 8-column chunks
-    while (((rp * 8) % 256) < 48 || ((rp * 8) % 256) > 208) rp += 8;
+    const int cols = (4 * (nbx - 1) + 4 * gx + 7) / 8 * 8;  // whole 8-column chunks
+    int rp2 = 2 * cols;
     const int planes = d + b - 1;  // also the window's rows per plane, odd
     if (planes >= 255) return false;  // tile rows keep base and phase numbers in bytes
-    const size_t win = (size_t)(planes * (planes + 1) + 2) * rp * 2;
+    const size_t win = (size_t)(planes * (planes + 1) / 2 + 1) * rp2 * 2;
     const size_t tab = win > (size_t)v->t_bytes ? win : (size_t)v->t_bytes;
     const size_t nrows = (size_t)nbx * nby * ((d + b - 1) / b);
     const size_t lds = tab + (nrows + 15) / 16 * 16 * 4;
     if (lds + sizeof(MfSmall) > limit) return false;
-    out->rp = rp;
+    out->rp2 = rp2;
     out->tab_off = (int)tab;
     out->lds = lds;
     return true;
@@ -906,7 +950,7 @@ hipError_t launch_match_mfma(const MatchArgs &a, hipStream_t stream, float *surf
     p.nstat = (int64_t)a.ox * a.oy * (a.nz - a.block + 1);
     p.ox = a.ox;
     p.oy = a.oy;
-    p.rp = pl.rp;
+    p.rp2 = pl.rp2;
     p.tab_off = pl.tab_off;
     const int d = 2 * a.window + 1;
     for (int px = 0; px < 2; ++px)
@@ -917,7 +961,7 @@ hipError_t launch_match_mfma(const MatchArgs &a, hipStream_t stream, float *surf
     p.surface = surface;
     // 32-bit record offsets reach the window's planes (and the masked ones
     // past it) unless the volume's planes are very large
-    const bool wide = (int64_t)a.nx * a.ny * 8 * (2 * d + 2 * a.block) >= (1ll << 31);
+    const bool wide = (int64_t)a.nx * a.ny * 8 * (2 * d + 3 * a.block) >= (1ll << 31);
     const mf_kernel_t fn = surface ? v->surf : wide ? v->wide : v->fn;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds);
