@@ -948,7 +948,7 @@ nrr_status nrr_tune_match(const void *ref, const void *flt, nrr_dtype dtype,
     if (bi < 0) return fail(NRR_ERR_UNSUPPORTED, "no compiled shape for block %d window %d", block,
                             window);
     // leave the outputs as the chosen shape computes them
-    nrr::set_tuned_shape(dtype, block, window, shapes[bi]);
+    nrr::set_tuned_shape(dtype, block, window, shapes[bi], false);
     if ((e = nrr::launch_match(dtype, a, st, &shapes[bi])) != hipSuccess)
         return hip_status(e, "block match launch");
     if (best) {
@@ -1000,7 +1000,7 @@ nrr_status nrr_set_tuned_shape(nrr_dtype dtype, int32_t block, int32_t window,
         return fail(NRR_ERR_UNSUPPORTED,
                     "shape (arith %d, %dx%d, %d threads, pf %d) is not compiled for block %d "
                     "window %d", t.arith, t.rx, t.ry, t.nt, t.pf, block, window);
-    nrr::set_tuned_shape(dtype, block, window, t);
+    nrr::set_tuned_shape(dtype, block, window, t, true);
     return ok();
 }
 

@@ -45,6 +45,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "mfma_filter.h"
 #include "nrr_internal.h"
 
 namespace nrr {
@@ -443,6 +444,12 @@ __device__ __attribute__((always_inline)) inline void dot2_cross(
         }
 }
 
+// Ranking key of float data from a cross term and its record.
+__device__ inline double key_f32_of(double dN, float x, double tsum, const StatF32 &rec, float c) {
+    const double cov = dN * (double)x - tsum * (rec.s - dN * (double)c);
+    return cov * rec.r;
+}
+
 // Ranking of a tile: key = N*cov * rsqrt(N*varF), proportional to the NCC for
 // the block at hand; keeps the largest key and, among equal keys, the
 // smallest shift index (irow + j*side + i).  Displacements past the valid
@@ -466,8 +473,7 @@ __device__ __attribute__((always_inline)) inline void rank_tile(
                                   -tsum * (SHIFT ? (double)rec[i][j].s + fshift : (double)rec[i][j].s));
                 key = (float)cov * rec[i][j].r;
             } else {
-                const double cov = dN * (double)xacc[i][j] - tsum * (rec[i][j].s - dN * (double)c);
-                key = cov * rec[i][j].r;
+                key = key_f32_of(dN, xacc[i][j], tsum, rec[i][j], c);
             }
             const bool take = valid && key > tk;  // ties keep the smaller index
             tk = take ? key : tk;
@@ -491,7 +497,8 @@ struct Small {
 // so a caller that reuses LDS for another block synchronises first.
 template <typename Vox, int ARITH, int B, int RX, int RY, int NT, bool PF, bool SURF = false>
 __device__ __attribute__((always_inline)) inline void match_one(const Params &p, int64_t blk,
-                                                                unsigned char *lds, Small &sm) {
+                                                                unsigned char *lds, Small &sm,
+                                                                int tid) {
     constexpr bool U16 = sizeof(Vox) == 2;
     static_assert(ARITH == FMA || U16, "DOT2 needs 12-bit data");
     constexpr int H = (B - 1) / 2, N = B * B * B, BP = (B + 3) & ~3;
@@ -508,7 +515,6 @@ __device__ __attribute__((always_inline)) inline void match_one(const Params &p,
     static_assert(NT <= 1024, "reduction scratch is sized for 16 wavefronts");
 
     const Geom g = make_geom(p, blk, H);
-    const int tid = threadIdx.x;
     if (!g.inside) {
         if (tid == 0) write_result(p, blk, 0, 0, 0, NAN);
         return;
@@ -848,7 +854,7 @@ __global__ __launch_bounds__(NT) void k_match(Params p) {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ Small sm;
     match_one<Vox, ARITH, B, RX, RY, NT, PF>(p, p.first + xcd_block(blockIdx.x, gridDim.x), lds,
-                                             sm);
+                                             sm, threadIdx.x);
 }
 
 // The same search also writing the ranking NCC of every valid displacement
@@ -858,9 +864,192 @@ __global__ __launch_bounds__(NT) void k_match_surf(Params p) {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ Small sm;
     match_one<Vox, ARITH, B, RX, RY, NT, PF, true>(
-        p, p.first + xcd_block(blockIdx.x, gridDim.x), lds, sm);
+        p, p.first + xcd_block(blockIdx.x, gridDim.x), lds, sm, threadIdx.x);
 }
 
+
+// The float search behind the matrix-core filter (mfma_filter.h): the same
+// winner, bit for bit, as match_one's FMA form, which it calls for the blocks
+// the filter leaves.  Every thread of the 256-thread workgroup calls it.
+// What bounds the FMA form is its vector issue (30% of the FP32 peak at
+// b = 7, W = 10); the filter moves the products to fp16 matrix instructions
+// and leaves the vector units one bound per displacement.  5508 blocks of
+// 256x256x124 float voxels, b = 7, W = 10: 0.29 ms against 0.66.  It waits for
+// memory about as the 12-bit matrix-core search does, once per block.
+template <int B>
+struct FiltShape {
+    static constexpr int NQ = ((B + 6) / 4 * ((B + 4) / 2) + 3) / 4;
+    static constexpr int KREG = B == 5 ? 20 : B == 7 ? 24 : 40;  // window chunks held per thread
+    static constexpr int AHEAD = B == 7 ? 3 : B == 5 ? 5 : 5;    // planes between a record's load and its use
+    static constexpr int WAVES = B == 9 ? 1 : 2;   // wavefronts per SIMD the registers allow
+};
+
+template <int B>
+__device__ __attribute__((always_inline)) inline void match_one_filtered(
+    const Params &p, const filt::Args &fa, int64_t blk, unsigned char *lds, Small &sm,
+    filt::Small &fs) {
+    using S = FiltShape<B>;
+    constexpr int H = (B - 1) / 2, N = B * B * B, BP = (B + 3) & ~3, NT = 256;
+    constexpr int TP_WORDS = B * B * BP;
+    constexpr int TPT = (N + NT - 1) / NT, TPI = (TP_WORDS + NT - 1) / NT;
+    const Geom g = make_geom(p, blk, H);
+    const int tid = threadIdx.x;
+    if (!g.inside) {
+        if (tid == 0) write_result(p, blk, 0, 0, 0, NAN);
+        return;
+    }
+    const float *ref = static_cast<const float *>(p.ref);
+    const float *flt = static_cast<const float *>(p.flt);
+    const int64_t nxy = (int64_t)p.nx * p.ny;
+    const int64_t rbase = (int64_t)(g.cz - H) * nxy + (int64_t)(g.cy - H) * p.nx + (g.cx - H);
+    // the block's voxels in the order of the FMA form's two sums over them,
+    // then the window, all in flight together
+    float tv[TPT], tw[TPI];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) {
+        const int o = min(tid + k * NT, N - 1);
+        const int oz = o / (B * B), oy = (o / B) % B, ox = o % B;
+        tv[k] = ref[rbase + oz * nxy + (int64_t)oy * p.nx + ox];
+    }
+#pragma unroll
+    for (int k = 0; k < TPI; ++k) {
+        const int i = tid + k * NT;
+        const int oz = min(i / (B * BP), B - 1), oy = (i / BP) % B, ox = min(i % BP, B - 1);
+        tw[k] = ref[rbase + oz * nxy + (int64_t)oy * p.nx + ox];
+    }
+    filt::Geo fg = filt::geometry<float>(fa, g.cx, g.cy, g.cz);
+    filt::Walk<float> walk0;
+    walk0.start(fa, fg);
+    filt::Walk<float> at = walk0;
+    filt::u32x4 w[S::KREG];
+#pragma unroll
+    for (int k2 = 0; k2 < S::KREG; k2 += 2)
+        if (k2 < walk0.kn) {
+#pragma unroll
+            for (int k = k2; k < k2 + 2; ++k) {
+                w[k] = at.load(fa, fg);
+                at.next(fg);
+            }
+        }
+    filt::open_block(fa, fg, lds, fs);
+
+    // T^ = T - mean as floats, its sums: the FMA form's operations
+    double sd[1] = {0.0};
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (tid + k * NT < N) sd[0] += (double)tv[k];
+    wg_sum<NT, double, 1>(sd, sm.redd);
+    const double tmean = sd[0] / (double)N;
+    const float c = (float)tmean;
+    float *tf = reinterpret_cast<float *>(lds + fa.z.t_off);
+    double ctr[2] = {0.0, 0.0};
+    uint32_t tmax = 0;
+#pragma unroll
+    for (int k = 0; k < TPI; ++k) {
+        const int i = tid + k * NT;
+        const int oz = i / (B * BP), oy = (i / BP) % B, ox = i % BP;
+        if (i >= TP_WORDS || ox >= B) continue;
+        const float v = (float)((double)tw[k] - tmean);
+        ctr[0] += (double)v;
+        ctr[1] += (double)v * (double)v;
+        tmax = max(tmax, __float_as_uint(v) & 0x7fffffffu);
+        tf[(oz * B + oy) * B + ox] = v;
+    }
+    tmax = filt::wave_max(tmax);
+    if ((tid & 63) == 63) fs.wmax[tid >> 6] = tmax;
+    wg_sum<NT, double, 2>(ctr, sm.redd);  // its barriers publish tf, the tables and the maxima
+    tmax = max(max(fs.wmax[0], fs.wmax[1]), max(fs.wmax[2], fs.wmax[3]));
+    tmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)tmax);
+    if (!(ctr[1] > 0.0)) {  // flat block
+        if (tid == 0) write_result(p, blk, g.lox, g.loy, g.loz, 0.0f);
+        __syncthreads();  // the maxima are read
+        return;
+    }
+    const double dN = (double)N, tsum = ctr[0];
+    const int side = 2 * p.w + 1;
+    const StatF32 *table = static_cast<const StatF32 *>(p.stats);
+    // the FMA form's key of shift index idx: lane oz sums block plane oz, the
+    // plane sums are added in order
+    auto exact = [&](int idx, int oz, double &key) {
+        const int id = max(idx, 0);
+        const int iz = id / (side * side), ir = id - iz * side * side, iy = ir / side,
+                  ix = ir - iy * side;
+        const int64_t o0 = (int64_t)(g.cz - H + iz - p.w) * nxy +
+                           (int64_t)(g.cy - H + iy - p.w) * p.nx + (g.cx - H + ix - p.w);
+        float acc = 0.0f;
+        if (idx >= 0) {
+            const float *f = flt + o0 + oz * nxy;
+            const float *t = tf + oz * B * B;
+#pragma unroll
+            for (int oy = 0; oy < B; ++oy)
+#pragma unroll
+                for (int ox = 0; ox < B; ++ox)
+                    acc = __builtin_fmaf(f[(int64_t)oy * p.nx + ox] - c, t[oy * B + ox], acc);
+        }
+        float x = 0.0f;
+        const int first = (tid & 63) - oz;
+#pragma unroll
+        for (int j = 0; j < B; ++j) x += __shfl(acc, (first + j) & 63);
+        if (idx >= 0) {
+            const StatF32 rec =
+                table[((int64_t)(g.cz - H + iz - p.w) * p.oy + (g.cy - H + iy - p.w)) * p.ox +
+                      (g.cx - H + ix - p.w)];
+            key = key_f32_of(dN, x, tsum, rec, c);
+        }
+    };
+    int best = 0;
+    const bool found = filt::search<float, double, B, S::NQ, S::KREG, S::AHEAD, B>(
+        fa, fg, lds, fs, w, walk0, at, c, (float)sqrt(ctr[1]), tmax, exact, best);
+    // an opaque copy of the thread index: what follows recomputes its
+    // addresses instead of holding them in registers through the sweep
+    int t2 = tid;
+    asm volatile("" : "+v"(t2));
+    if (!found) {  // uniform
+        __syncthreads();
+        match_one<float, FMA, B, 4, 4, NT, false>(p, blk, lds, sm, t2);
+        return;
+    }
+    const int ddx = best % side - p.w, ddy = (best / side) % side - p.w,
+              ddz = best / (side * side) - p.w;
+    const int64_t fbase = rbase + ddz * nxy + (int64_t)ddy * p.nx + ddx;
+    float fv[TPT];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) {
+        const int o = min(t2 + k * NT, N - 1);
+        const int oz = o / (B * B), oy = (o / B) % B, ox = o % B;
+        fv[k] = flt[fbase + oz * nxy + (int64_t)oy * p.nx + ox];
+    }
+    double m2[1] = {0.0};
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (t2 + k * NT < N) m2[0] += (double)fv[k];
+    wg_sum<NT, double, 1>(m2, sm.redd);
+    const double fmean = m2[0] / (double)N;
+    double q[3] = {0.0, 0.0, 0.0};  // A, B, X of the two-pass Pearson form
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (t2 + k * NT < N) {
+            const double a = (double)tv[k] - tmean, b = (double)fv[k] - fmean;
+            q[0] += a * a;
+            q[1] += b * b;
+            q[2] += a * b;
+        }
+    wg_sum<NT, double, 3>(q, sm.redd);
+    if (tid == 0) {
+        const double ab = q[0] * q[1];
+        const double v = ab > 0.0 ? q[2] / sqrt(ab) : 0.0;
+        write_result(p, blk, ddx, ddy, ddz, (float)v);
+    }
+}
+
+template <int B>
+__global__ __launch_bounds__(256, FiltShape<B>::WAVES) void k_match_f32_filtered(Params p,
+                                                                                 filt::Args fa) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ Small sm;
+    __shared__ filt::Small fs;
+    match_one_filtered<B>(p, fa, p.first + xcd_block(blockIdx.x, gridDim.x), lds, sm, fs);
+}
 
 // ------------------------------------------------------------ batched search
 //
@@ -904,12 +1093,12 @@ __global__ __launch_bounds__(256) void k_match_batch(const BatchSet *__restrict_
         const int64_t blk = it - S.first_item;
         if constexpr (sizeof(Vox) == 4) {
 #define CASE_F32(ID, B, RX, RY, PF) \
-    case ID: match_one<float, FMA, B, RX, RY, 256, PF>(p, blk, lds, sm); break;
+    case ID: match_one<float, FMA, B, RX, RY, 256, PF>(p, blk, lds, sm, threadIdx.x); break;
             switch (S.variant) { BATCH_F32(CASE_F32) }
 #undef CASE_F32
         } else {
 #define CASE_U16(ID, B, RX, RY, PF) \
-    case ID: match_one<uint16_t, DOT2, B, RX, RY, 256, PF>(p, blk, lds, sm); break;
+    case ID: match_one<uint16_t, DOT2, B, RX, RY, 256, PF>(p, blk, lds, sm, threadIdx.x); break;
             switch (S.variant) { BATCH_U16(CASE_U16) }
 #undef CASE_U16
         }
@@ -1051,6 +1240,7 @@ struct TunedEntry {
     nrr_dtype dtype;
     int b, w;
     TileShape sh;
+    bool pinned;  // set by the caller, not by the tuner
 };
 std::mutex g_tuned_mu;
 std::vector<TunedEntry> g_tuned;
@@ -1216,14 +1406,23 @@ bool tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, TileShape *sh) 
     return false;
 }
 
-void set_tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, const TileShape &sh) {
+void set_tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, const TileShape &sh,
+                     bool pinned) {
     std::lock_guard<std::mutex> lk(g_tuned_mu);
     for (TunedEntry &t : g_tuned)
         if (t.dtype == dtype && t.b == block && t.w == window) {
             t.sh = sh;
+            t.pinned = pinned;
             return;
         }
-    g_tuned.push_back(TunedEntry{dtype, block, window, sh});
+    g_tuned.push_back(TunedEntry{dtype, block, window, sh, pinned});
+}
+
+bool pinned_shape(nrr_dtype dtype, int32_t block, int32_t window) {
+    std::lock_guard<std::mutex> lk(g_tuned_mu);
+    for (const TunedEntry &t : g_tuned)
+        if (t.dtype == dtype && t.b == block && t.w == window) return t.pinned;
+    return false;
 }
 
 void clear_tuned_shapes() {
@@ -1242,6 +1441,48 @@ static bool wants_mfma(nrr_dtype dtype, int32_t block, int32_t window, const Til
     const int pref = arith_preference();
     if (pref >= 0) return pref == kArithMfma;
     if (tuned_shape(dtype, block, window, &sh)) return sh.arith == kArithMfma;
+    return true;
+}
+
+// The float search's launch behind the matrix-core filter.
+struct FiltPlan {
+    filt::Args fa;
+    int cz;  // z-chunk of the FMA form, for the blocks the filter leaves
+    size_t lds;
+};
+
+// The filter serves float volumes with block edges 5, 7 and 9 whose window
+// fits in LDS, by default: a shape asked for by the caller (a tuner's trial, a
+// pinned shape, an environment override) runs as the FMA form itself.  At
+// edge 3 the FMA form's 27 products per displacement cost less than the
+// bounds.  Record and voxel offsets from the window's corner are 32-bit.
+static bool filt_plan(nrr_dtype dtype, const MatchArgs &a, const TileShape *shape, FiltPlan *out) {
+    if (dtype != NRR_F32 || shape || (a.block != 5 && a.block != 7 && a.block != 9)) return false;
+    TileShape sh;
+    if (shape_from_env(&sh) || arith_preference() >= 0 || pinned_shape(dtype, a.block, a.window))
+        return false;
+    const int d = 2 * a.window + 1;
+    if ((int64_t)a.nx * a.ny * 16 * (2 * d + 3 * a.block) >= (1ll << 31)) return false;
+    const size_t limit = device_lds_limit(), fixed = sizeof(Small) + sizeof(filt::Small) + 64;
+    const int32_t b[3] = {a.block, a.block, a.block}, w[3] = {a.window, a.window, a.window};
+    if (limit < fixed || !filt::plan(b, w, limit - fixed, &out->fa.z)) return false;
+    const Variant v{NRR_F32, FMA, a.block, 4, 4, 256, 0, nullptr};
+    Plan fb;
+    if (!plan_variant(v, a.window, limit, (size_t)out->fa.z.lds, &fb)) return false;
+    out->cz = fb.cz;
+    out->lds = std::max((size_t)out->fa.z.lds, fb.lds);
+    for (int i = 0; i < 3; ++i) {
+        out->fa.b[i] = b[i];
+        out->fa.w[i] = w[i];
+    }
+    out->fa.nx = a.nx;
+    out->fa.ny = a.ny;
+    out->fa.nz = a.nz;
+    out->fa.ox = a.ox;
+    out->fa.oy = a.oy;
+    out->fa.flt = a.flt;
+    out->fa.stats = a.stats;
+    out->fa.nstat = (int64_t)a.ox * a.oy * (a.nz - a.block + 1);
     return true;
 }
 
@@ -1315,11 +1556,18 @@ hipError_t launch_match(nrr_dtype dtype, const MatchArgs &a, hipStream_t stream,
     if (mfma_fits(a) && wants_mfma(dtype, a.block, a.window, shape))
         return launch_match_mfma(a, stream);
     Plan pl;
-    if (!choose(dtype, a.block, a.window, device_lds_limit(), shape, &pl))
+    FiltPlan fp;
+    const bool filtered = filt_plan(dtype, a, shape, &fp);
+    if (!filtered && !choose(dtype, a.block, a.window, device_lds_limit(), shape, &pl))
         return hipErrorInvalidValue;
-    const Variant *v = pl.v;
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(v->fn),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds) != hipSuccess)
+    const auto ffn = a.block == 5 ? k_match_f32_filtered<5>
+                     : a.block == 7 ? k_match_f32_filtered<7>
+                                    : k_match_f32_filtered<9>;
+    const void *fn = filtered ? reinterpret_cast<const void *>(ffn)
+                              : reinterpret_cast<const void *>(pl.v->fn);
+    const size_t lds = filtered ? fp.lds : pl.lds;
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+        hipSuccess)
         return hipGetLastError();
     Params p;
     p.ref = a.ref;
@@ -1330,7 +1578,7 @@ hipError_t launch_match(nrr_dtype dtype, const MatchArgs &a, hipStream_t stream,
     p.centers = a.centers;
     p.n = a.n;
     p.w = a.window;
-    p.cz = pl.cz;
+    p.cz = filtered ? fp.cz : pl.cz;
     p.stats = a.stats;
     p.pv = a.pairs;
     p.ox = a.ox;
@@ -1343,7 +1591,10 @@ hipError_t launch_match(nrr_dtype dtype, const MatchArgs &a, hipStream_t stream,
     for (int64_t first = 0; first < a.n; first += chunk) {
         p.first = first;
         const int64_t cnt = a.n - first < chunk ? a.n - first : chunk;
-        hipLaunchKernelGGL(v->fn, dim3((unsigned)cnt), dim3(v->nt), pl.lds, stream, p);
+        if (filtered)
+            hipLaunchKernelGGL(ffn, dim3((unsigned)cnt), dim3(256), lds, stream, p, fp.fa);
+        else
+            hipLaunchKernelGGL(pl.v->fn, dim3((unsigned)cnt), dim3(pl.v->nt), lds, stream, p);
     }
     return hipGetLastError();
 }

@@ -214,7 +214,11 @@ hipError_t launch_match(nrr_dtype dtype, const MatchArgs &a, hipStream_t stream,
 int match_shapes(nrr_dtype dtype, int32_t block, int32_t window, TileShape *out, int cap);
 // Process-wide table of tuned shapes used by every later launch.
 bool tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, TileShape *sh);
-void set_tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, const TileShape &sh);
+// `pinned`: asked for by the caller (the float search then runs as that shape);
+// a tuner's result serves the vector form only.
+void set_tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, const TileShape &sh,
+                     bool pinned);
+bool pinned_shape(nrr_dtype dtype, int32_t block, int32_t window);
 void clear_tuned_shapes();
 
 // The matrix-core form of the search (12-bit data, block edges 3-9, whole
