@@ -342,11 +342,12 @@ struct BatchLayout {
     std::vector<int64_t> ncand, k, off;  // per set (off: nsets + 1 rows offsets)
     std::vector<int32_t> grid;           // per set, 3 values
     std::vector<int32_t> variant, cz;
+    std::vector<size_t> set_lds;         // per set: LDS bytes of its search shape
     std::vector<double> cost;            // per set: K times the per-block cost
     std::vector<int32_t> bvals;          // distinct block sizes
     std::vector<size_t> stats_off;       // per distinct block size
-    size_t sel_off = 0, sets_off = 0, keys_off = 0, total = 0, lds = 0;
-    int64_t nitems = 0, max_cand = 0, sum_cand = 0;
+    size_t sel_off = 0, sets_off = 0, keys_off = 0, total = 0;
+    int64_t max_cand = 0, sum_cand = 0;
 };
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
@@ -384,8 +385,7 @@ nrr_status batch_layout(nrr_dtype dtype, const int32_t dims[3], const nrr_param_
         L->variant.push_back(var);
         L->cz.push_back(cz);
         L->cost.push_back(per * (double)k);
-        L->lds = std::max(L->lds, lds);
-        L->nitems += k;
+        L->set_lds.push_back(lds);
         L->max_cand = std::max(L->max_cand, nc);
         L->sum_cand += nc;
         if (std::find(L->bvals.begin(), L->bvals.end(), q.block) == L->bvals.end())
@@ -1015,6 +1015,15 @@ struct nrr_batch_plan {
     BatchLayout L;
     char *ws = nullptr;
     int32_t nsets = 0;
+    // search launches: runs of the set table (float sets behind the filter by
+    // block edge, then the rest)
+    struct Group {
+        int32_t block;  // 0: the persistent search of any shape
+        int32_t first, count;
+        int64_t items;
+        size_t lds;
+    };
+    std::vector<Group> groups;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
 };
@@ -1056,10 +1065,14 @@ hipError_t batch_enqueue(const nrr_batch_plan &P, hipStream_t st) {
             reinterpret_cast<const nrr::BatchSelectSet *>(P.ws + P.L.sel_off), P.nsets,
             P.L.max_cand, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(st, fs->join, 0);
-    if (e != hipSuccess) return e;
-    return nrr::launch_match_batch(P.dtype,
-                                   reinterpret_cast<const nrr::BatchSet *>(P.ws + P.L.sets_off),
-                                   P.nsets, P.L.nitems, P.L.lds, st);
+    for (const nrr_batch_plan::Group &g : P.groups) {
+        if (e != hipSuccess) return e;
+        const nrr::BatchSet *sets =
+            reinterpret_cast<const nrr::BatchSet *>(P.ws + P.L.sets_off) + g.first;
+        e = g.block ? nrr::launch_match_batch_filtered(g.block, sets, g.count, g.items, g.lds, st)
+                    : nrr::launch_match_batch(P.dtype, sets, g.count, g.items, g.lds, st);
+    }
+    return e;
 }
 
 }  // namespace
@@ -1123,11 +1136,23 @@ nrr_status nrr_batch_plan_create(const void *ref, const void *flt, nrr_dtype dty
     // set tables: selection in the caller's order, search by falling cost
     std::vector<nrr::BatchSelectSet> sel(nsets);
     std::vector<nrr::BatchSet> bs(nsets);
+    // per set: its filter sizes, or none
+    std::vector<nrr::FiltSizes> fz(nsets);
+    std::vector<int32_t> fcz(nsets, 0);
+    std::vector<size_t> flds(nsets, 0);
+    for (int i = 0; i < nsets; ++i) {
+        const nrr::StatsLayout SL = nrr::stats_layout(dtype, dims, sets[i].block);
+        const nrr::MatchArgs a = match_args(ref, flt, dims, nullptr, P->L.k[i], sets[i].block,
+                                            sets[i].window, nullptr, nullptr, nullptr, P->ws, SL);
+        if (!nrr::plan_batch_filter(dtype, a, &fz[i], &fcz[i], &flds[i])) flds[i] = 0;
+    }
+    auto group_of = [&](int i) { return flds[i] ? (int)sets[i].block : 0; };
     std::vector<int> order(nsets);
     std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int x, int y) { return P->L.cost[x] > P->L.cost[y]; });
-    int64_t item = 0;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+        if (group_of(x) != group_of(y)) return group_of(x) > group_of(y);
+        return P->L.cost[x] > P->L.cost[y];
+    });
     std::vector<int64_t> key_at(nsets + 1, 0);
     for (int i = 0; i < nsets; ++i) key_at[i + 1] = key_at[i] + P->L.ncand[i];
     for (int j = 0; j < nsets; ++j) {
@@ -1153,10 +1178,16 @@ nrr_status nrr_batch_plan_create(const void *ref, const void *flt, nrr_dtype dty
         b.a = match_args(ref, flt, dims, t.centers, t.k, q.block, q.window,
                          disp ? disp + 3 * off : nullptr, ncc ? ncc + off : nullptr,
                          conf ? conf + off : nullptr, stats, SL);
-        b.cz = P->L.cz[i];
+        b.cz = flds[i] ? fcz[i] : P->L.cz[i];
         b.variant = P->L.variant[i];
-        b.first_item = item;
-        item += t.k;
+        b.filt = fz[i];
+        if (P->groups.empty() || P->groups.back().block != group_of(i))
+            P->groups.push_back({group_of(i), j, 0, 0, 0});
+        nrr_batch_plan::Group &g = P->groups.back();
+        b.first_item = g.items;
+        g.items += t.k;
+        ++g.count;
+        g.lds = std::max(g.lds, flds[i] ? flds[i] : P->L.set_lds[i]);
     }
     hipError_t e = hipSuccess;
     if (nsets > 0) {

@@ -1106,6 +1106,60 @@ __global__ __launch_bounds__(256) void k_match_batch(const BatchSet *__restrict_
     }
 }
 
+// The float sets of one block edge behind the filter: a workgroup per item
+// (one block of one set), the most expensive sets first.
+template <int B>
+__global__ __launch_bounds__(256, FiltShape<B>::WAVES) void k_match_batch_filtered(
+    const BatchSet *__restrict__ sets, int nsets) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ Small sm;
+    __shared__ filt::Small fs;
+    // the item's set: the last whose first item is not past it (64 at a time)
+    const int64_t it = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    int s = -1;
+    for (int s0 = 0; s0 < nsets; s0 += 64) {
+        const bool at = s0 + lane < nsets && sets[s0 + lane].first_item <= it;
+        s += __popcll(__ballot(at));
+    }
+    s = __builtin_amdgcn_readfirstlane(s);
+    const BatchSet &S = sets[s];
+    Params p;
+    p.ref = S.a.ref;
+    p.flt = S.a.flt;
+    p.nx = S.a.nx;
+    p.ny = S.a.ny;
+    p.nz = S.a.nz;
+    p.centers = S.a.centers;
+    p.n = S.a.n;
+    p.first = 0;
+    p.w = S.a.window;
+    p.cz = S.cz;
+    p.stats = S.a.stats;
+    p.pv = nullptr;
+    p.ox = S.a.ox;
+    p.oy = S.a.oy;
+    p.disp = S.a.disp;
+    p.ncc = S.a.ncc;
+    p.conf = S.a.conf;
+    p.surface = nullptr;
+    filt::Args fa;
+    fa.z = S.filt;
+    for (int i = 0; i < 3; ++i) {
+        fa.b[i] = B;
+        fa.w[i] = p.w;
+    }
+    fa.nx = p.nx;
+    fa.ny = p.ny;
+    fa.nz = p.nz;
+    fa.ox = p.ox;
+    fa.oy = p.oy;
+    fa.flt = p.flt;
+    fa.stats = p.stats;
+    fa.nstat = (int64_t)p.ox * p.oy * (p.nz - B + 1);
+    match_one_filtered<B>(p, fa, it - S.first_item, lds, sm, fs);
+}
+
 // ------------------------------------------------------------ dispatch
 
 typedef void (*kernel_t)(Params);
@@ -1484,6 +1538,30 @@ static bool filt_plan(nrr_dtype dtype, const MatchArgs &a, const TileShape *shap
     out->fa.stats = a.stats;
     out->fa.nstat = (int64_t)a.ox * a.oy * (a.nz - a.block + 1);
     return true;
+}
+
+bool plan_batch_filter(nrr_dtype dtype, const MatchArgs &a, FiltSizes *z, int32_t *cz,
+                       size_t *lds) {
+    FiltPlan fp;
+    if (!filt_plan(dtype, a, nullptr, &fp)) return false;
+    *z = fp.fa.z;
+    *cz = fp.cz;
+    *lds = fp.lds;
+    return true;
+}
+
+hipError_t launch_match_batch_filtered(int32_t block, const BatchSet *sets, int32_t nsets,
+                                       int64_t nitems, size_t lds, hipStream_t stream) {
+    if (nitems <= 0) return hipSuccess;
+    if (nitems >= (1ll << 31)) return hipErrorInvalidValue;
+    const auto fn = block == 5 ? k_match_batch_filtered<5>
+                    : block == 7 ? k_match_batch_filtered<7>
+                                 : k_match_batch_filtered<9>;
+    const hipError_t e = hipFuncSetAttribute(
+        reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fn, dim3((unsigned)nitems), dim3(256), lds, stream, sets, nsets);
+    return hipGetLastError();
 }
 
 int match_shapes(nrr_dtype dtype, int32_t block, int32_t window, TileShape *out, int cap) {

@@ -112,14 +112,7 @@ __device__ inline bool scale_of(uint32_t bits, float &scale) {
 
 // Host and device sizes of one (block, window): the K layout (groups of 4
 // columns by 2 rows that any offset of the patch touches) and LDS offsets.
-struct Sizes {
-    int gx, gyp, nq;             // x groups, y row pairs, 32-wide K chunks per plane
-    int txw, tyw, tcopy;         // T table row width, rows per plane, halves per copy
-    int rp2;                     // window pitch of a row pair (halves)
-    int t_off, tab_off, l_off;   // bytes: T^ floats, tile rows, candidates
-    int lds;                     // total bytes
-    int tz;                      // phase length of an unclipped window
-};
+using Sizes = FiltSizes;
 
 __host__ __device__ inline int best_phase(int nxy, int dzn, int bz, int nq) {
     int best = bz;

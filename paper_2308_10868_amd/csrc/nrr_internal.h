@@ -173,11 +173,28 @@ hipError_t launch_match_aniso(nrr_dtype dtype, const AnisoArgs &a, hipStream_t s
 // One parameter set of a batched search: its arguments (centres and outputs
 // already offset to the set's rows), z-chunk, compiled tile shape and first
 // work item (items = the set's blocks, sets ordered by falling cost).
+// Sizes of the matrix-core filter for one (block, window), mfma_filter.h.
+struct FiltSizes {
+    int gx, gyp, nq;            // x groups, y row pairs, 32-wide K chunks per plane
+    int txw, tyw, tcopy;        // T table row width, rows per plane, halves per copy
+    int rp2;                    // window pitch of a row pair (halves)
+    int t_off, tab_off, l_off;  // bytes: T^ floats, tile rows, candidates
+    int lds;                    // total bytes
+    int tz;                     // phase length of an unclipped window
+};
 struct BatchSet {
     MatchArgs a;
     int32_t cz, variant;
     int64_t first_item;
+    FiltSizes filt;  // of a set that runs behind the filter
 };
+// Whether a set's search runs behind the matrix-core filter (then its filter
+// sizes, the z-chunk of the blocks the filter leaves, and LDS bytes).
+bool plan_batch_filter(nrr_dtype dtype, const MatchArgs &a, FiltSizes *z, int32_t *cz,
+                       size_t *lds);
+// One workgroup per item over sets of one block edge, all behind the filter.
+hipError_t launch_match_batch_filtered(int32_t block, const BatchSet *sets, int32_t nsets,
+                                       int64_t nitems, size_t lds, hipStream_t stream);
 // Tile shape, z-chunk and LDS bytes of one set in the batched kernel; false
 // when no compiled batched shape serves (dtype, block, window).
 bool plan_batch_set(nrr_dtype dtype, int32_t block, int32_t window, int32_t *variant,
