@@ -146,8 +146,7 @@ __device__ inline void wg_argmax(K &key, int &idx, K *s_key, int *s_idx) {
 template <int NT, typename T, int NV>
 __device__ inline void wg_sum(T (&v)[NV], T *s_red) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k)
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off);
+    for (int k = 0; k < NV; ++k) v[k] = wave_xor_sum(v[k]);
     const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
@@ -933,17 +932,30 @@ __device__ __attribute__((always_inline)) inline void match_one_filtered(
         }
     filt::open_block(fa, fg, lds, fs);
 
-    // T^ = T - mean as floats, its sums: the FMA form's operations
+    // T^ = T - mean as floats, its sums: the FMA form's operations.  The largest
+    // |T^| follows from the smallest and largest voxel (the same operations,
+    // monotone; a NaN among them makes the mean one).
     double sd[1] = {0.0};
+    uint32_t tmn = 0xffffffffu, tmx = 0;
 #pragma unroll
     for (int k = 0; k < TPT; ++k)
-        if (tid + k * NT < N) sd[0] += (double)tv[k];
-    wg_sum<NT, double, 1>(sd, sm.redd);
+        if (tid + k * NT < N) {
+            sd[0] += (double)tv[k];
+            tmn = min(tmn, filt::ordered(tv[k]));
+            tmx = max(tmx, filt::ordered(tv[k]));
+        }
+    tmn = ~wave_max(~tmn);
+    tmx = wave_max(tmx);
+    if ((tid & 63) == 63) {
+        fs.tmin[tid >> 6] = tmn;
+        fs.tmax[tid >> 6] = tmx;
+    }
+    wg_sum<NT, double, 1>(sd, sm.redd);  // its barrier publishes the extremes too
     const double tmean = sd[0] / (double)N;
     const float c = (float)tmean;
-    float *tf = reinterpret_cast<float *>(lds + fa.z.t_off);
+    float sT = 0.0f;
+    bool scales = filt::block_scale(fs, tmean, sT);
     double ctr[2] = {0.0, 0.0};
-    uint32_t tmax = 0;
 #pragma unroll
     for (int k = 0; k < TPI; ++k) {
         const int i = tid + k * NT;
@@ -952,59 +964,62 @@ __device__ __attribute__((always_inline)) inline void match_one_filtered(
         const float v = (float)((double)tw[k] - tmean);
         ctr[0] += (double)v;
         ctr[1] += (double)v * (double)v;
-        tmax = max(tmax, __float_as_uint(v) & 0x7fffffffu);
-        tf[(oz * B + oy) * B + ox] = v;
+        filt::put_voxel(fa, lds, ox, oy, oz, v, sT);
     }
-    tmax = filt::wave_max(tmax);
-    if ((tid & 63) == 63) fs.wmax[tid >> 6] = tmax;
-    wg_sum<NT, double, 2>(ctr, sm.redd);  // its barriers publish tf, the tables and the maxima
-    tmax = max(max(fs.wmax[0], fs.wmax[1]), max(fs.wmax[2], fs.wmax[3]));
-    tmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)tmax);
+    wg_sum<NT, double, 2>(ctr, sm.redd);  // its barriers publish T^
     if (!(ctr[1] > 0.0)) {  // flat block
         if (tid == 0) write_result(p, blk, g.lox, g.loy, g.loz, 0.0f);
-        __syncthreads();  // the maxima are read
         return;
     }
+    const float *tf = reinterpret_cast<const float *>(lds + fa.z.t_off);
     const double dN = (double)N, tsum = ctr[0];
     const int side = 2 * p.w + 1;
     const StatF32 *table = static_cast<const StatF32 *>(p.stats);
-    // the FMA form's key of shift index idx: lane oz sums block plane oz, the
-    // plane sums are added in order
-    auto exact = [&](int idx, int oz, double &key) {
-        const int id = max(idx, 0);
-        const int iz = id / (side * side), ir = id - iz * side * side, iy = ir / side,
-                  ix = ir - iy * side;
-        const int64_t o0 = (int64_t)(g.cz - H + iz - p.w) * nxy +
-                           (int64_t)(g.cy - H + iy - p.w) * p.nx + (g.cx - H + ix - p.w);
-        float acc = 0.0f;
-        if (idx >= 0) {
-            const float *f = flt + o0 + oz * nxy;
-            const float *t = tf + oz * B * B;
+    int ncand = scales ? filt::search<float, B, S::NQ, S::KREG, S::AHEAD>(
+                             fa, fg, lds, fs, w, walk0, at, c, (float)sqrt(ctr[1]), sT)
+                       : 0;
+    const int *cand = filt::candidates(fa, lds);
+    int best = cand[0];
+    if (ncand > 1) {
+        // the FMA form's key of each candidate: lane oz sums block plane oz, the
+        // plane sums are added in order
+        double *keys = reinterpret_cast<double *>(lds + fa.z.l_off + filt::LIST * 8 +
+                                                  filt::CAND * 4);
+        constexpr int PER = 64 / B;  // candidates per wavefront step
+        const int lane = tid & 63, sub = lane / B, oz = lane - sub * B;
+        for (int k0 = (tid >> 6) * PER; k0 < ncand; k0 += filt::NW * PER) {
+            const int k = k0 + sub;
+            const bool on = sub < PER && k < ncand;
+            const int id = on ? cand[k] : 0;
+            const int iz = id / (side * side), ir = id - iz * side * side, iy = ir / side,
+                      ix = ir - iy * side;
+            const int x0 = g.cx - H + ix - p.w, y0 = g.cy - H + iy - p.w, z0 = g.cz - H + iz - p.w;
+            float acc = 0.0f;
+            if (on) {
+                const float *f = flt + (int64_t)(z0 + oz) * nxy + (int64_t)y0 * p.nx + x0;
+                const float *t = tf + oz * B * B;
 #pragma unroll
-            for (int oy = 0; oy < B; ++oy)
+                for (int oy = 0; oy < B; ++oy)
 #pragma unroll
-                for (int ox = 0; ox < B; ++ox)
-                    acc = __builtin_fmaf(f[(int64_t)oy * p.nx + ox] - c, t[oy * B + ox], acc);
+                    for (int ox = 0; ox < B; ++ox)
+                        acc = __builtin_fmaf(f[(int64_t)oy * p.nx + ox] - c, t[oy * B + ox], acc);
+            }
+            float x = 0.0f;
+#pragma unroll
+            for (int j = 0; j < B; ++j) x += __shfl(acc, (lane - oz + j) & 63);
+            if (on && oz == 0)
+                keys[k] = key_f32_of(dN, x, tsum,
+                                     table[((int64_t)z0 * p.oy + y0) * p.ox + x0], c);
         }
-        float x = 0.0f;
-        const int first = (tid & 63) - oz;
-#pragma unroll
-        for (int j = 0; j < B; ++j) x += __shfl(acc, (first + j) & 63);
-        if (idx >= 0) {
-            const StatF32 rec =
-                table[((int64_t)(g.cz - H + iz - p.w) * p.oy + (g.cy - H + iy - p.w)) * p.ox +
-                      (g.cx - H + ix - p.w)];
-            key = key_f32_of(dN, x, tsum, rec, c);
-        }
-    };
-    int best = 0;
-    const bool found = filt::search<float, double, B, S::NQ, S::KREG, S::AHEAD, B>(
-        fa, fg, lds, fs, w, walk0, at, c, (float)sqrt(ctr[1]), tmax, exact, best);
+        __syncthreads();
+        best = filt::pick(cand, keys, ncand);
+        if (best == INT_MAX) ncand = 0;
+    }
     // an opaque copy of the thread index: what follows recomputes its
     // addresses instead of holding them in registers through the sweep
     int t2 = tid;
     asm volatile("" : "+v"(t2));
-    if (!found) {  // uniform
+    if (ncand == 0) {  // uniform
         __syncthreads();
         match_one<float, FMA, B, 4, 4, NT, false>(p, blk, lds, sm, t2);
         return;

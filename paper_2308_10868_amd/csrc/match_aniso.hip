@@ -27,11 +27,13 @@
 //     sums of F'' from the statistics table.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 
+#include "mfma_filter.h"
 #include "nrr_internal.h"
 
 namespace nrr {
@@ -65,7 +67,7 @@ __device__ inline int64_t xcd_order(int64_t wg, int64_t n) {
 
 // Sum of v over the workgroup (every thread gets it).
 __device__ inline double wg_sum(double v, double *red) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    v = wave_xor_sum(v);
     __syncthreads();  // red is reused across calls
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -110,25 +112,12 @@ __device__ inline void write_outside(const AnisoArgs &p, int64_t blk) {
     p.conf[blk] = 0.0f;
 }
 
-// Workgroup argmax of (key, shift index), then the winner's NCC in two FP64
-// passes over the block (mt = the ref block's mean); thread 0 writes.
-template <typename Vox, typename Key>
-__device__ inline void aniso_finish(const AnisoArgs &p, const AGeom &g, int64_t blk, Key bk, int bi,
-                                    double mt, Key *s_key, int *s_idx, double *red) {
-    const int tid = threadIdx.x, nt = blockDim.x;
-    for (int off = 32; off > 0; off >>= 1) {
-        const Key ok = __shfl_xor(bk, off);
-        const int oi = __shfl_xor(bi, off);
-        better(bk, bi, ok, oi);
-    }
-    if ((tid & 63) == 0) {
-        s_key[tid >> 6] = bk;
-        s_idx[tid >> 6] = bi;
-    }
-    __syncthreads();
-    bk = s_key[0];
-    bi = s_idx[0];
-    for (int w = 1; w < nt / 64; ++w) better(bk, bi, s_key[w], s_idx[w]);
+// The NCC of shift index bi in two FP64 passes over the block (mt = the ref
+// block's mean); thread 0 writes.
+template <typename Vox>
+__device__ inline void aniso_score(const AnisoArgs &p, const AGeom &g, int64_t blk, int bi,
+                                   double mt, double *red, int tid) {
+    const int nt = blockDim.x;
     const int sxn = 2 * p.w[0] + 1, syn = 2 * p.w[1] + 1;
     const int dx = bi % sxn - p.w[0], dy = (bi / sxn) % syn - p.w[1], dz = bi / (sxn * syn) - p.w[2];
 
@@ -164,6 +153,28 @@ __device__ inline void aniso_finish(const AnisoArgs &p, const AGeom &g, int64_t 
     }
 }
 
+// Workgroup argmax of (key, shift index), then the winner's NCC in two FP64
+// passes over the block (mt = the ref block's mean); thread 0 writes.
+template <typename Vox, typename Key>
+__device__ inline void aniso_finish(const AnisoArgs &p, const AGeom &g, int64_t blk, Key bk, int bi,
+                                    double mt, Key *s_key, int *s_idx, double *red, int tid) {
+    const int nt = blockDim.x;
+    for (int off = 32; off > 0; off >>= 1) {
+        const Key ok = __shfl_xor(bk, off);
+        const int oi = __shfl_xor(bi, off);
+        better(bk, bi, ok, oi);
+    }
+    if ((tid & 63) == 0) {
+        s_key[tid >> 6] = bk;
+        s_idx[tid >> 6] = bi;
+    }
+    __syncthreads();
+    bk = s_key[0];
+    bi = s_idx[0];
+    for (int w = 1; w < nt / 64; ++w) better(bk, bi, s_key[w], s_idx[w]);
+    aniso_score<Vox>(p, g, blk, bi, mt, red, tid);
+}
+
 template <typename Vox>
 struct Rec;
 template <>
@@ -181,16 +192,22 @@ struct Rec<float> {
     }
 };
 
-// FMA form (any voxel type).
+// Workgroup scratch of the reductions.
+struct ASmall {
+    double red[NT / 64];
+    double key[NT / 64];
+    int idx[NT / 64];
+};
+
+// FMA form (any voxel type): one block.
 template <typename Vox, int RX>
-__global__ __launch_bounds__(NT) void k_match_aniso(AnisoArgs p) {
+__device__ __attribute__((always_inline)) inline void aniso_one(const AnisoArgs &p, int64_t blk,
+                                                                float *lds, ASmall &sm, int tid) {
     using Key = typename Rec<Vox>::Key;
-    extern __shared__ __align__(16) float lds[];
-    __shared__ double red[NT / 64];
-    __shared__ Key s_key[NT / 64];
-    __shared__ int s_idx[NT / 64];
-    const int64_t blk = xcd_order(blockIdx.x, gridDim.x);
-    const int tid = threadIdx.x, nt = blockDim.x;
+    double *red = sm.red;
+    Key *s_key = reinterpret_cast<Key *>(sm.key);
+    int *s_idx = sm.idx;
+    const int nt = blockDim.x;
     const Vox *ref = static_cast<const Vox *>(p.ref);
     const Vox *flt = static_cast<const Vox *>(p.flt);
     const AGeom g = aniso_geom(p, blk);
@@ -309,7 +326,196 @@ __global__ __launch_bounds__(NT) void k_match_aniso(AnisoArgs p) {
             }
         }
     }
-    aniso_finish<Vox, Key>(p, g, blk, bk, bi, mt, s_key, s_idx, red);
+    aniso_finish<Vox, Key>(p, g, blk, bk, bi, mt, s_key, s_idx, red, tid);
+}
+
+template <typename Vox, int RX>
+__global__ __launch_bounds__(NT) void k_match_aniso(AnisoArgs p) {
+    extern __shared__ __align__(16) float lds[];
+    __shared__ ASmall sm;
+    aniso_one<Vox, RX>(p, xcd_order(blockIdx.x, gridDim.x), lds, sm, threadIdx.x);
+}
+
+// The same search behind the matrix-core filter (mfma_filter.h): the same
+// winner, bit for bit; the FMA form takes the blocks the filter leaves.  BZ is
+// the block's z edge, NQ the 32-wide K chunks its x and y edges need at most.
+// What bounds the FMA form is the latency of its staging and the issue of its
+// products (20% of the FP32 peak at 7x7x3 blocks); here the products are matrix
+// instructions, and the survivors' chains are run one candidate per lane from
+// LDS.
+template <typename Vox, int BZ, int NQ>
+__global__ __launch_bounds__(NT, BZ * NQ <= 15 ? 3 : BZ * NQ <= 28 ? 2 : 1) void k_aniso_filtered(
+    AnisoArgs p, filt::Args fa) {
+    using Key = typename Rec<Vox>::Key;
+    constexpr int KREG = (BZ * NQ <= 15 ? 12 : 20) * 4 / filt::Chunk<Vox>::C;
+    constexpr int AHEAD = BZ < 5 ? BZ : BZ == 7 ? 3 : 5;
+    extern __shared__ __align__(16) unsigned char ldsb[];
+    __shared__ ASmall sm;
+    __shared__ filt::Small fs;
+    __shared__ float s_sq[NT / 64];
+    __shared__ double s_q[NT / 64][3];
+    const int64_t blk = xcd_order(blockIdx.x, gridDim.x);
+    const int tid = threadIdx.x;
+    const Vox *ref = static_cast<const Vox *>(p.ref);
+    const Vox *flt = static_cast<const Vox *>(p.flt);
+    const AGeom g = aniso_geom(p, blk);
+    if (!g.inside) {
+        if (tid == 0) write_outside(p, blk);
+        return;
+    }
+    // the block's voxels (at most 3 per thread), then the window's chunks
+    constexpr int TPT = (filt::MAXN + NT - 1) / NT;
+    Vox tv[TPT];
+    const int bxy = g.bx * g.by;
+    auto voxel = [&](int o) {
+        const int z = quotient(o, bxy), r = o - z * bxy, y = quotient(r, g.bx);
+        return z * g.sz + (int64_t)y * g.sy + (r - y * g.bx);
+    };
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (k * NT < g.nb) tv[k] = ref[g.rbase + voxel(min(tid + k * NT, g.nb - 1))];
+    filt::Geo fg = filt::geometry<Vox>(fa, g.cx, g.cy, g.cz);
+    filt::Walk<Vox> walk0;
+    walk0.start(fa, fg);
+    filt::Walk<Vox> at = walk0;
+    filt::u32x4 w[KREG];
+#pragma unroll
+    for (int k2 = 0; k2 < KREG; k2 += 2)
+        if (k2 < walk0.kn) {
+#pragma unroll
+            for (int k = k2; k < k2 + 2; ++k) {
+                w[k] = at.load(fa, fg);
+                at.next(fg);
+            }
+        }
+    filt::open_block(fa, fg, ldsb, fs);
+    double st = 0.0;
+    uint32_t tmn = 0xffffffffu, tmx = 0;
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (tid + k * NT < g.nb) {
+            st += (double)tv[k];
+            tmn = min(tmn, filt::ordered((float)tv[k]));
+            tmx = max(tmx, filt::ordered((float)tv[k]));
+        }
+    tmn = ~wave_max(~tmn);
+    tmx = wave_max(tmx);
+    if ((tid & 63) == 63) {
+        fs.tmin[tid >> 6] = tmn;
+        fs.tmax[tid >> 6] = tmx;
+    }
+    const double mt = wg_sum(st, sm.red) / g.nb;  // its barrier publishes the extremes too
+    const float cf = (float)mt;
+    float sT = 0.0f, sq = 0.0f;
+    const bool scales = filt::block_scale(fs, mt, sT);
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (tid + k * NT < g.nb) {
+            const float v = (float)((double)tv[k] - mt);
+            const int o = tid + k * NT, z = quotient(o, bxy), r = o - z * bxy,
+                      y = quotient(r, g.bx);
+            filt::put_voxel(fa, ldsb, r - y * g.bx, y, z, v, sT);
+            sq = fmaf(v, v, sq);
+        }
+    sq = wave_xor_sum(sq);
+    if ((tid & 63) == 63) s_sq[tid >> 6] = sq;
+    __syncthreads();  // T^, the sums
+    const float *tf = reinterpret_cast<const float *>(ldsb + fa.z.t_off);
+    int ncand = scales ? filt::search<Vox, BZ, NQ, KREG, AHEAD>(
+                             fa, fg, ldsb, fs, w, walk0, at, cf,
+                             sqrtf((s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3])), sT)
+                       : 0;
+    const int *cand = filt::candidates(fa, ldsb);
+    int best = cand[0];
+    const int sxn = 2 * p.w[0] + 1, syn = 2 * p.w[1] + 1;
+    if (ncand > 1) {
+        // the candidates' windows as F - mean(T) in the window's place (an odd
+        // pitch: one candidate per lane reads without conflicts), as many as fit
+        Key *keys = reinterpret_cast<Key *>(ldsb + fa.z.l_off + filt::LIST * 8 + filt::CAND * 4);
+        float *fw = reinterpret_cast<float *>(ldsb);
+        const int pitch = g.nb | 1, fit = min(fa.z.t_off / (4 * pitch), NT);
+        for (int k0 = 0; k0 < ncand; k0 += fit) {
+            const int n = min(fit, ncand - k0);
+            for (int e = tid; e < n * g.nb; e += NT) {
+                const int k = quotient(e, g.nb), o = e - k * g.nb, id = cand[k0 + k];
+                const int iz = quotient(id, sxn * syn), ir = id - iz * sxn * syn,
+                          iy = quotient(ir, sxn);
+                const int64_t d = (iz - p.w[2]) * g.sz + (int64_t)(iy - p.w[1]) * g.sy +
+                                  (ir - iy * sxn - p.w[0]);
+                fw[k * pitch + o] = (float)flt[g.rbase + d + voxel(o)] - cf;
+            }
+            __syncthreads();
+            if (tid < n) {  // the FMA form's chain: z, y, x
+                const float *f = fw + tid * pitch;
+                float acc = 0.0f;
+#pragma unroll 8
+                for (int o = 0; o < g.nb; ++o) acc = fmaf(tf[o], f[o], acc);
+                const int id = cand[k0 + tid];
+                const int iz = quotient(id, sxn * syn), ir = id - iz * sxn * syn,
+                          iy = quotient(ir, sxn), ix = ir - iy * sxn;
+                const Key r = Rec<Vox>::r(
+                    p.stats, ((int64_t)(g.cz - g.hz + iz - p.w[2]) * p.oy +
+                              (g.cy - g.hy + iy - p.w[1])) * p.ox + g.cx - g.hx + ix - p.w[0]);
+                Key key = (Key)acc * r;
+                if (key != key) key = -INFINITY;  // as the FMA form ranks them: last
+                keys[k0 + tid] = key;
+            }
+            __syncthreads();
+        }
+        best = filt::pick(cand, keys, ncand);
+    }
+    // an opaque copy of the thread index: what follows recomputes its addresses
+    // instead of holding them in registers through the sweep
+    int t2 = tid;
+    asm volatile("" : "+v"(t2));
+    if (ncand == 0) {  // uniform
+        __syncthreads();
+        aniso_one<Vox, 8>(p, blk, reinterpret_cast<float *>(ldsb), sm, t2);
+        return;
+    }
+    // ---- the winner's NCC: aniso_score's sums, the voxels read once
+    const int iz = quotient(best, sxn * syn), ir = best - iz * sxn * syn, iy = quotient(ir, sxn),
+              ix = ir - iy * sxn;
+    const int dx = ix - p.w[0], dy = iy - p.w[1], dz = iz - p.w[2];
+    const int64_t fbase = g.rbase + dz * g.sz + (int64_t)dy * g.sy + dx;
+    Vox fv[TPT];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (k * NT < g.nb) fv[k] = flt[fbase + voxel(min(t2 + k * NT, g.nb - 1))];
+    double sf = 0.0;
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (t2 + k * NT < g.nb) sf += (double)fv[k];
+    const double mf = wg_sum(sf, sm.red) / g.nb;
+    double q[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (t2 + k * NT < g.nb) {
+            const double a = (double)tv[k] - mt, b = (double)fv[k] - mf;
+            q[0] += a * a;
+            q[1] += b * b;
+            q[2] += a * b;
+        }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        q[j] = wave_xor_sum(q[j]);
+        if ((t2 & 63) == 0) s_q[t2 >> 6][j] = q[j];
+    }
+    __syncthreads();
+    if (t2 == 0) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            q[j] = 0.0;
+            for (int i = 0; i < NT / 64; ++i) q[j] += s_q[i][j];
+        }
+        const double ab = q[0] * q[1];
+        const double v = ab > 0.0 ? q[2] / sqrt(ab) : 0.0;
+        p.disp[3 * blk] = dx;
+        p.disp[3 * blk + 1] = dy;
+        p.disp[3 * blk + 2] = dz;
+        p.ncc[blk] = (float)v;
+        p.conf[blk] = v > 0.0 ? (float)v : 0.0f;
+    }
 }
 
 __device__ inline uint32_t pack2(int lo, int hi) {
@@ -452,7 +658,7 @@ __global__ __launch_bounds__(NT) void k_match_aniso_dot2(AnisoArgs p) {
             }
         }
     }
-    aniso_finish<uint16_t, double>(p, g, blk, bk, bi, mt, s_key, s_idx, red);
+    aniso_finish<uint16_t, double>(p, g, blk, bk, bi, mt, s_key, s_idx, red, threadIdx.x);
 }
 
 // Compiled register tiles: RX consecutive x displacements per thread.
@@ -514,6 +720,54 @@ bool aniso_plan(const int32_t b[3], const int32_t w[3], AnisoPlan *out) {
     return true;
 }
 
+// Filtered instantiations, smallest that serves first: z edge, K chunks.
+typedef void (*filtered_t)(AnisoArgs, filt::Args);
+struct Filtered {
+    int bz, nq;
+    filtered_t u16, f32;
+};
+#define FILTERED(BZ, NQ) {BZ, NQ, k_aniso_filtered<uint16_t, BZ, NQ>, k_aniso_filtered<float, BZ, NQ>}
+const Filtered kFiltered[] = {FILTERED(3, 2), FILTERED(3, 4), FILTERED(3, 5), FILTERED(5, 2),
+                              FILTERED(5, 4), FILTERED(5, 5), FILTERED(7, 4), FILTERED(7, 5),
+                              FILTERED(9, 5)};
+#undef FILTERED
+
+// The filter serves block edges up to 9 (z: 3 to 9) whose window fits in LDS
+// beside room for one plane run of the FMA form, with 32-bit record and voxel
+// offsets from the window's corner.  A form or tile asked for by the
+// environment runs as asked.
+filtered_t aniso_filter(nrr_dtype dtype, const AnisoArgs &a, filt::Args *fa, size_t *lds) {
+    for (const char *v : {"NRR_ANISO_ARITH", "NRR_ANISO_TILE", "NRR_ANISO_CZ"})
+        if (const char *e = getenv(v))
+            if (*e) return nullptr;
+    const int64_t rec = dtype == NRR_U16 ? sizeof(StatU16) : sizeof(StatF32);
+    if ((int64_t)a.nx * a.ny * rec * (2 * (2 * a.w[2] + 1) + 3 * a.b[2]) >= (1ll << 31))
+        return nullptr;
+    const size_t limit = device_lds_limit(),
+                 fixed = sizeof(ASmall) + sizeof(filt::Small) + NT / 64 * 28 + 64;
+    if (limit < fixed || !filt::plan(a.b, a.w, limit - fixed, &fa->z)) return nullptr;
+    const Filtered *f = nullptr;
+    for (const Filtered &v : kFiltered)
+        if (!f && v.bz == a.b[2] && v.nq >= fa->z.nq) f = &v;
+    const int tp = (a.b[0] + TU - 1) / TU * TU, n = 2 * a.w[0] + 1;
+    if (!f || (n + 7) / 8 * 8 + tp > 64) return nullptr;  // the FMA form's widest row (8 per thread)
+    *lds = std::max((size_t)fa->z.lds, aniso_lds(a.b, a.w, 8, 1));
+    if (*lds > limit - fixed) return nullptr;
+    for (int i = 0; i < 3; ++i) {
+        fa->b[i] = a.b[i];
+        fa->w[i] = a.w[i];
+    }
+    fa->nx = a.nx;
+    fa->ny = a.ny;
+    fa->nz = a.nz;
+    fa->ox = a.ox;
+    fa->oy = a.oy;
+    fa->flt = a.flt;
+    fa->stats = a.stats;
+    fa->nstat = (int64_t)a.ox * a.oy * (a.nz - a.b[2] + 1);
+    return dtype == NRR_U16 ? f->u16 : f->f32;
+}
+
 }  // namespace
 
 const char *aniso_unsupported_reason(const int32_t block[3], const int32_t window[3]) {
@@ -536,6 +790,16 @@ hipError_t launch_match_aniso(nrr_dtype dtype, const AnisoArgs &a0, hipStream_t 
     AnisoPlan pl;
     if (!aniso_plan(a.b, a.w, &pl)) return hipErrorInvalidValue;
     a.cz = pl.cz;
+    filt::Args fa;
+    size_t flds = 0;
+    if (const filtered_t ffn = aniso_filter(dtype, a, &fa, &flds)) {
+        a.cz = aniso_cz(a.b, a.w, 8, flds);  // the FMA form's run in the filter's LDS
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(ffn),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)flds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(ffn, dim3((unsigned)a.n), dim3(NT), flds, stream, a, fa);
+        return hipGetLastError();
+    }
     void (*fn)(AnisoArgs) = pl.tile->f32;
     if (dtype == NRR_U16) {
         const char *e = getenv("NRR_ANISO_ARITH");

@@ -40,6 +40,7 @@
 #include <utility>
 
 #include "nrr_internal.h"
+#include "wave64.h"
 
 namespace nrr {
 namespace filt {
@@ -68,27 +69,6 @@ __device__ __attribute__((always_inline)) inline void static_for_seq(
 template <int N, typename F>
 __device__ __attribute__((always_inline)) inline void static_for(F &&f) {
     static_for_seq(f, std::make_integer_sequence<int, N>());
-}
-
-// a / b for 0 <= a < 65536, b > 0: (a + 1/2) / b is at least 1 / (2 b) away
-// from the next integer, beyond the rounding of the reciprocal.
-__device__ inline int quotient(int a, int b) {
-    return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
-}
-
-// Largest value over a wavefront (lane 63 ends with it), by DPP moves.
-template <int CTRL>
-__device__ inline uint32_t dpp_max_step(uint32_t v) {
-    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
-    return v > o ? v : o;
-}
-__device__ inline uint32_t wave_max(uint32_t v) {
-    v = dpp_max_step<0x111>(v);  // row_shr 1, 2, 4, 8
-    v = dpp_max_step<0x112>(v);
-    v = dpp_max_step<0x114>(v);
-    v = dpp_max_step<0x118>(v);
-    v = dpp_max_step<0x142>(v);  // row_bcast 15, 31
-    return dpp_max_step<0x143>(v);
 }
 
 // Floats as integers of the same order (never 0 for a finite float).
@@ -166,9 +146,21 @@ inline bool plan(const int32_t b[3], const int32_t w[3], size_t limit, Sizes *s)
 
 struct Small {
     uint32_t wmax[NW];  // largest |F'| bits per wavefront
+    uint32_t tmin[NW], tmax[NW];  // smallest and largest block voxel (ordered) per wavefront
     uint32_t low;       // largest lower bound (ordered)
     int nlist, ncand, overflow;
 };
+
+// The block's scale from its extremes and mean; false where it does not scale.
+// Uniform.
+__device__ inline bool block_scale(const Small &sm, double mean, float &sT) {
+    const uint32_t mn = min(min(sm.tmin[0], sm.tmin[1]), min(sm.tmin[2], sm.tmin[3]));
+    const uint32_t mx = max(max(sm.tmax[0], sm.tmax[1]), max(sm.tmax[2], sm.tmax[3]));
+    const float lo = (float)((double)unordered(mn) - mean), hi = (float)((double)unordered(mx) - mean);
+    const uint32_t top =
+        max(__float_as_uint(lo) & 0x7fffffffu, __float_as_uint(hi) & 0x7fffffffu);
+    return scale_of((uint32_t)__builtin_amdgcn_readfirstlane((int)top), sT);
+}
 
 // One block's search: geometry (uniform), then the steps below in order.
 struct Args {
@@ -328,21 +320,15 @@ __device__ inline void centred(const u32x4 &v, float c, float (&f)[Chunk<Vox>::C
     }
 }
 
-// The four fp16 copies of T^ sT (copy a moved right by a columns) from the
-// T^ floats in LDS.
-__device__ __attribute__((always_inline)) inline void write_tables(const Args &p,
-                                                                   unsigned char *lds, float sT) {
-    const float *tf = reinterpret_cast<const float *>(lds + p.z.t_off);
-    _Float16 *tt = reinterpret_cast<_Float16 *>(lds);
-    const int n = p.b[0] * p.b[1] * p.b[2], bxy = p.b[0] * p.b[1];
-    for (int o = threadIdx.x; o < n; o += NT) {
-        const int oz = quotient(o, bxy), r = o - oz * bxy, oy = quotient(r, p.b[0]),
-                  ox = r - oy * p.b[0];
-        const _Float16 v = (_Float16)(tf[o] * sT);
-        _Float16 *d = tt + (oz * p.z.tyw + oy + OFF) * p.z.txw + ox;
+// T^ of block voxel (ox, oy, oz): the float, and its four fp16 copies scaled by
+// sT (copy a moved right by a columns).
+__device__ inline void put_voxel(const Args &p, unsigned char *lds, int ox, int oy, int oz,
+                                 float v, float sT) {
+    reinterpret_cast<float *>(lds + p.z.t_off)[(oz * p.b[1] + oy) * p.b[0] + ox] = v;
+    _Float16 *d = reinterpret_cast<_Float16 *>(lds) + (oz * p.z.tyw + oy + OFF) * p.z.txw + ox;
+    const _Float16 h = (_Float16)(v * sT);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) d[a * p.z.tcopy + a] = v;
-    }
+    for (int a = 0; a < 4; ++a) d[a * p.z.tcopy + a] = h;
 }
 
 template <int BZ, int NQ>
@@ -398,6 +384,11 @@ __device__ __attribute__((always_inline)) inline void sweep_block(
     });
 }
 
+// The candidates' shift indices, and behind them their keys.
+__device__ inline int *candidates(const Args &p, unsigned char *lds) {
+    return reinterpret_cast<int *>(lds + p.z.l_off + LIST * 8);
+}
+
 template <typename Vox>
 struct Record;
 template <>
@@ -409,29 +400,22 @@ struct Record<uint16_t> {
     using Type = StatU16;
 };
 
-// Everything after the caller's T^ (floats in LDS at t_off, published by a
-// barrier together with open_block's clears): w[] holds the first KREG chunks
-// of `walk0`'s walk, and `at` the walk behind them.  Returns false where the
-// block is left to the FP32 search, else the winner's shift index in `best`.
-// `exact(idx, key)` gives the FP32 search's key of shift index idx; it is
-// called by every lane of a wavefront, the candidates spread over groups of
-// `lanes` lanes (idx < 0: no candidate), and is valid in each group's first.
-// Ends with the workgroup's LDS free for reuse after a barrier.
-template <typename Vox, typename Key, int BZ, int NQ, int KREG, int AHEAD, int LANES,
-          typename Exact>
-__device__ __attribute__((always_inline)) inline bool search(
+// Everything after the caller's T^ (put_voxel, after open_block's clears, and
+// published by a barrier): w[] holds the first KREG chunks
+// of `walk0`'s walk, and `at` the walk behind them.  Returns the number of
+// displacements that can win (shift indices in candidates(), with repeats), or
+// 0 where the block is left to the FP32 search.  Uniform; the window in LDS is
+// free for reuse, and the list published, on return.
+template <typename Vox, int BZ, int NQ, int KREG, int AHEAD>
+__device__ __attribute__((always_inline)) inline int search(
     const Args &p, const Geo &g, unsigned char *lds, Small &sm, u32x4 (&w)[KREG],
-    const Walk<Vox> &walk0, Walk<Vox> at, float c, float tnorm, uint32_t tmax_bits, Exact exact,
-    int &best) {
+    const Walk<Vox> &walk0, Walk<Vox> at, float c, float tnorm, float sT) {
     using Rec = typename Record<Vox>::Type;
     constexpr int C = Chunk<Vox>::C;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int N = p.b[0] * p.b[1] * p.b[2];
-    float sT, sF;
-    if (!scale_of(tmax_bits, sT)) return false;  // uniform
-    write_tables(p, lds, sT);
-    __syncthreads();
+    float sF;
     half8 bop[BZ][NQ];
     build_operands<BZ, NQ>(p, lds, lane, bop);
 
@@ -455,7 +439,7 @@ __device__ __attribute__((always_inline)) inline bool search(
     __syncthreads();  // every wavefront's operands are built: the window takes their place
     fmax = max(max(sm.wmax[0], sm.wmax[1]), max(sm.wmax[2], sm.wmax[3]));
     fmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)fmax);
-    if (!scale_of(fmax, sF)) return false;  // uniform
+    if (!scale_of(fmax, sF)) return 0;  // uniform
 
     // ---- the window as fp16 F' sF: rows two by two, 4 columns of the upper
     // row then the same 4 of the lower; three row pairs past the last plane are
@@ -495,11 +479,10 @@ __device__ __attribute__((always_inline)) inline bool search(
     const uint32_t *rowtab = reinterpret_cast<const uint32_t *>(lds + p.z.tab_off);
     u32x2 *list = reinterpret_cast<u32x2 *>(lds + p.z.l_off);
     const int sx = 2 * p.w[0] + 1, sxy = sx * (2 * p.w[1] + 1);
+    const float ea = EPS * sqrtf((float)N) * (tnorm * sT) * (__uint_as_float(fmax) * sF);
     {
         const int n16 = lane & 15, grp = lane >> 4;
         const int oa = n16 & 3, ob = n16 >> 2;
-        const float ea =
-            EPS * sqrtf((float)N) * (tnorm * sT) * (__uint_as_float(fmax) * sF);
         const int plane_rec = p.oy * p.ox;
         const int64_t corner = ((int64_t)g.oz0 * p.oy + g.oy0) * p.ox + g.ox0;
         const Rec *srec = static_cast<const Rec *>(p.stats) + corner;
@@ -622,46 +605,58 @@ __device__ __attribute__((always_inline)) inline bool search(
     }
     __syncthreads();
 
-    // ---- candidates: list entries that still reach the largest lower bound
-    int *cand = reinterpret_cast<int *>(list + LIST);
-    Key *keys = reinterpret_cast<Key *>(cand + CAND);
-    const uint32_t all = sm.low;
+    // ---- candidates: of the list entries that still reach the largest lower
+    // end, the single displacements get their own bound, with |F'| from their
+    // record: sqrt(N) |F'| r = sqrt(1 + m^2), m = (sum F - N c) r, and 2^-17 of
+    // the window's bound (2^-28 of Fmax for operands below fp16's range).  It is a
+    // third to a twentieth of the window's: most blocks keep one displacement.
+    int *cand = candidates(p, lds);
+    uint32_t all = sm.low;
     const int nlist = sm.nlist;
-    if (nlist > LIST) return false;  // uniform
-    if (tid < nlist) {
-        const u32x2 e = list[tid];
-        if (e[0] >= all) {
-            const int planes = (int)(e[1] >> 24), idx = (int)(e[1] & 0xffffffu);
-            if (planes == 0) {
-                const int k = atomicAdd(&sm.ncand, 1);
-                if (k < CAND) cand[k] = idx;
-            } else {
-                const int k = atomicAdd(&sm.ncand, planes);
-                for (int j = 0; j < planes; ++j)
-                    if (k + j < CAND) cand[k + j] = idx + j * sxy;
-            }
+    if (nlist > LIST) return 0;  // uniform
+    const u32x2 e = tid < nlist ? list[tid] : u32x2{0, 0};
+    const int planes = (int)(e[1] >> 24), idx = (int)(e[1] & 0xffffffu);
+    uint32_t top = e[0];
+    if (top >= all && planes == 0) {
+        const int iz = quotient(idx, sxy), ir = idx - iz * sxy, iy = quotient(ir, sx);
+        const int64_t at_rec =
+            ((int64_t)(g.oz0 + iz - p.w[2] - g.loz) * p.oy + (g.oy0 + iy - p.w[1] - g.loy)) * p.ox +
+            (g.ox0 + ir - iy * sx - p.w[0] - g.lox);
+        const Rec rec = static_cast<const Rec *>(p.stats)[at_rec];
+        float m;
+        if constexpr (sizeof(Rec) == 16)
+            m = (float)((rec.s - (double)N * (double)c) * rec.r);
+        else  // sums of F - 2048
+            m = ((float)rec.s + (float)N * (2048.0f - c)) * rec.r;
+        const float r = (float)rec.r;
+        const float t = unordered(top) - ea * r;  // C r, to 2^-20 of its size and of ea r
+        const float own = EPS * (tnorm * sT) * sF * rsqrtf((float)N) * (1.0f + fabsf(m)) +
+                          0x1p-17f * (ea * r) + 0x1p-19f * fabsf(t);
+        if (r < 0x1p86f && own < ea * r) {  // (also not taken where a term is not a number)
+            atomicMax(&sm.low, ordered(t - own));
+            top = ordered(t + own);
         }
     }
     __syncthreads();
-    const int ncand = sm.ncand;
-    if (ncand > CAND || ncand < 1) return false;  // uniform
-    if (ncand == 1) {
-        best = cand[0];
-        return true;
-    }
-    constexpr int PER = 64 / LANES;  // candidates per wavefront step
-    const int sub = lane / LANES;
-    for (int k0 = wave * PER; k0 < ncand; k0 += NW * PER) {
-        const int k = k0 + sub;
-        const bool live = sub < PER && k < ncand;
-        Key key = 0;
-        exact(live ? cand[k] : -1, lane - sub * LANES, key);
-        if (live && lane == sub * LANES) keys[k] = key;
+    all = sm.low;
+    if (tid < nlist && top >= all) {
+        const int n = max(planes, 1);
+        const int k = atomicAdd(&sm.ncand, n);
+        for (int j = 0; j < n; ++j)
+            if (k + j < CAND) cand[k + j] = idx + j * sxy;
     }
     __syncthreads();
+    const int ncand = __builtin_amdgcn_readfirstlane(sm.ncand);
+    return ncand <= CAND ? ncand : 0;
+}
+
+// The best of the re-ranked candidates (keys in LDS beside them, published):
+// largest key, smallest shift index; INT_MAX where every key is a NaN.
+template <typename Key>
+__device__ inline int pick(const int *cand, const Key *keys, int ncand) {
     Key bk = -INFINITY;
     int bi = INT_MAX;
-    for (int k = lane; k < ncand; k += 64) {
+    for (int k = threadIdx.x & 63; k < ncand; k += 64) {
         const Key key = keys[k];
         const int i = cand[k];
         if (key > bk || (key == bk && i < bi)) {
@@ -669,16 +664,8 @@ __device__ __attribute__((always_inline)) inline bool search(
             bi = i;
         }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        const Key ok = __shfl_xor(bk, off);
-        const int oi = __shfl_xor(bi, off);
-        if (ok > bk || (ok == bk && oi < bi)) {
-            bk = ok;
-            bi = oi;
-        }
-    }
-    best = bi;
-    return bi != INT_MAX;
+    wave_best(bk, bi);
+    return __builtin_amdgcn_readlane(bi, 63);
 }
 
 }  // namespace filt
