@@ -22,6 +22,7 @@
 
 #include "nrr_internal.h"
 #include "stats_cols.h"
+#include "wave64.h"
 
 namespace nrr {
 namespace {
@@ -349,10 +350,10 @@ struct ThrShared {
 };
 
 // The select of one 1024-thread workgroup (see above), for at most NK * 1024
-// keys (NK key slots per thread).
-template <int NK = kThrKeys>
-__device__ __attribute__((always_inline)) inline void select_threshold_wg(
-    const uint64_t *__restrict__ keys, int64_t n, int64_t k, const int64_t *__restrict__ kd,
+// keys (NK key slots per thread); key(i) gives candidate i's.
+template <int NK, typename KeyOf>
+__device__ __attribute__((always_inline)) inline void select_threshold_of(
+    KeyOf key, int64_t n, int64_t k, const int64_t *__restrict__ kd,
     SelectState *__restrict__ st, const BoxGrid &G, int32_t *__restrict__ centers,
     ThrShared &sm) {
     static_assert(NK % 4 == 0 && NK <= kThrKeys, "whole scan entries, within the LDS tables");
@@ -374,7 +375,7 @@ __device__ __attribute__((always_inline)) inline void select_threshold_wg(
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
         const int64_t i = (int64_t)j * 1024 + tid;
-        kr[j] = i < n ? keys[i] : 0;
+        kr[j] = i < n ? key(i) : 0;
     }
     __syncthreads();
     uint64_t orv = 0;
@@ -549,6 +550,14 @@ __device__ __attribute__((always_inline)) inline void select_threshold_wg(
             centers[3 * pos + 2] = (int32_t)(iz * G.s[2] + (G.b[2] - 1) / 2);
         }
     }
+}
+
+template <int NK = kThrKeys>
+__device__ __attribute__((always_inline)) inline void select_threshold_wg(
+    const uint64_t *__restrict__ keys, int64_t n, int64_t k, const int64_t *__restrict__ kd,
+    SelectState *__restrict__ st, const BoxGrid &G, int32_t *__restrict__ centers,
+    ThrShared &sm) {
+    select_threshold_of<NK>([&](int64_t i) { return keys[i]; }, n, k, kd, st, G, centers, sm);
 }
 
 // NK key slots per thread: grids of at most NK * 1024 candidates.
@@ -798,27 +807,6 @@ __global__ __launch_bounds__(256) void k_compact(const uint64_t *__restrict__ ke
 }
 
 
-// Inclusive scan of one value per thread over a 1024-thread workgroup
-// (wavefront shuffles, then the 16 wavefront totals); `tot` gets the sum.
-__device__ inline int64_t wg_scan1024_ex(int64_t v, int64_t *s_w, int64_t *tot) {
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t o = __shfl_up(v, off);
-        if (lane >= off) v += o;
-    }
-    if (lane == 63) s_w[w] = v;
-    __syncthreads();
-    int64_t before = 0, all = 0;
-    for (int i = 0; i < 16; ++i) {
-        const int64_t x = s_w[i];
-        before += i < w ? x : 0;
-        all += x;
-    }
-    __syncthreads();
-    *tot = all;
-    return v + before;
-}
-
 // ------------------------------------------------------- selection variants
 //
 // Selection with a candidate mask and a connectivity pattern (the region
@@ -834,207 +822,9 @@ __device__ inline int64_t wg_scan1024_ex(int64_t v, int64_t *s_w, int64_t *tot) 
 // candidates' state and "ranked-above" neighbour masks in LDS.
 constexpr int kExCand = 24576;
 
-// Neighbour j (0..25) of the 26-neighbourhood, the centre skipped.
-__device__ inline void nb_offset(int j, int *dx, int *dy, int *dz) {
-    const int i = j < 13 ? j : j + 1;
-    *dx = i % 3 - 1;
-    *dy = (i / 3) % 3 - 1;
-    *dz = i / 9 - 1;
-}
-
 __device__ inline bool ranks_above(uint64_t ka, int64_t ia, uint64_t kb, int64_t ib) {
     return ka > kb || (ka == kb && ia < ib);
 }
-
-__global__ __launch_bounds__(1024) void k_select_ex(const uint64_t *__restrict__ keys, int64_t n,
-                                                    BoxGrid G, int nx, int ny,
-                                                    const uint8_t *__restrict__ mask,
-                                                    int connectivity, double fraction,
-                                                    int32_t *__restrict__ centers,
-                                                    int64_t *__restrict__ k_out) {
-    __shared__ uint8_t state[kExCand];       // 0 open, 1 taken, 2 left out, 3 outside the mask
-    __shared__ uint32_t above[kExCand];      // bit j: neighbour j ranks above
-    __shared__ uint32_t hist[2048];
-    __shared__ int64_t s_w[16];
-    __shared__ int s_changed;
-    __shared__ int32_t s_off[26];  // grid-index offset of neighbour j
-    __shared__ int8_t s_dir[26][4];  // the pattern's neighbours: j, dx, dy, dz
-    __shared__ int s_ndir;
-    __shared__ uint64_t s_prefix, s_mask;
-    __shared__ int64_t s_need;
-    const int tid = threadIdx.x;
-    const int gx = G.g[0], gy = G.g[1], gz = G.g[2];
-    // neighbours of the pattern: one, up to two, or up to three axis steps
-    const int max_steps = connectivity == 6 ? 1 : (connectivity == 18 ? 2 : (connectivity == 26 ? 3 : 0));
-    if (tid < 26) {
-        int dx, dy, dz;
-        nb_offset(tid, &dx, &dy, &dz);
-        s_off[tid] = (dz * gy + dy) * gx + dx;
-    }
-    if (tid == 0) {  // the neighbours the pattern looks at
-        int c = 0;
-        for (int j = 0; j < 26; ++j) {
-            int dx, dy, dz;
-            nb_offset(j, &dx, &dy, &dz);
-            if ((dx != 0) + (dy != 0) + (dz != 0) > max_steps) continue;
-            s_dir[c][0] = (int8_t)j;
-            s_dir[c][1] = (int8_t)dx;
-            s_dir[c][2] = (int8_t)dy;
-            s_dir[c][3] = (int8_t)dz;
-            ++c;
-        }
-        s_ndir = c;
-    }
-    __syncthreads();
-    const int ndir = s_ndir;
-    int64_t in_local = 0;
-    const int gxy = gx * gy;
-    for (int g = tid; g < (int)n; g += 1024) {  // n <= kExCand: 32-bit index arithmetic
-        const int iz = g / gxy, r = g - iz * gxy, iy = r / gx, ix = r - iy * gx;
-        bool in = true;
-        if (mask)
-            in = mask[((int64_t)(iz * G.s[2] + (G.b[2] - 1) / 2) * ny +
-                       (iy * G.s[1] + (G.b[1] - 1) / 2)) * nx +
-                      (ix * G.s[0] + (G.b[0] - 1) / 2)] != 0;
-        state[g] = in ? 0 : 3;
-        in_local += in;
-        uint32_t bits = 0;
-        const uint64_t kg = keys[g];
-        for (int t = 0; t < ndir; ++t) {
-            const int x = ix + s_dir[t][1], y = iy + s_dir[t][2], z = iz + s_dir[t][3];
-            if (x < 0 || y < 0 || z < 0 || x >= gx || y >= gy || z >= gz) continue;
-            const int q = (z * gy + y) * gx + x;
-            if (ranks_above(keys[q], q, kg, g)) bits |= 1u << s_dir[t][0];
-        }
-        above[g] = bits;
-    }
-    int64_t n_in;
-    (void)wg_scan1024_ex(in_local, s_w, &n_in);
-    // the count rule over the candidates inside the mask
-    double kd = floor(0.5 + (double)n_in * fraction);
-    const int64_t k = kd < 0 ? 0 : (kd > (double)n_in ? n_in : (int64_t)kd);
-    __syncthreads();
-    // greedy set by rounds (every candidate inside the mask when no pattern)
-    for (;;) {
-        if (tid == 0) s_changed = 0;
-        __syncthreads();
-        int changed = 0;
-        for (int g = tid; g < (int)n; g += 1024) {  // n <= kExCand
-            if (state[g] != 0) continue;
-            bool any_taken = false, all_out = true;
-            uint32_t bits = above[g];  // only neighbours inside the grid are flagged
-            while (bits) {
-                const int j = __ffs(bits) - 1;
-                bits &= bits - 1;
-                const uint8_t sq = state[g + s_off[j]];
-                any_taken |= sq == 1;
-                all_out &= sq >= 2;
-            }
-            if (any_taken) {
-                state[g] = 2;
-                changed = 1;
-            } else if (all_out) {
-                state[g] = 1;
-                changed = 1;
-            }
-        }
-        if (changed) s_changed = 1;
-        __syncthreads();
-        if (!s_changed) break;
-        __syncthreads();
-    }
-    // the K best of the taken candidates: radix select of the K-th key among them
-    int64_t t_local = 0;
-    for (int64_t g = tid; g < n; g += 1024) t_local += state[g] == 1;
-    int64_t n_taken;
-    (void)wg_scan1024_ex(t_local, s_w, &n_taken);
-    const int64_t want = k < n_taken ? k : n_taken;
-    uint64_t kth = 0;
-    int64_t take_eq = 0;
-    const bool all = want == n_taken;  // keep every taken candidate
-    if (!all) {
-        if (tid == 0) {
-            s_prefix = 0;
-            s_mask = 0;
-            s_need = want;
-        }
-        __syncthreads();
-        for (int hi = 63; hi >= 0; hi -= 11) {
-            const int shift = hi - 10 > 0 ? hi - 10 : 0, width = hi - shift + 1;
-            const uint64_t dmask = (width == 64 ? ~0ull : ((1ull << width) - 1)) << shift;
-            for (int i = tid; i < 2048; i += 1024) hist[i] = 0;
-            __syncthreads();
-            const uint64_t prefix = s_prefix, pm = s_mask;
-            for (int64_t g = tid; g < n; g += 1024) {
-                const uint64_t kv = keys[g];
-                if (state[g] == 1 && (kv & pm) == prefix) atomicAdd(&hist[(kv & dmask) >> shift], 1u);
-            }
-            __syncthreads();
-            const uint32_t a = hist[2047 - 2 * tid], b = hist[2046 - 2 * tid];
-            int64_t tot;
-            const int64_t incl = wg_scan1024_ex((int64_t)a + b, s_w, &tot);
-            const int64_t above_cnt = incl - a - b, need = s_need;
-            __syncthreads();
-            if (above_cnt < need && need <= incl) {
-                const bool first = above_cnt + a >= need;
-                const uint64_t d = (uint64_t)(first ? 2047 - 2 * tid : 2046 - 2 * tid);
-                s_need = need - (first ? above_cnt : above_cnt + a);
-                s_prefix = prefix | (d << shift);
-                s_mask = pm | dmask;
-            }
-            __syncthreads();
-        }
-        kth = s_prefix;
-        take_eq = s_need;
-    }
-    // ordered compaction: thread t owns candidates [t*per, (t+1)*per)
-    const int64_t per = (n + 1023) / 1024;
-    const int64_t lo = (int64_t)tid * per < n ? (int64_t)tid * per : n, hi = lo + per < n ? lo + per : n;
-    int64_t lg = 0, le = 0;
-    for (int64_t g = lo; g < hi; ++g) {
-        if (state[g] != 1) continue;
-        const uint64_t kv = keys[g];
-        lg += all || kv > kth;
-        le += !all && kv == kth;
-    }
-    int64_t tg, te;
-    int64_t gt_before = wg_scan1024_ex(lg, s_w, &tg) - lg;
-    int64_t eq_before = wg_scan1024_ex(le, s_w, &te) - le;
-    for (int64_t g = lo; g < hi; ++g) {
-        if (state[g] != 1) continue;
-        const uint64_t kv = keys[g];
-        const bool is_gt = all || kv > kth, is_eq = !all && kv == kth;
-        if (is_gt || (is_eq && eq_before < take_eq)) {
-            const int64_t pos = gt_before + (eq_before < take_eq ? eq_before : take_eq);
-            const int gi = (int)g, iz = gi / (gx * gy), r = gi - iz * gx * gy, iy = r / gx,
-                      ix = r - iy * gx;
-            centers[3 * pos + 0] = (int32_t)(ix * G.s[0] + (G.b[0] - 1) / 2);
-            centers[3 * pos + 1] = (int32_t)(iy * G.s[1] + (G.b[1] - 1) / 2);
-            centers[3 * pos + 2] = (int32_t)(iz * G.s[2] + (G.b[2] - 1) / 2);
-        }
-        gt_before += is_gt;
-        eq_before += is_eq;
-    }
-    if (tid == 0) *k_out = want;
-}
-
-// ---------------------------------------------- selection variants, large grids
-//
-// The same greedy rank-order set on grids of any size, in rounds.  The state
-// of each candidate (0 open, 1 taken, 2 left out, 3 outside the mask) and
-// the mask of its pattern neighbours ranked above it live in global memory.
-// A round launch gives each workgroup a tile of 8 x 8 x 8 candidates, which
-// it iterates in LDS until nothing in the tile changes, reading the states
-// of neighbours outside the tile from global memory (a state only ever goes
-// from open to final, and a candidate is decided only from final states, so
-// reading a neighbour late just delays a decision).  Each launch settles at
-// least the best candidate still open, whose ranked-above neighbours are all
-// final, so launches repeat until none is open.  The K best taken
-// candidates then come from the multi-workgroup radix select, on keys
-// remapped so that only taken candidates can be chosen (taken: key + 1, any
-// other: 0; the order among taken candidates is unchanged).
-constexpr int EXT = 8;  // tile edge (candidates)
-enum { EX_N_IN = 0, EX_OPEN = 1, EX_TAKEN = 3, EX_WANT = 4 };  // counters (EX_OPEN: 2 slots)
 
 struct ExDirs {
     int n;
@@ -1057,6 +847,143 @@ ExDirs ex_dirs(int connectivity) {
     }
     return d;
 }
+
+// Ranked-above masks of a small grid, one candidate per thread over the whole
+// chip: bit t for pattern neighbour t, bit 31 for a candidate outside the
+// mask.  (In the one-workgroup kernel these reads, a few dependent ones per
+// candidate and 22 candidates per thread, were a third of its time.)
+__global__ __launch_bounds__(256) void k_ex_bits(const uint64_t *__restrict__ keys, int n,
+                                                 BoxGrid G, int nx, int ny,
+                                                 const uint8_t *__restrict__ mask, ExDirs D,
+                                                 uint32_t *__restrict__ above) {
+    const int g = blockIdx.x * 256 + threadIdx.x;
+    if (g >= n) return;
+    const int gx = G.g[0], gy = G.g[1], gz = G.g[2], gxy = gx * gy;
+    const int iz = g / gxy, r = g - iz * gxy, iy = r / gx, ix = r - iy * gx;
+    bool in = true;
+    if (mask)
+        in = mask[((int64_t)(iz * G.s[2] + (G.b[2] - 1) / 2) * ny +
+                   (iy * G.s[1] + (G.b[1] - 1) / 2)) * nx +
+                  (ix * G.s[0] + (G.b[0] - 1) / 2)] != 0;
+    uint32_t bits = in ? 0u : 1u << 31;
+    const uint64_t kg = keys[g];
+    for (int t = 0; t < D.n; ++t) {
+        const int x = ix + D.dx[t], y = iy + D.dy[t], z = iz + D.dz[t];
+        const bool real = x >= 0 && y >= 0 && z >= 0 && x < gx && y < gy && z < gz;
+        const int q = real ? (z * gy + y) * gx + x : g;  // itself never ranks above itself
+        if (ranks_above(keys[q], q, kg, g)) bits |= 1u << t;
+    }
+    above[g] = bits;
+}
+
+// The rounds, the count and the selection of a small grid in one 1024-thread
+// workgroup (thread t holds candidates t + 1024 j).  A thread keeps the bits
+// of its open candidates, so a round visits only those; the K best of the
+// taken ones come from the one-workgroup radix select with the keys in
+// registers (taken: key + 1, any other: 0).  256x256x124, 22,032 candidates,
+// 6-connectivity inside an ellipsoid: 205 us when the set-up, six radix passes
+// over the keys in global memory and a serial compaction ran here.
+template <int NK>
+__global__ __launch_bounds__(1024) void k_select_ex(const uint64_t *__restrict__ keys, int n,
+                                                    BoxGrid G, ExDirs D, double fraction,
+                                                    const uint32_t *__restrict__ above_g,
+                                                    int32_t *__restrict__ centers,
+                                                    int64_t *__restrict__ k_out) {
+    constexpr int CAND = NK * 1024 < kExCand ? NK * 1024 : kExCand;
+    __shared__ union {
+        uint32_t above[CAND];  // bit t: pattern neighbour t ranks above
+        ThrShared thr;         // after the rounds
+    } u;
+    __shared__ uint8_t state[CAND];  // 0 open, 1 taken, 2 left out, 3 outside the mask
+    __shared__ int32_t s_off[26];    // grid-index offset of pattern neighbour t
+    __shared__ int s_changed[3], s_count[2][16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (tid < D.n) s_off[tid] = (D.dz[tid] * G.g[1] + D.dy[tid]) * G.g[0] + D.dx[tid];
+    if (tid < 3) s_changed[tid] = 0;
+    uint32_t a[NK];
+#pragma unroll
+    for (int j = 0; j < NK; ++j) a[j] = j * 1024 + tid < n ? above_g[j * 1024 + tid] : 1u << 31;
+    uint32_t open = 0;  // bit j: candidate t + 1024 j is open
+#pragma unroll
+    for (int j = 0; j < NK; ++j) {
+        const int g = j * 1024 + tid;
+        const bool in = !(a[j] >> 31);
+        open |= (uint32_t)in << j;
+        if (g < n) {
+            u.above[g] = a[j];
+            state[g] = in ? 0 : 3;
+        }
+    }
+    const int in_wave = wave_xor_sum(__popc(open));
+    if (lane == 0) s_count[0][w] = in_wave;
+    __syncthreads();
+    // greedy set by rounds (every candidate inside the mask when no pattern);
+    // three flags in turn, so that a round needs one barrier
+    uint32_t taken = 0;
+    for (int round = 0;; ++round) {
+        uint32_t left = open;
+        bool changed = false;
+        while (left) {
+            const int j = __ffs(left) - 1;
+            left &= left - 1;
+            const int g = j * 1024 + tid;
+            bool any_taken = false, all_out = true;
+            uint32_t bits = u.above[g];  // only neighbours inside the grid are flagged
+            while (bits) {
+                const int t = __ffs(bits) - 1;
+                bits &= bits - 1;
+                const uint8_t sq = *(volatile uint8_t *)&state[g + s_off[t]];
+                any_taken |= sq == 1;
+                all_out &= sq >= 2;
+            }
+            if (any_taken | all_out) {
+                state[g] = any_taken ? 2 : 1;
+                open &= ~(1u << j);
+                taken |= (uint32_t)!any_taken << j;
+                changed = true;
+            }
+        }
+        if (changed) s_changed[round % 3] = 1;
+        if (tid == 0) s_changed[(round + 1) % 3] = 0;
+        __syncthreads();
+        if (!s_changed[round % 3]) break;
+    }
+    const int taken_wave = wave_xor_sum(__popc(taken));
+    if (lane == 0) s_count[1][w] = taken_wave;
+    __syncthreads();
+    int64_t n_in = 0, n_taken = 0;
+    for (int i = 0; i < 16; ++i) {
+        n_in += s_count[0][i];
+        n_taken += s_count[1][i];
+    }
+    // the count rule over the candidates inside the mask
+    const double kd = floor(0.5 + (double)n_in * fraction);
+    const int64_t k = kd < 0 ? 0 : (kd > (double)n_in ? n_in : (int64_t)kd);
+    const int64_t want = k < n_taken ? k : n_taken;
+    if (tid == 0) *k_out = want;
+    __syncthreads();  // the rounds' masks make room for the select
+    select_threshold_of<NK>(
+        [&](int64_t i) { return state[i] == 1 ? keys[i] + 1 : (uint64_t)0; }, n, want, nullptr,
+        nullptr, G, centers, u.thr);
+}
+
+// ---------------------------------------------- selection variants, large grids
+//
+// The same greedy rank-order set on grids of any size, in rounds.  The state
+// of each candidate (0 open, 1 taken, 2 left out, 3 outside the mask) and
+// the mask of its pattern neighbours ranked above it live in global memory.
+// A round launch gives each workgroup a tile of 8 x 8 x 8 candidates, which
+// it iterates in LDS until nothing in the tile changes, reading the states
+// of neighbours outside the tile from global memory (a state only ever goes
+// from open to final, and a candidate is decided only from final states, so
+// reading a neighbour late just delays a decision).  Each launch settles at
+// least the best candidate still open, whose ranked-above neighbours are all
+// final, so launches repeat until none is open.  The K best taken
+// candidates then come from the multi-workgroup radix select, on keys
+// remapped so that only taken candidates can be chosen (taken: key + 1, any
+// other: 0; the order among taken candidates is unchanged).
+constexpr int EXT = 8;  // tile edge (candidates)
+enum { EX_N_IN = 0, EX_OPEN = 1, EX_TAKEN = 3, EX_WANT = 4 };  // counters (EX_OPEN: 2 slots)
 
 // Adds the workgroup's total of `c` to *dst with one atomic (the per-wavefront
 // atomics on one address serialise at L2 across thousands of wavefronts).
@@ -1313,11 +1240,17 @@ hipError_t launch_select_ex(const void *vol, nrr_dtype dtype, const int32_t dims
     if (n > kSelectExCand)
         return launch_select_ex_large(vol, dtype, dims, G, fraction, mask, connectivity, centers,
                                       k_device, workspace, stream);
-    SelectLayout L = select_layout(n);
-    uint64_t *keys = reinterpret_cast<uint64_t *>(static_cast<char *>(workspace) + L.keys_off);
+    const SelectLayout L = select_layout(n, true);
+    char *ws = static_cast<char *>(workspace);
+    uint64_t *keys = reinterpret_cast<uint64_t *>(ws + L.keys_off);
+    uint32_t *above = reinterpret_cast<uint32_t *>(ws + L.ex_above_off);
+    const ExDirs D = ex_dirs(connectivity);
     launch_keys(vol, dtype, dims, G, n, keys, stream);
-    hipLaunchKernelGGL(k_select_ex, dim3(1), dim3(1024), 0, stream, keys, n, G, dims[0], dims[1],
-                       mask, connectivity, fraction, centers, k_device);
+    hipLaunchKernelGGL(k_ex_bits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, keys,
+                       (int)n, G, dims[0], dims[1], mask, D, above);
+    const auto fn = n <= kSmallSelect ? k_select_ex<4> : k_select_ex<kExCand / 1024>;
+    hipLaunchKernelGGL(fn, dim3(1), dim3(1024), 0, stream, keys, (int)n, G, D, fraction, above,
+                       centers, k_device);
     return hipGetLastError();
 }
 
@@ -1414,8 +1347,9 @@ SelectLayout select_layout(int64_t n_candidates, bool variants) {
     L.ex_ctr_off = L.total;
     L.ex_state_off = L.ex_ctr_off + 256;
     L.ex_above_off = L.ex_state_off + align_up((size_t)n_candidates, 256);
-    if (variants && n_candidates > kSelectExCand)
-        L.total = L.ex_above_off + align_up((size_t)n_candidates * 4, 256);
+    // (small grids: the masks alone)
+    if (n_candidates <= kSelectExCand) L.ex_above_off = L.ex_ctr_off;
+    if (variants) L.total = L.ex_above_off + align_up((size_t)n_candidates * 4, 256);
     return L;
 }
 
