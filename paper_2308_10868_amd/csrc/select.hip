@@ -32,8 +32,8 @@ struct SelectState {
     int64_t take_eq;  // how many candidates with key == kth are kept (lowest indices)
 };
 
-// One wavefront per candidate block (grids whose candidates do not overlap,
-// or whose tile region is too large for the tiled kernel): lanes take the
+// One wavefront per candidate block (grids of more than 65535 candidate rows
+// along y or z): lanes take the
 // block's by*bz rows, sum them exactly in integers and reduce across the
 // wavefront.
 __global__ __launch_bounds__(256) void k_block_keys_u16(const uint16_t *__restrict__ vol, int nx,
@@ -67,12 +67,13 @@ __global__ __launch_bounds__(256) void k_block_keys_u16(const uint16_t *__restri
     if (lane == 0) keys[g] = (uint64_t)bx * by * bz * q - s * s;  // >= 0 by Cauchy-Schwarz
 }
 
-// Keys by candidate rows (grids whose candidates do not overlap in x and y):
-// a workgroup takes the candidates of one (y, z) grid row whose columns fit
-// in 64 voxels.  Lane t owns voxel column x0 + t; the four wavefronts split
-// the block's bz planes (every load a contiguous run of 64 voxels, a plane's
-// by rows issued together) and each candidate adds its bx columns of the
-// four partial sums from LDS.
+// Keys by candidate rows: a workgroup takes the candidates of one (y, z) grid
+// row whose columns fit in 64 voxels.  Lane t owns voxel column x0 + t; the four
+// wavefronts split the block's bz planes (every load a contiguous run of 64
+// voxels, a plane's by rows issued together) and each candidate adds its bx
+// columns of the four partial sums from LDS.  Rows that neighbouring candidate
+// rows share are read again (b / stride times along y), 128 contiguous bytes a
+// load.
 __global__ __launch_bounds__(256) void k_block_keys_u16_rows(const uint16_t *__restrict__ vol,
                                                              int nx, int ny, BoxGrid G, int cx,
                                                              uint64_t *__restrict__ keys) {
@@ -119,8 +120,8 @@ __global__ __launch_bounds__(256) void k_block_keys_u16_rows(const uint16_t *__r
     }
 }
 
-// Tiled keys for overlapping candidates (tile regions up to 120 voxels a side): a
-// workgroup takes 16 x 16 candidates in x and y at one candidate plane z.
+// Tiled keys for many small overlapping candidates (tile regions up to 120
+// voxels a side): a workgroup takes 16 x 16 candidates in x and y at one candidate plane z.
 // For each of the block's bz voxel planes it stages the tile's region
 // ((15 sx + bx) x (15 sy + by) voxels, rows along x, coalesced) in LDS, forms
 // for every region row the sums over each candidate column's bx voxels, and
@@ -1303,18 +1304,22 @@ hipError_t launch_select_ex_large(const void *vol, nrr_dtype dtype, const int32_
 // Ranking keys of every candidate of the grid G.
 void launch_keys(const void *vol, nrr_dtype dtype, const int32_t dims[3], const BoxGrid &G,
                  int64_t n, uint64_t *keys, hipStream_t stream) {
-    // overlapping candidates (stride below the edge in x or y) whose tile
-    // region fits: the tiled kernel; candidates apart in x and y: by grid
-    // rows; otherwise one wavefront per candidate
+    // by candidate rows, unless many small candidates share each voxel: at
+    // stride 1, and at strides up to 3 with edges up to 5, staging a tile's
+    // region once costs less (512x512x256 selections, rows / tiles: edge 5
+    // stride 2 852 / 788 us, edge 5 stride 3 319 / 311, edge 7 stride 2 909 /
+    // 991, edge 9 stride 5 166 / 271, edge 9 stride 7 112 / 224)
+    const int smin = G.s[0] < G.s[1] ? G.s[0] : G.s[1], bmax = G.b[0] > G.b[1] ? G.b[0] : G.b[1];
     const bool overlap = G.s[0] < G.b[0] || G.s[1] < G.b[1];
+    const bool tiles = overlap && (smin == 1 || (bmax <= 5 && smin <= 3));
     const int rx = ((KT - 1) * G.s[0] + G.b[0] + 1) & ~1, ry = (KT - 1) * G.s[1] + G.b[1];
-    if (dtype == NRR_U16 && overlap && rx <= KT_MAXR && ry <= KT_MAXR)
+    if (dtype == NRR_U16 && tiles && rx <= KT_MAXR && ry <= KT_MAXR)
         hipLaunchKernelGGL(k_block_keys_u16_tiled,
                            dim3((unsigned)((G.g[0] + KT - 1) / KT), (unsigned)((G.g[1] + KT - 1) / KT),
                                 (unsigned)G.g[2]),
                            dim3(256), (size_t)rx * ry * 2 + (size_t)ry * KT * 8, stream,
                            static_cast<const uint16_t *>(vol), dims[0], dims[1], G, keys);
-    else if (dtype == NRR_U16 && !overlap && G.g[1] <= 65535 && G.g[2] <= 65535) {
+    else if (dtype == NRR_U16 && G.g[1] <= 65535 && G.g[2] <= 65535) {
         const int cx = (64 - G.b[0]) / G.s[0] + 1;  // candidates of a row per workgroup
         hipLaunchKernelGGL(k_block_keys_u16_rows,
                            dim3((unsigned)((G.g[0] + cx - 1) / cx), (unsigned)G.g[1],
