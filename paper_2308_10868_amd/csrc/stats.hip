@@ -35,6 +35,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "nrr_internal.h"
 #include "stats_cols.h"
@@ -45,7 +47,7 @@ namespace {
 constexpr int TX = 64, TY = 4, ZC = 32, MAXB = 15, SEG = 4;  // ZC: most origin planes per run
 constexpr int PW = TX + MAXB - 1, PH = TY + MAXB - 1;
 constexpr int PATCH = PH * PW;
-constexpr int PER = (PATCH + 255) / 256;  // patch elements staged per thread
+constexpr int PER_MAX = (PATCH + 255) / 256;  // patch elements staged per thread
 
 // Workgroup barrier for LDS traffic only.  __syncthreads also orders global
 // memory, which on this architecture means waiting for every load in flight
@@ -57,17 +59,37 @@ __device__ inline void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// f(0) .. f(N - 1) with the index as a compile-time constant.
+template <typename F, int... I>
+__device__ __attribute__((always_inline)) inline void static_for_seq(
+    F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ __attribute__((always_inline)) inline void static_for(F &&f) {
+    static_for_seq(f, std::make_integer_sequence<int, N>());
+}
+
 // Body of the float statistics kernel.  V: staged voxel type, A/AQ: row and
 // plane sums of F and F^2, AS/AQQ: block sums, re-added from the ring of the
 // last bz plane sums.  Global loads run two planes ahead of the plane being
-// summed.
-template <typename V, typename A, typename AQ, typename AS, typename AQQ, typename Src,
+// summed.  B > 0: a cubic block of that edge, its sums unrolled and its ring in
+// registers (the planes of a run are stepped through in unrolled rounds of 2 B,
+// so that slots and load buffers are constants); 0: any block, the ring in LDS.
+// The order of every sum is the same.  What bounds it is the latency of the LDS
+// reads between a plane's two barriers: with the ring (half the LDS and its
+// traffic) out of LDS twice the workgroups share a CU.
+template <int B, typename V, typename A, typename AQ, typename AS, typename AQQ, typename Src,
           typename Conv, typename Emit>
-__device__ inline void stats_body(const Src *__restrict__ flt, int nx, int ny, int nz, int bx,
-                                  int by, int bz, int ox, int oy, int oz, int zc, int tile_x,
+__device__ inline void stats_body(const Src *__restrict__ flt, int nx, int ny, int nz, int bx_,
+                                  int by_, int bz_, int ox, int oy, int oz, int zc, int tile_x,
                                   int tile_y, int run, V *patch /*[2][PATCH]*/, A *rs, AQ *rq,
                                   A *ringP, AQ *ringQ, Conv conv, Emit emit) {
     const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;  // output (tx, ty)
+    const int bx = B > 0 ? B : bx_, by = B > 0 ? B : by_, bz = B > 0 ? B : bz_;
+    constexpr int PER = B > 0 ? ((TY + B - 1) * (TX + B - 1) + 255) / 256 : PER_MAX;
+    [[maybe_unused]] A regP[B > 0 ? B : 1];
+    [[maybe_unused]] AQ regQ[B > 0 ? B : 1];
     const int x0 = tile_x * TX, y0 = tile_y * TY, z0 = run * zc;
     const int ph = TY + by - 1, pw = TX + bx - 1;
     const int zend = min(z0 + zc + bz - 1, nz);  // input planes [z0, zend)
@@ -112,7 +134,8 @@ __device__ inline void stats_body(const Src *__restrict__ flt, int nx, int ny, i
     // one plane step; rn holds plane zi + 1 (fetched a step earlier), rf
     // receives plane zi + 2.  The loop runs two steps per iteration with the
     // buffers' roles swapped, so no register copy waits on a load in flight.
-    auto step = [&](int zi, Raw &rn, Raw &rf) {
+    auto step = [&](int zi, Raw &rn, Raw &rf, auto slot_c) {
+        constexpr int SLOT = decltype(slot_c)::value;  // of this plane (B > 0)
         const int cur = (zi - z0) & 1;
         const V *pc = patch + cur * PATCH;
         fetch(rf, zi + 2);
@@ -122,6 +145,7 @@ __device__ inline void stats_body(const Src *__restrict__ flt, int nx, int ny, i
             const V *row = pc + r * pw + xs;
             A sv = 0;
             AQ qv = 0;
+#pragma unroll(B > 0 ? B : 1)
             for (int k = 0; k < bx; ++k) {
                 const A v = (A)row[k];
                 sv += v;
@@ -141,21 +165,35 @@ __device__ inline void stats_body(const Src *__restrict__ flt, int nx, int ny, i
         lds_barrier();
         A P = 0;  // then along y
         AQ Q = 0;
+#pragma unroll(B > 0 ? B : 1)
         for (int k = 0; k < by; ++k) {
             P += rs[(ty + k) * TX + tx];
             Q += rq[(ty + k) * TX + tx];
         }
-        const int slot = (zi - z0) % bz;
-        ringP[slot * 256 + tid] = P;
-        ringQ[slot * 256 + tid] = Q;
+        if constexpr (B > 0) {
+            regP[SLOT] = P;
+            regQ[SLOT] = Q;
+        } else {
+            const int slot = (zi - z0) % bz;
+            ringP[slot * 256 + tid] = P;
+            ringQ[slot * 256 + tid] = Q;
+        }
         if (zi - z0 >= bz - 1) {  // the last bz plane sums give the block sums
             const int z = zi - bz + 1, x = x0 + tx, y = y0 + ty;
             if (x < ox && y < oy && z < oz) {
                 AS sb = 0;
                 AQQ qb = 0;
-                for (int k = 0; k < bz; ++k) {
-                    sb += (AS)ringP[k * 256 + tid];
-                    qb += (AQQ)ringQ[k * 256 + tid];
+                if constexpr (B > 0) {
+#pragma unroll
+                    for (int k = 0; k < B; ++k) {
+                        sb += (AS)regP[k];
+                        qb += (AQQ)regQ[k];
+                    }
+                } else {
+                    for (int k = 0; k < bz; ++k) {
+                        sb += (AS)ringP[k * 256 + tid];
+                        qb += (AQQ)ringQ[k * 256 + tid];
+                    }
                 }
                 emit(((int64_t)z * oy + y) * ox + x, sb, qb);
             }
@@ -165,9 +203,24 @@ __device__ inline void stats_body(const Src *__restrict__ flt, int nx, int ny, i
         for (int k = 0; k < PER; ++k) pn[tid + 256 * k] = value(rn, k);
         lds_barrier();
     };
-    for (int zi = z0; zi < zend; zi += 2) {
-        step(zi, r1, r2);
-        if (zi + 1 < zend) step(zi + 1, r2, r1);
+    if constexpr (B > 0) {
+        for (int zb = z0; zb < zend; zb += 2 * B)
+            static_for<2 * B>([&](auto u) {
+                constexpr int U = decltype(u)::value;
+                const std::integral_constant<int, U % B> slot;
+                if (zb + U < zend) {  // uniform
+                    if constexpr (U % 2 == 0)
+                        step(zb + U, r1, r2, slot);
+                    else
+                        step(zb + U, r2, r1, slot);
+                }
+            });
+    } else {
+        const std::integral_constant<int, 0> none;
+        for (int zi = z0; zi < zend; zi += 2) {
+            step(zi, r1, r2, none);
+            if (zi + 1 < zend) step(zi + 1, r2, r1, none);
+        }
     }
 }
 
@@ -184,27 +237,42 @@ __global__ __launch_bounds__(256) void k_stats_u16(const uint16_t *__restrict__ 
                             blockIdx.y * 4 + w, blockIdx.z, xch[w]);
 }
 
+// A float record from the block's sums.
+__device__ inline StatF32 record_f32(double n, double S, double QQ) {
+    const double nq = n * QQ;
+    const double var = nq - S * S;
+    StatF32 rec;
+    rec.s = S;
+    rec.r = var > 1e-12 * nq ? 1.0 / sqrt(var) : 0.0;
+    return rec;
+}
+
+// LDS of a float statistics workgroup but the ring.
+struct StatsF32Shared {
+    float patch[2 * PATCH + 256];
+    double rs[PH * TX], rq[PH * TX];
+};
+
+template <int B>
+__device__ __attribute__((always_inline)) inline void stats_f32_tile(
+    const float *__restrict__ flt, int nx, int ny, int nz, int bx, int by, int bz, int ox, int oy,
+    int oz, int zc, int tile_x, int tile_y, int run, StatsF32Shared &sm, double *ring,
+    StatF32 *__restrict__ out) {
+    const double n = (double)bx * by * bz;
+    stats_body<B, float, double, double, double, double>(
+        flt, nx, ny, nz, bx, by, bz, ox, oy, oz, zc, tile_x, tile_y, run, sm.patch, sm.rs, sm.rq,
+        ring, ring + (size_t)bz * 256, [](float v) { return v; },
+        [&](int64_t o, double S, double QQ) { out[o] = record_f32(n, S, QQ); });
+}
+
+template <int B>
 __global__ __launch_bounds__(256) void k_stats_f32(const float *__restrict__ flt, int nx, int ny,
                                                    int nz, int bx, int by, int bz, int ox, int oy,
                                                    int oz, int zc, StatF32 *__restrict__ out) {
-    __shared__ float patch[2 * PATCH + 256];
-    __shared__ double rs[PH * TX];
-    __shared__ double rq[PH * TX];
-    extern __shared__ __align__(16) unsigned char dyn_f32[];
-    double *ringP = reinterpret_cast<double *>(dyn_f32);
-    double *ringQ = reinterpret_cast<double *>(dyn_f32 + (size_t)bz * 256 * 8);
-    const double n = (double)bx * by * bz;
-    stats_body<float, double, double, double, double>(
-        flt, nx, ny, nz, bx, by, bz, ox, oy, oz, zc, blockIdx.x, blockIdx.y, blockIdx.z, patch, rs,
-        rq, ringP, ringQ, [](float v) { return v; },
-        [&](int64_t o, double S, double QQ) {
-            const double nq = n * QQ;
-            const double var = nq - S * S;
-            StatF32 rec;
-            rec.s = S;
-            rec.r = var > 1e-12 * nq ? 1.0 / sqrt(var) : 0.0;
-            out[o] = rec;
-        });
+    __shared__ StatsF32Shared sm;
+    extern __shared__ __align__(16) double dyn_f32[];
+    stats_f32_tile<B>(flt, nx, ny, nz, bx, by, bz, ox, oy, oz, zc, blockIdx.x, blockIdx.y,
+                      blockIdx.z, sm, dyn_f32, out);
 }
 
 // One cubic block edge's share of a several-edge float statistics launch.
@@ -223,30 +291,28 @@ struct StatsF32Jobs {
 // or y tiles leaves at once.  The same body and records as k_stats_f32.
 __global__ __launch_bounds__(256) void k_stats_f32_multi(const float *__restrict__ flt, int nx,
                                                          int ny, int nz, StatsF32Jobs J) {
-    __shared__ float patch[2 * PATCH + 256];
-    __shared__ double rs[PH * TX];
-    __shared__ double rq[PH * TX];
-    extern __shared__ __align__(16) unsigned char dyn_f32m[];
+    __shared__ StatsF32Shared sm;
+    extern __shared__ __align__(16) double dyn_f32m[];
     StatsF32Job jb = J.job[0];
 #pragma unroll
     for (int i = 1; i < kStatsJobs; ++i)  // constant indices: the table stays in kernel arguments
         if (i < J.n && (int)blockIdx.z >= J.job[i].z_first) jb = J.job[i];
     if ((int)blockIdx.x >= jb.tiles_x || (int)blockIdx.y >= jb.tiles_y) return;
-    double *ringP = reinterpret_cast<double *>(dyn_f32m);
-    double *ringQ = reinterpret_cast<double *>(dyn_f32m + (size_t)jb.b * 256 * 8);
-    const double n = (double)jb.b * jb.b * jb.b;
-    StatF32 *out = jb.out;
-    stats_body<float, double, double, double, double>(
-        flt, nx, ny, nz, jb.b, jb.b, jb.b, jb.ox, jb.oy, jb.oz, jb.zc, blockIdx.x, blockIdx.y,
-        (int)blockIdx.z - jb.z_first, patch, rs, rq, ringP, ringQ, [](float v) { return v; },
-        [&](int64_t o, double S, double QQ) {
-            const double nq = n * QQ;
-            const double var = nq - S * S;
-            StatF32 rec;
-            rec.s = S;
-            rec.r = var > 1e-12 * nq ? 1.0 / sqrt(var) : 0.0;
-            out[o] = rec;
-        });
+    switch (jb.b) {
+#define NRR_JOB(B)                                                                              \
+    case B:                                                                                     \
+        stats_f32_tile<B>(flt, nx, ny, nz, B, B, B, jb.ox, jb.oy, jb.oz, jb.zc, blockIdx.x,     \
+                          blockIdx.y, (int)blockIdx.z - jb.z_first, sm, dyn_f32m, jb.out);      \
+        break;
+        NRR_JOB(5)
+        NRR_JOB(7)
+        NRR_JOB(9)
+#undef NRR_JOB
+    default:
+        stats_f32_tile<0>(flt, nx, ny, nz, jb.b, jb.b, jb.b, jb.ox, jb.oy, jb.oz, jb.zc,
+                          blockIdx.x, blockIdx.y, (int)blockIdx.z - jb.z_first, sm, dyn_f32m,
+                          jb.out);
+    }
 }
 
 // Plane-pair copy of a 12-bit volume: one 4-byte word per voxel holding the
@@ -433,9 +499,14 @@ hipError_t launch_stats(const void *flt, nrr_dtype dtype, const int32_t dims[3],
     }
     const int zc = f32_run_planes(L);
     dim3 grid((L.ox + TX - 1) / TX, (L.oy + TY - 1) / TY, (L.oz + zc - 1) / zc);
-    hipLaunchKernelGGL(k_stats_f32, grid, dim3(256), (size_t)bz * 256 * 16, stream,
-                       static_cast<const float *>(flt), dims[0], dims[1], dims[2], bx, by, bz,
-                       L.ox, L.oy, L.oz, zc, reinterpret_cast<StatF32 *>(ws));
+    const bool cubic = bx == by && by == bz;
+    const auto fn = cubic && bx == 5   ? k_stats_f32<5>
+                    : cubic && bx == 7 ? k_stats_f32<7>
+                    : cubic && bx == 9 ? k_stats_f32<9>
+                                       : k_stats_f32<0>;
+    hipLaunchKernelGGL(fn, grid, dim3(256), fn == k_stats_f32<0> ? (size_t)bz * 256 * 16 : 0,
+                       stream, static_cast<const float *>(flt), dims[0], dims[1], dims[2], bx, by,
+                       bz, L.ox, L.oy, L.oz, zc, reinterpret_cast<StatF32 *>(ws));
     return hipGetLastError();
 }
 
@@ -516,7 +587,8 @@ hipError_t launch_stats_f32_multi(const float *flt, const int32_t dims[3], const
         j.out = static_cast<StatF32 *>(outs[i]);
         gx = std::max(gx, j.tiles_x);
         gy = std::max(gy, j.tiles_y);
-        maxb = std::max(maxb, (int)blocks[i]);
+        if (blocks[i] != 5 && blocks[i] != 7 && blocks[i] != 9)  // its ring is in LDS
+            maxb = std::max(maxb, (int)blocks[i]);
     }
     hipLaunchKernelGGL(k_stats_f32_multi, dim3((unsigned)gx, (unsigned)gy, (unsigned)gz), dim3(256),
                        (size_t)maxb * 256 * 16, stream, flt, dims[0], dims[1], dims[2], J);
