@@ -132,13 +132,14 @@ constexpr int KT = 16, KT_MAXR = 120;  // region edge 15 s + b at most 120
 __global__ __launch_bounds__(256) void k_block_keys_u16_tiled(const uint16_t *__restrict__ vol,
                                                               int nx, int ny, BoxGrid G,
                                                               uint64_t *__restrict__ keys) {
-    // dynamic LDS: the region [RY][RX] (u16, RX even), then the row sums
-    // [RY][KT] and sums of squares [RY][KT] (u32); RX, RY of a full tile
+    // dynamic LDS: the row sums of squares [RY][KT] (64 bits, as in the other
+    // key kernels: any 16-bit voxels), the row sums [RY][KT], then the region
+    // [RY][RX] (u16, RX even); RX, RY of a full tile
     extern __shared__ __align__(16) unsigned char lds_keys[];
     const int RX = ((KT - 1) * G.s[0] + G.b[0] + 1) & ~1, RY = (KT - 1) * G.s[1] + G.b[1];
-    uint16_t *reg = reinterpret_cast<uint16_t *>(lds_keys);
-    uint32_t *rsum = reinterpret_cast<uint32_t *>(lds_keys + (size_t)RX * RY * 2);
-    uint32_t *rsq = rsum + RY * KT;
+    uint64_t *rsq = reinterpret_cast<uint64_t *>(lds_keys);
+    uint32_t *rsum = reinterpret_cast<uint32_t *>(rsq + RY * KT);
+    uint16_t *reg = reinterpret_cast<uint16_t *>(rsum + RY * KT);
     const int tid = threadIdx.x;
     const int bx = G.b[0], by = G.b[1], bz = G.b[2];
     const int cx0 = blockIdx.x * KT, cy0 = blockIdx.y * KT, cz = blockIdx.z;
@@ -158,7 +159,8 @@ __global__ __launch_bounds__(256) void k_block_keys_u16_tiled(const uint16_t *__
         for (int e = tid; e < ry * ncx; e += 256) {  // row r, candidate column ci
             const int r = e / ncx, ci = e - r * ncx;
             const uint16_t *row = reg + r * RX + ci * G.s[0];
-            uint32_t a = 0, b2 = 0;  // bx <= 120 voxels: < 2^32
+            uint32_t a = 0;  // bx <= 120 voxels: < 2^32
+            uint64_t b2 = 0;
             for (int k = 0; k < bx; ++k) {
                 const uint32_t v = row[k];
                 a += v;
@@ -1317,7 +1319,7 @@ void launch_keys(const void *vol, nrr_dtype dtype, const int32_t dims[3], const 
         hipLaunchKernelGGL(k_block_keys_u16_tiled,
                            dim3((unsigned)((G.g[0] + KT - 1) / KT), (unsigned)((G.g[1] + KT - 1) / KT),
                                 (unsigned)G.g[2]),
-                           dim3(256), (size_t)rx * ry * 2 + (size_t)ry * KT * 8, stream,
+                           dim3(256), (size_t)rx * ry * 2 + (size_t)ry * KT * 12, stream,
                            static_cast<const uint16_t *>(vol), dims[0], dims[1], G, keys);
     else if (dtype == NRR_U16 && G.g[1] <= 65535 && G.g[2] <= 65535) {
         const int cx = (64 - G.b[0]) / G.s[0] + 1;  // candidates of a row per workgroup
