@@ -316,9 +316,7 @@ bool holds_pairs(const void *ws) {
 
 // Does the search planned for these sizes read the plane-pair volume?
 bool plan_reads_pairs(nrr_dtype dtype, const nrr::MatchArgs &a) {
-    if (dtype != NRR_U16) return false;
-    nrr::TileShape t;
-    return !nrr::match_plan(dtype, a, &t) || t.arith == 0;
+    return nrr::match_reads_pairs(dtype, a);
 }
 
 nrr_status run_match(const void *ref, const void *flt, nrr_dtype dtype, const int32_t dims[3],

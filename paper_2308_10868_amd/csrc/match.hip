@@ -1066,6 +1066,375 @@ __global__ __launch_bounds__(256, FiltShape<B>::WAVES) void k_match_f32_filtered
     match_one_filtered<B>(p, fa, p.first + xcd_block(blockIdx.x, gridDim.x), lds, sm, fs);
 }
 
+// ------------------------------------------------- large blocks of 12-bit data
+//
+// Block edges 11, 13 and 15 by 8-bit matrix instructions, exactly: a voxel less
+// 2048 is 64 hi + lo with hi in [-32, 31] and lo in [0, 63], the cross term is
+// 4096 hi hi + 64 (hi lo + lo hi) + lo lo, and each part sums exactly in int32.
+// The ranking and the winner's NCC are the dot2 form's, on the same integers, so
+// the results are its bits.
+//
+// A tile is 16 rows (window bases 4 apart in x and y, and z phases) by the 16
+// (dx, dy) offsets of a 4x4 patch; a block plane is WideShape::NS chunks of 64 voxels, the
+// block a Toeplitz operand.  A 13^3 block's operands need more registers than
+// a wavefront has, so each of the four wavefronts holds a quarter of the block
+// planes (operands in registers for the whole search), sweeps the window's
+// planes with a ring of TW accumulators, and adds its share of each finished
+// displacement plane to 64-bit sums in LDS (integers: the order does not
+// matter).
+//
+// What bounds the dot2 form is its vector issue; here it is the latency of the
+// phases before the sweep, and at many blocks the matrix cores (half their
+// 8-bit rate at edge 13).  192x192x96 voxels, dot2 form / this, us: edge 11,
+// 400 blocks, W = 3 33 / 17, W = 6 83 / 30, W = 12 473 / 162; edge 13, 400
+// blocks, W = 6 134 / 35, 3000 blocks 716 / 186; edge 15, 250 blocks, W = 10
+// 582 / 93.  The records are read after the sweep: held through it they spill
+// (45 us at edge 13), as do the next plane's operands (37).
+template <int B>
+struct WideShape {
+    static constexpr int GX = (B + 6) / 4;  // 4-voxel groups of a row that any offset touches
+    static constexpr int RY = B + 3;        // rows
+    // K order: rows of four groups, then (edge 15) the fifth group of four rows each
+    static constexpr int XG = GX > 4 ? (RY + 3) / 4 : 0;
+    static constexpr int NG = RY + XG, NS = (NG + 3) / 4;
+    static constexpr int TW = (B + 3) / 4;  // block planes of a wavefront
+    static constexpr int PT = 4 * GX;       // T table: row pitch, rows (three above), bytes
+    static constexpr int TY = 3 + (XG ? 4 * XG : RY);
+    static constexpr int COPY = B * TY * PT;
+    static constexpr int WAVES = B == 15 ? 1 : 2;
+};
+constexpr int kWideTz = 13;     // displacement planes of a phase at most
+constexpr int kWideKeep = 12;   // window chunks a thread holds while the operands are built
+constexpr int kWideSlack = 8;   // window rows read past the last plane (against zeros)
+
+typedef int int4v __attribute__((ext_vector_type(4)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+typedef uint32_t uint4u __attribute__((ext_vector_type(4), aligned(2)));
+typedef int int4a __attribute__((ext_vector_type(4), aligned(4)));
+
+struct WideSizes {
+    int lo_off, x_off;  // LDS: hi bytes at 0, lo bytes, 64-bit sums
+    int tz, lds;
+};
+
+// Displacement planes per phase: as few 16-row tiles and sweep steps as may be.
+__host__ __device__ inline int wide_phase(int nxy, int dzn, int tw) {
+    int best = 1, bc = INT_MAX;
+    for (int tz = 1; tz <= (dzn < kWideTz ? dzn : kWideTz); ++tz) {
+        const int tiles = (nxy * ((dzn + tz - 1) / tz) + 15) / 16;
+        const int c = tiles * ((tz + 2 * tw - 2) / tw * tw + 2);  // + 2: the tile's ranking
+        if (c < bc) {
+            bc = c;
+            best = tz;
+        }
+    }
+    return best;
+}
+
+template <int B>
+bool wide_sizes(int w, size_t limit, WideSizes *s) {
+    using S = WideShape<B>;
+    const int d = 2 * w + 1, nb = (d + 3) / 4;
+    const int pitch = (4 * (nb - 1) + S::PT + 7) / 8 * 8, e = d + B - 1;
+    const size_t half = ((size_t)e * e + kWideSlack) * pitch;
+    s->lo_off = (int)half;
+    s->x_off = (int)((std::max(2 * half, (size_t)8 * S::COPY) + 15) / 16 * 16);
+    s->tz = wide_phase(nb * nb, d, S::TW);
+    // (blocks at the volume's faces may take more planes per phase)
+    s->lds = s->x_off + std::min(d, kWideTz) * 2048;
+    return (size_t)s->lds <= limit;
+}
+
+template <int B>
+__global__ __launch_bounds__(256, WideShape<B>::WAVES) void k_match_wide(Params p, WideSizes z) {
+    using S = WideShape<B>;
+    constexpr int H = (B - 1) / 2, N = B * B * B, NT = 256, TW = S::TW, NS = S::NS, PT = S::PT;
+    constexpr int TPT = (N + NT - 1) / NT;
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ double s_red[12];
+    __shared__ float s_key[4];
+    __shared__ int s_idx[4];
+    const int64_t blk = p.first + xcd_block(blockIdx.x, gridDim.x);
+    const int tid = threadIdx.x, lane = tid & 63, grp = lane >> 4, n16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const Geom g = make_geom(p, blk, H);
+    if (!g.inside) {
+        if (tid == 0) write_result(p, blk, 0, 0, 0, NAN);
+        return;
+    }
+    const uint16_t *ref = static_cast<const uint16_t *>(p.ref);
+    const uint16_t *flt = static_cast<const uint16_t *>(p.flt);
+    const int nxy = p.nx * p.ny;
+    const uint16_t *tb = ref + ((int64_t)(g.cz - H) * p.ny + (g.cy - H)) * p.nx + (g.cx - H);
+    auto voxel = [&](int o) {  // offset of the block's voxel o
+        const int oz = o / (B * B), oy = (o / B) % B, ox = o % B;
+        return oz * nxy + oy * p.nx + ox;
+    };
+
+    // ---- the block's voxels and the window's first chunks, in flight together
+    uint16_t tv[TPT];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) tv[k] = tb[voxel(min(tid + k * NT, N - 1))];
+    const int nbx = (g.dx + 3) / 4, nby = (g.dy + 3) / 4;
+    const int ey = g.dy + B - 1, ez = g.dz + B - 1;
+    const int cpr = (4 * (nbx - 1) + PT + 7) / 8, pitch = 8 * cpr, plane = ey * pitch;
+    const int nchunk = ez * ey * cpr;
+    const int64_t w0 = ((int64_t)g.wz0 * p.ny + g.wy0) * p.nx + g.wx0;
+    const uint16_t *wb = flt + w0;
+    const int64_t end = (int64_t)nxy * p.nz - 1 - w0;  // the volume's last voxel
+    const bool edge = (int64_t)(ez - 1) * nxy + (int64_t)(ey - 1) * p.nx + 8 * cpr - 1 > end;
+    auto load = [&](int i) {  // 8 voxels of a window row (past the row's end: its neighbours)
+        i = min(i, nchunk - 1);
+        const int row = quotient(i, cpr), xc = i - row * cpr;
+        const int zz = quotient(row, ey), yy = row - zz * ey;
+        const int at = zz * nxy + yy * p.nx + 8 * xc;
+        if (edge) {  // uniform: voxel by voxel, clamped to the volume's last
+            uint4v v = {0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                v[j / 2] |= (uint32_t)wb[min((int64_t)at + j, end)] << (16 * (j & 1));
+            return v;
+        }
+        return __builtin_bit_cast(uint4v, *reinterpret_cast<const uint4u *>(wb + at));
+    };
+    uint4v wv[kWideKeep];
+#pragma unroll
+    for (int k = 0; k < kWideKeep; ++k)
+        if (k * NT < nchunk) wv[k] = load(tid + k * NT);
+
+    // ---- T tables: hi and lo bytes, four copies each (copy a moved right by a
+    // columns), rows of zeros around each plane
+    for (int i = tid; i < S::COPY / 2; i += NT)
+        *reinterpret_cast<int4v *>(lds + 16 * i) = int4v{0, 0, 0, 0};
+    __syncthreads();
+    double st[2] = {0.0, 0.0};  // exact sums of T and T^2
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (tid + k * NT < N) {
+            const int o = tid + k * NT, oz = o / (B * B), oy = (o / B) % B, ox = o % B;
+            const int v = tv[k];
+            st[0] += (double)v;
+            st[1] += (double)v * (double)v;
+            unsigned char *d = lds + (oz * S::TY + oy + 3) * PT + ox;
+            const int hi = (v - 2048) >> 6, lo = v & 63;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                d[a * S::COPY + a] = (unsigned char)hi;
+                d[(4 + a) * S::COPY + a] = (unsigned char)lo;
+            }
+        }
+    wg_sum<NT, double, 2>(st, s_red);  // its barriers publish the tables
+    const long long st0 = (long long)st[0], st1 = (long long)st[1];
+    if (N * st1 - st0 * st0 == 0) {  // flat block: all NCC are 0
+        if (tid == 0) write_result(p, blk, g.lox, g.loy, g.loz, 0.0f);
+        return;
+    }
+    const int tau0 = wave * TW;
+    int4v bh[TW][NS], bl[TW][NS];
+    {
+        const int oa = n16 & 3, ob = n16 >> 2;
+        const unsigned char *t0 = lds + oa * S::COPY;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int gi = 4 * s + grp;
+            const bool main = gi < S::RY, real = gi < S::NG;
+            const int row = main ? gi : 4 * (gi - S::RY), step = main ? 4 : PT;
+            const int at = real ? (row - ob + 3) * PT + (main ? 0 : 16) : 0;
+#pragma unroll
+            for (int j = 0; j < TW; ++j) {
+                const bool on = real && tau0 + j < B;
+                const unsigned char *q = t0 + (on ? (tau0 + j) * S::TY * PT + at : 0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int h = *reinterpret_cast<const int *>(q + e * step);
+                    const int l = *reinterpret_cast<const int *>(q + 4 * S::COPY + e * step);
+                    bh[j][s][e] = on ? h : 0;
+                    bl[j][s][e] = on ? l : 0;
+                }
+            }
+        }
+    }
+    __syncthreads();  // every wavefront's operands are built: the window takes their place
+
+    // ---- the window's hi and lo bytes
+    auto store = [&](int i, const uint4v &v) {
+        if (i >= nchunk) return;
+        uint32_t h[2], l[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t a = v[2 * e], b = v[2 * e + 1];
+            l[e] = __builtin_amdgcn_perm(b, a, 0x06040200) & 0x3f3f3f3fu;
+            // per byte (v >> 6) - 32 without a borrow between bytes
+            const uint32_t q = __builtin_amdgcn_perm(b >> 6, a >> 6, 0x06040200);
+            h[e] = ((q | 0x80808080u) - 0x20202020u) ^ 0x80808080u;
+        }
+        *reinterpret_cast<uint2 *>(lds + 8 * i) = make_uint2(h[0], h[1]);
+        *reinterpret_cast<uint2 *>(lds + z.lo_off + 8 * i) = make_uint2(l[0], l[1]);
+    };
+#pragma unroll
+    for (int k = 0; k < kWideKeep; ++k)
+        if (k * NT < nchunk) store(tid + k * NT, wv[k]);
+    for (int i = tid + kWideKeep * NT; i < nchunk; i += 4 * NT) {
+        uint4v v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = load(i + k * NT);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) store(i + k * NT, v[k]);
+    }
+    unsigned long long *xs = reinterpret_cast<unsigned long long *>(lds + z.x_off);
+    const bool whole = g.dx == 2 * p.w + 1 && g.dy == 2 * p.w + 1 && g.dz == 2 * p.w + 1;
+    const int tz = whole ? z.tz : wide_phase(nbx * nby, g.dz, TW);
+    for (int i = tid; i < tz * 256; i += NT) xs[i] = 0;
+    __syncthreads();
+
+    // ---- sweep
+    const int nb = nbx * nby, nrows = nb * ((g.dz + tz - 1) / tz);
+    const int side = 2 * p.w + 1, plane_rec = p.oy * p.ox;
+    const StatU16 *rec0 = static_cast<const StatU16 *>(p.stats) +
+                          ((int64_t)g.wz0 * p.oy + g.wy0) * p.ox + g.wx0;
+    const double dN = (double)N, tsum = (double)(st0 - 2048ll * N);
+    int aoff[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int gi = 4 * s + grp;
+        aoff[s] = gi < S::RY ? gi * pitch : gi < S::NG ? 4 * (gi - S::RY) * pitch + 16 : 0;
+    }
+    float bk = -INFINITY;
+    int bi = INT_MAX;
+    for (int r0 = 0; r0 < nrows; r0 += 16) {
+        // the records of this thread's displacements: row tid / 16, offset tid % 16
+        const int rr = r0 + (tid >> 4), rc = rr < nrows ? rr : 0;
+        const int rph = quotient(rc, nb) , rxy = rc - rph * nb;
+        const int ryi = quotient(rxy, nbx), rxi = rxy - ryi * nbx;
+        const int dx = 4 * rxi + (tid & 3), dy = 4 * ryi + (tid >> 2 & 3), dz0 = rph * tz;
+        int abase, alim;
+        {
+            const int r = r0 + n16 < nrows ? r0 + n16 : 0;
+            const int ph = quotient(r, nb), xy = r - ph * nb;
+            const int yi = quotient(xy, nbx), xi = xy - yi * nbx;
+            abase = ph * tz * plane + 4 * yi * pitch + 4 * xi;
+            alim = ez - 1 - ph * tz;
+        }
+        int4v hh[TW], hl[TW], ll[TW];
+#pragma unroll
+        for (int j = 0; j < TW; ++j) hh[j] = hl[j] = ll[j] = int4v{0, 0, 0, 0};
+        auto read = [&](int at, auto sc, int4v &ah, int4v &al) __attribute__((always_inline)) {
+            constexpr int s = decltype(sc)::value;
+            const unsigned char *q = lds + at + aoff[s];
+            if constexpr (4 * s + 3 < S::RY || S::XG == 0) {
+                ah = *reinterpret_cast<const int4a *>(q);
+                al = *reinterpret_cast<const int4a *>(q + z.lo_off);
+            } else {
+                const int step = 4 * s + grp < S::RY ? 4 : pitch;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    ah[e] = *reinterpret_cast<const int *>(q + e * step);
+                    al[e] = *reinterpret_cast<const int *>(q + e * step + z.lo_off);
+                }
+            }
+        };
+        int4v ah, al;  // the window's chunk at hand; the next one is read early
+        int at = abase + min(tau0, alim) * plane;
+        read(at, std::integral_constant<int, 0>(), ah, al);
+        for (int u0 = 0; u0 < tz + TW - 1; u0 += TW) {
+            filt::static_for<TW>([&](auto uc) __attribute__((always_inline)) {
+                constexpr int u = decltype(uc)::value;
+                filt::static_for<NS>([&](auto sc) __attribute__((always_inline)) {
+                    constexpr int s = decltype(sc)::value;
+                    int4v nh, nl;
+                    if constexpr (s == NS - 1) at = abase + min(tau0 + u0 + u + 1, alim) * plane;
+                    read(at, std::integral_constant<int, (s + 1) % NS>(), nh, nl);
+#pragma unroll
+                    for (int j = 0; j < TW; ++j) {
+                        const int k = (u - j + TW) % TW;
+                        hh[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah, bh[j][s], hh[k], 0, 0, 0);
+                        hl[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah, bl[j][s], hl[k], 0, 0, 0);
+                        ll[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al, bl[j][s], ll[k], 0, 0, 0);
+                        hl[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al, bh[j][s], hl[k], 0, 0, 0);
+                    }
+                    ah = nh;
+                    al = nl;
+                });
+                constexpr int f = (u + 1) % TW;  // the slot whose last block plane this was
+                const int dzl = u0 + u - (TW - 1);
+                if (dzl >= 0 && dzl < tz) {  // uniform
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        atomicAdd(&xs[(dzl * 16 + 4 * grp + i) * 16 + n16],
+                                  (unsigned long long)((long long)hh[f][i] * 4096 +
+                                                       (long long)(hl[f][i] * 64 + ll[f][i])));
+                }
+                hh[f] = hl[f] = ll[f] = int4v{0, 0, 0, 0};
+            });
+        }
+        StatU16 rec[kWideTz];
+        {
+            const StatU16 *rb = rec0 + min(dy, g.dy - 1) * p.ox + min(dx, g.dx - 1);
+#pragma unroll
+            for (int k = 0; k < kWideTz; ++k) rec[k] = rb[(int64_t)min(dz0 + k, g.dz - 1) * plane_rec];
+        }
+        __syncthreads();  // the tile's cross terms
+        const bool on = rr < nrows && dx < g.dx && dy < g.dy;
+#pragma unroll
+        for (int k = 0; k < kWideTz; ++k)
+            if (k < tz) {
+                const double x = (double)(long long)xs[k * 256 + tid];
+                xs[k * 256 + tid] = 0;
+                // the dot2 form's key
+                const double cov = __builtin_fma(dN, x, -tsum * (double)rec[k].s);
+                const float key = (float)cov * rec[k].r;
+                const int idx = ((g.loz + dz0 + k + p.w) * side + (g.loy + dy + p.w)) * side +
+                                (g.lox + dx + p.w);
+                if (on && dz0 + k < g.dz) better(bk, bi, key, idx);
+            }
+        __syncthreads();  // cleared
+    }
+    wave_best(bk, bi);
+    if (lane == 63) {
+        s_key[wave] = bk;
+        s_idx[wave] = bi;
+    }
+    __syncthreads();
+    bk = s_key[0];
+    bi = s_idx[0];
+#pragma unroll
+    for (int i = 1; i < 4; ++i) better(bk, bi, s_key[i], s_idx[i]);
+    if (bi == INT_MAX) {  // no key compares (a table of NaNs): report, never index
+        if (tid == 0) write_result(p, blk, 0, 0, 0, NAN);
+        return;
+    }
+
+    // ---- exact NCC at the winning displacement, from the volumes
+    const int ddx = bi % side - p.w, ddy = (bi / side) % side - p.w, ddz = bi / (side * side) - p.w;
+    const uint16_t *fb = flt + ((int64_t)(g.cz - H + ddz) * p.ny + (g.cy - H + ddy)) * p.nx +
+                         (g.cx - H + ddx);
+    uint16_t fv[TPT];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) {
+        const int o = voxel(min(tid + k * NT, N - 1));
+        tv[k] = tb[o];
+        fv[k] = fb[o];
+    }
+    double sums[3] = {0.0, 0.0, 0.0};  // F, F^2, TF: exact
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)
+        if (tid + k * NT < N) {
+            const double f = (double)fv[k], t = (double)tv[k];
+            sums[0] += f;
+            sums[1] += f * f;
+            sums[2] += t * f;
+        }
+    wg_sum<NT, double, 3>(sums, s_red);
+    if (tid == 0) {
+        const long long f0 = (long long)sums[0];
+        const long long vt = N * st1 - st0 * st0;
+        const long long vf = N * (long long)sums[1] - f0 * f0;
+        const long long cv = N * (long long)sums[2] - st0 * f0;
+        const double v = (vt > 0 && vf > 0) ? (double)cv / sqrt((double)vt * (double)vf) : 0.0;
+        write_result(p, blk, ddx, ddy, ddz, (float)v);
+    }
+}
+
 // ------------------------------------------------------------ batched search
 //
 // Many parameter sets (block size, window, selection) over one volume pair in
@@ -1178,6 +1547,7 @@ __global__ __launch_bounds__(256, FiltShape<B>::WAVES) void k_match_batch_filter
 // ------------------------------------------------------------ dispatch
 
 typedef void (*kernel_t)(Params);
+typedef void (*kernel_wide_t)(Params, WideSizes);
 
 struct Variant {
     nrr_dtype dtype;
@@ -1513,6 +1883,27 @@ static bool wants_mfma(nrr_dtype dtype, int32_t block, int32_t window, const Til
     return true;
 }
 
+// The 8-bit matrix-core search serves 12-bit blocks with edges 11 to 15 whose
+// window fits in LDS beside its sums, by default: a shape or form asked for by
+// the caller (a tuner's trial, a pinned shape, an environment override) runs as
+// asked.  Voxel offsets from the window's corner are 32-bit.
+static kernel_wide_t wide_plan(nrr_dtype dtype, const MatchArgs &a, const TileShape *shape,
+                               WideSizes *z) {
+    if (dtype != NRR_U16 || shape || a.block < 11 || a.block > 15) return nullptr;
+    TileShape sh;
+    if (shape_from_env(&sh) || arith_preference() >= 0 || pinned_shape(dtype, a.block, a.window))
+        return nullptr;
+    const int e = 2 * a.window + a.block;
+    if ((int64_t)a.nx * a.ny * e >= (1ll << 31) || (int64_t)e * e * (e / 8 + 2) >= (1 << 20))
+        return nullptr;
+    const size_t limit = device_lds_limit() - 256;
+    switch (a.block) {
+    case 11: return wide_sizes<11>(a.window, limit, z) ? k_match_wide<11> : nullptr;
+    case 13: return wide_sizes<13>(a.window, limit, z) ? k_match_wide<13> : nullptr;
+    default: return wide_sizes<15>(a.window, limit, z) ? k_match_wide<15> : nullptr;
+    }
+}
+
 // The float search's launch behind the matrix-core filter.
 struct FiltPlan {
     filt::Args fa;
@@ -1604,6 +1995,14 @@ int match_shapes(nrr_dtype dtype, int32_t block, int32_t window, TileShape *out,
     return n < cap ? n : cap;
 }
 
+bool match_reads_pairs(nrr_dtype dtype, const MatchArgs &a) {
+    if (dtype != NRR_U16) return false;
+    TileShape t;
+    WideSizes z;
+    return !wide_plan(dtype, a, nullptr, &z) &&
+           (!match_plan(dtype, a, &t) || t.arith == DOT2);
+}
+
 bool match_plan(nrr_dtype dtype, const MatchArgs &a, TileShape *out) {
     if (mfma_fits(a) && wants_mfma(dtype, a.block, a.window, nullptr)) {
         *out = TileShape{kArithMfma, 0, 0, 256, -1, 0};
@@ -1650,15 +2049,18 @@ hipError_t launch_match(nrr_dtype dtype, const MatchArgs &a, hipStream_t stream,
         return launch_match_mfma(a, stream);
     Plan pl;
     FiltPlan fp;
+    WideSizes wz;
     const bool filtered = filt_plan(dtype, a, shape, &fp);
-    if (!filtered && !choose(dtype, a.block, a.window, device_lds_limit(), shape, &pl))
+    const kernel_wide_t wide = wide_plan(dtype, a, shape, &wz);
+    if (!filtered && !wide && !choose(dtype, a.block, a.window, device_lds_limit(), shape, &pl))
         return hipErrorInvalidValue;
     const auto ffn = a.block == 5 ? k_match_f32_filtered<5>
                      : a.block == 7 ? k_match_f32_filtered<7>
                                     : k_match_f32_filtered<9>;
     const void *fn = filtered ? reinterpret_cast<const void *>(ffn)
+                     : wide   ? reinterpret_cast<const void *>(wide)
                               : reinterpret_cast<const void *>(pl.v->fn);
-    const size_t lds = filtered ? fp.lds : pl.lds;
+    const size_t lds = filtered ? fp.lds : wide ? (size_t)wz.lds : pl.lds;
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess)
         return hipGetLastError();
@@ -1671,7 +2073,7 @@ hipError_t launch_match(nrr_dtype dtype, const MatchArgs &a, hipStream_t stream,
     p.centers = a.centers;
     p.n = a.n;
     p.w = a.window;
-    p.cz = filtered ? fp.cz : pl.cz;
+    p.cz = filtered ? fp.cz : wide ? 0 : pl.cz;
     p.stats = a.stats;
     p.pv = a.pairs;
     p.ox = a.ox;
@@ -1686,6 +2088,8 @@ hipError_t launch_match(nrr_dtype dtype, const MatchArgs &a, hipStream_t stream,
         const int64_t cnt = a.n - first < chunk ? a.n - first : chunk;
         if (filtered)
             hipLaunchKernelGGL(ffn, dim3((unsigned)cnt), dim3(256), lds, stream, p, fp.fa);
+        else if (wide)
+            hipLaunchKernelGGL(wide, dim3((unsigned)cnt), dim3(256), lds, stream, p, wz);
         else
             hipLaunchKernelGGL(pl.v->fn, dim3((unsigned)cnt), dim3(pl.v->nt), lds, stream, p);
     }

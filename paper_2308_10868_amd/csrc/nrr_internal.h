@@ -219,6 +219,8 @@ hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t stream);
 // The shape launch_match would use now (arith 0 dot2, 1 FMA, 2 MFMA); false
 // when no compiled shape serves.
 bool match_plan(nrr_dtype dtype, const MatchArgs &a, TileShape *out);
+// Does the default search of these sizes read the plane-pair volume?
+bool match_reads_pairs(nrr_dtype dtype, const MatchArgs &a);
 // Whether `sh` (cz ignored) is a compiled plain or batched shape for
 // (dtype, block, window).
 bool shape_known(nrr_dtype dtype, int32_t block, int32_t window, const TileShape &sh);

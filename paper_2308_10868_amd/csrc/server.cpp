@@ -269,8 +269,7 @@ hipError_t enqueue(nrr_server *S, Request &q) {
         a.ncc = reinterpret_cast<float *>(b + f.ncc);
         a.conf = reinterpret_cast<float *>(b + f.conf);
         // window statistics, with the plane-pair volume only for the dot2 form
-        nrr::TileShape t;
-        const bool pairs = r.dtype == NRR_U16 && (!nrr::match_plan(r.dtype, a, &t) || t.arith == 0);
+        const bool pairs = nrr::match_reads_pairs(r.dtype, a);
         const int32_t b3[3] = {r.block, r.block, r.block};
         if ((e = nrr::launch_stats(flt, r.dtype, r.dims, b3, pairs, b + f.stats, st)) != hipSuccess)
             return e;
