@@ -462,7 +462,11 @@ hipError_t launch_stats(const void *flt, nrr_dtype dtype, const int32_t dims[3],
     char *ws = static_cast<char *>(workspace);
     const int bx = block[0], by = block[1], bz = block[2];
     if (dtype == NRR_U16) {
-        const ColsGrid cg = cols_grid(L, bx);
+        // a run first sums bz planes: runs of one or two origin planes cost more
+        // than the wavefronts they add (192x192x96, runs of one plane / three,
+        // us: edge 9 24 / 17, 11 30 / 21, 13 32 / 24, 15 40 / 28; at bz = 3 one
+        // plane is best, 17.9 against 18.9)
+        const ColsGrid cg = cols_grid(L, bx, SC_WAVES, bz >= 9 ? 3 : bz >= 5 ? 2 : 1);
         const int zc = cg.zc;
         const dim3 grid((unsigned)cg.nwx, (unsigned)((cg.nwy + 3) / 4), (unsigned)cg.runs);
         StatU16 *out = reinterpret_cast<StatU16 *>(ws);

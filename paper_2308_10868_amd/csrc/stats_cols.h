@@ -23,6 +23,7 @@ __device__ inline void wave_lds_sync() {
 constexpr int SC_RY = 8;        // origin rows per wavefront
 constexpr int SC_LW = 64 + 16;  // LDS slots of a row: the lanes, then the x reach
 constexpr int SC_WAVES = 8192;  // wavefronts a launch aims at (z-runs are cut to reach it)
+constexpr int SC_FEW = 1536;    // wavefronts below which longer z-runs leave CUs idle
 
 // One wavefront of the 12-bit statistics by voxel columns.  BY: block edge
 // in y; BC: the cubic block edge when it is known at compile time (then bx =
@@ -156,18 +157,21 @@ __device__ __attribute__((always_inline)) inline void stats_cols_wave(
 }
 
 // Launch shape of the column statistics: x-tiles, y-tiles and z-runs of
-// zc origin planes, runs cut so the launch has about `target` wavefronts.
+// zc origin planes, runs cut so the launch has about `target` wavefronts, but
+// not below `zmin` planes while SC_FEW wavefronts remain.
 struct ColsGrid {
     int64_t nwx, nwy, runs;
     int zc;
 };
 
-inline ColsGrid cols_grid(const StatsLayout &L, int bx, int64_t target = SC_WAVES) {
+inline ColsGrid cols_grid(const StatsLayout &L, int bx, int64_t target = SC_WAVES, int zmin = 1) {
     ColsGrid c;
     const int txw = 65 - bx;
     c.nwx = (L.ox + txw - 1) / txw;
     c.nwy = (L.oy + SC_RY - 1) / SC_RY;
     int64_t runs = (target + c.nwx * c.nwy - 1) / (c.nwx * c.nwy);
+    const int64_t few = (SC_FEW + c.nwx * c.nwy - 1) / (c.nwx * c.nwy);
+    runs = std::min(runs, std::max((L.oz + zmin - 1) / (int64_t)zmin, few));
     runs = runs < 1 ? 1 : (runs > L.oz ? L.oz : runs);
     c.zc = (int)((L.oz + runs - 1) / runs);
     c.runs = (L.oz + c.zc - 1) / c.zc;
