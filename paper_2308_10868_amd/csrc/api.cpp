@@ -314,9 +314,12 @@ bool holds_pairs(const void *ws) {
     return g_pairs.find(ws) == g_pairs.end();
 }
 
-// Does the search planned for these sizes read the plane-pair volume?
+// Does the plan reported for these sizes read the plane-pair volume?  (What the
+// prepared statistics hold; nrr::match_reads_pairs is what the search reads.)
 bool plan_reads_pairs(nrr_dtype dtype, const nrr::MatchArgs &a) {
-    return nrr::match_reads_pairs(dtype, a);
+    if (dtype != NRR_U16) return false;
+    nrr::TileShape t;
+    return !nrr::match_plan(dtype, a, &t) || t.arith == 0;
 }
 
 nrr_status run_match(const void *ref, const void *flt, nrr_dtype dtype, const int32_t dims[3],
@@ -325,7 +328,7 @@ nrr_status run_match(const void *ref, const void *flt, nrr_dtype dtype, const in
                      const nrr::StatsLayout &L, hipStream_t st) {
     const nrr::MatchArgs a =
         match_args(ref, flt, dims, centers, n, block, window, disp, ncc, conf, workspace, L);
-    if (L.pair_off && plan_reads_pairs(dtype, a) && !holds_pairs(workspace)) {
+    if (L.pair_off && nrr::match_reads_pairs(dtype, a) && !holds_pairs(workspace)) {
         // statistics made for another plan: add the pair volume now
         hipError_t e = nrr::launch_pair_volume(static_cast<const uint16_t *>(flt), dims,
                                                const_cast<uint32_t *>(a.pairs), st);
@@ -591,10 +594,10 @@ nrr_status nrr_block_match(const void *ref, const void *flt, nrr_dtype dtype,
                                workspace, workspace_bytes, &L);
     if (s != NRR_OK || n == 0) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // the plane-pair volume only when the planned search reads it
+    // the plane-pair volume only when the search reads it
     const nrr::MatchArgs a =
         match_args(ref, flt, dims, centers, n, block, window, disp, ncc, conf, workspace, L);
-    const bool pairs = plan_reads_pairs(dtype, a);
+    const bool pairs = nrr::match_reads_pairs(dtype, a);
     note_pairs(workspace, pairs);
     const int32_t b3[3] = {block, block, block};
     hipError_t e = nrr::launch_stats(flt, dtype, dims, b3, pairs, workspace, st);

@@ -39,7 +39,7 @@ def test_same_bits_as_the_dot2_form(monkeypatch, kind, b, w):
     got2 = [to_host(t) for t in nrr.block_match(r, f, c, b, w, workspace=ws, prepared=True)]
     monkeypatch.setenv("NRR_ARITH", "dot2")
     want = [to_host(t) for t in nrr.block_match(r, f, c, b, w)]
-    # statistics made for the other search: the pair volume is added
+    # the prepared statistics serve either search
     late = [to_host(t) for t in nrr.block_match(r, f, c, b, w, workspace=ws, prepared=True)]
     for a, a2, e, e2, name in zip(got, got2, want, late, ("disp", "ncc", "conf")):
         for x in (a, a2, e2):
