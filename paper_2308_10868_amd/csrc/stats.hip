@@ -146,12 +146,15 @@ __device__ inline void stats_body(const Src *__restrict__ flt, int nx, int ny, i
             const V *row = pc + r * pw + xs;
             A sv = 0;
             AQ qv = 0;
-#pragma unroll(B > 0 ? B : 1)
-            for (int k = 0; k < bx; ++k) {
+            auto add = [&](int k) {
                 const A v = (A)row[k];
                 sv += v;
                 qv += (AQ)(v * v);
-            }
+            };
+            if constexpr (B > 0)
+                static_for<B>(add);
+            else
+                for (int k = 0; k < bx; ++k) add(k);
             rs[r * TX + xs] = sv;
             rq[r * TX + xs] = qv;
 #pragma unroll
@@ -166,11 +169,14 @@ __device__ inline void stats_body(const Src *__restrict__ flt, int nx, int ny, i
         lds_barrier();
         A P = 0;  // then along y
         AQ Q = 0;
-#pragma unroll(B > 0 ? B : 1)
-        for (int k = 0; k < by; ++k) {
+        auto add = [&](int k) {
             P += rs[(ty + k) * TX + tx];
             Q += rq[(ty + k) * TX + tx];
-        }
+        };
+        if constexpr (B > 0)
+            static_for<B>(add);
+        else
+            for (int k = 0; k < by; ++k) add(k);
         if constexpr (B > 0) {
             regP[SLOT] = P;
             regQ[SLOT] = Q;
@@ -560,10 +566,14 @@ hipError_t launch_stats(const void *flt, nrr_dtype dtype, const int32_t dims[3],
     const int zc = f32_run_planes(L);
     dim3 grid((L.ox + TX - 1) / TX, (L.oy + TY - 1) / TY, (L.oz + zc - 1) / zc);
     const bool cubic = bx == by && by == bz;
-    const auto fn = cubic && bx == 5   ? k_stats_f32<5>
-                    : cubic && bx == 7 ? k_stats_f32<7>
-                    : cubic && bx == 9 ? k_stats_f32<9>
-                                       : k_stats_f32<0>;
+    const auto fn = cubic && bx == 3    ? k_stats_f32<3>
+                    : cubic && bx == 5  ? k_stats_f32<5>
+                    : cubic && bx == 7  ? k_stats_f32<7>
+                    : cubic && bx == 9  ? k_stats_f32<9>
+                    : cubic && bx == 11 ? k_stats_f32<11>
+                    : cubic && bx == 13 ? k_stats_f32<13>
+                    : cubic && bx == 15 ? k_stats_f32<15>
+                                        : k_stats_f32<0>;
     hipLaunchKernelGGL(fn, grid, dim3(256), fn == k_stats_f32<0> ? (size_t)bz * 256 * 16 : 0,
                        stream, static_cast<const float *>(flt), dims[0], dims[1], dims[2], bx, by,
                        bz, L.ox, L.oy, L.oz, zc, reinterpret_cast<StatF32 *>(ws));

@@ -18,7 +18,7 @@ from tests.test_gpu_stats_table import box_sum
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("b", [3, 5, 7, 9, 11])
+@pytest.mark.parametrize("b", [3, 5, 7, 9, 11, 13, 15])
 @pytest.mark.parametrize("extra", [(0, 0, 0), (1, 2, 1), (63, 3, 5), (64, 4, 10), (70, 9, 41)])
 def test_float_statistics_are_exact(b, extra):
     import torch
