@@ -732,6 +732,24 @@ const Filtered kFiltered[] = {FILTERED(3, 2), FILTERED(3, 4), FILTERED(3, 5), FI
                               FILTERED(9, 5)};
 #undef FILTERED
 
+// Where the filter pays: it costs a block about the same whatever its window
+// (its phases wait for memory, and its tiles take whole block-deep runs of
+// planes), the FMA form its products per thread.  Measured over 107 random
+// sizes (edges 5-9, z 3 or 5; whole calls, FMA form / filter): all 40 of 3300
+// and more gain, 1.08 to 2.4x (9x9x5, window 11x21x11: 491 / 203 us); below,
+// thin blocks with many planes still do (7x7x3, 11x21x9: 75 / 47), the others
+// go either way, down to 0.7x (7x9x3, 13x9x3: 40 / 54).
+bool filter_pays(const AnisoArgs &a) {
+    AnisoPlan pl;
+    if (!aniso_plan(a.b, a.w, &pl)) return false;
+    const int64_t rx = pl.tile->rx, dx = 2 * a.w[0] + 1, dy = 2 * a.w[1] + 1, dz = 2 * a.w[2] + 1;
+    const int64_t tiles = (dx + rx - 1) / rx * dy * dz;
+    const int64_t rows = (int64_t)a.b[2] * a.b[1] * ((a.b[0] + TU - 1) / TU * TU);
+    // (wavefronts of 64 tiles, four of them a workgroup's turn)
+    const int64_t per = (tiles + 63) / 64 * rx * rows / 4 * std::min<int64_t>(dz, a.b[2]) / a.b[2];
+    return per >= 3300 || (a.b[2] == 3 && dz >= 9 && per >= 1200);
+}
+
 // The filter serves block edges up to 9 (z: 3 to 9) whose window fits in LDS
 // beside room for one plane run of the FMA form, with 32-bit record and voxel
 // offsets from the window's corner.  A form or tile asked for by the
@@ -746,6 +764,7 @@ filtered_t aniso_filter(nrr_dtype dtype, const AnisoArgs &a, filt::Args *fa, siz
     const size_t limit = device_lds_limit(),
                  fixed = sizeof(ASmall) + sizeof(filt::Small) + NT / 64 * 28 + 64;
     if (limit < fixed || !filt::plan(a.b, a.w, limit - fixed, &fa->z)) return nullptr;
+    if (!filter_pays(a)) return nullptr;
     const Filtered *f = nullptr;
     for (const Filtered &v : kFiltered)
         if (!f && v.bz == a.b[2] && v.nq >= fa->z.nq) f = &v;

@@ -20,7 +20,11 @@ SIZES = [((7, 7, 3), (10, 10, 4)), ((3, 5, 3), (4, 6, 2)), ((9, 9, 3), (5, 4, 1)
          ((5, 5, 5), (3, 3, 3)), ((7, 5, 5), (6, 0, 2)), ((9, 7, 5), (3, 5, 4)),
          ((7, 7, 7), (4, 4, 4)), ((9, 9, 7), (2, 3, 5)), ((9, 9, 9), (6, 5, 4)),
          ((1, 9, 9), (5, 2, 0)), ((9, 1, 3), (0, 0, 0)), ((9, 9, 9), (15, 15, 15)),
-         ((3, 3, 1), (3, 3, 3)), ((11, 5, 3), (3, 3, 2))]
+         ((3, 3, 1), (3, 3, 3)), ((11, 5, 3), (3, 3, 2)),
+         # windows large enough for the filter, for each of its shapes
+         ((5, 5, 3), (8, 7, 4)), ((9, 9, 3), (9, 7, 2)), ((5, 5, 5), (8, 8, 5)),
+         ((7, 7, 5), (9, 8, 4)), ((9, 9, 5), (7, 9, 4)), ((7, 7, 7), (8, 8, 4)),
+         ((9, 7, 7), (6, 8, 3))]
 
 
 def pair(kind, dims, seed):
