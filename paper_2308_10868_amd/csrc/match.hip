@@ -1915,9 +1915,15 @@ struct FiltPlan {
 // fits in LDS, by default: a shape asked for by the caller (a tuner's trial, a
 // pinned shape, an environment override) runs as the FMA form itself.  At
 // edge 3 the FMA form's 27 products per displacement cost less than the
-// bounds.  Record and voxel offsets from the window's corner are 32-bit.
-static bool filt_plan(nrr_dtype dtype, const MatchArgs &a, const TileShape *shape, FiltPlan *out) {
+// bounds, as do small windows' products at the other edges (192x192x96, 4000
+// blocks, FMA form / filter, us: edge 5 W = 5 77 / 90, W = 7 112 / 103; edge 9
+// W = 3 233 / 256, W = 4 422 / 265; edge 7 gains from W = 1, 144 / 106); sets of
+// a batch share their launch, whatever their window.  Record and voxel offsets
+// from the window's corner are 32-bit.
+static bool filt_plan(nrr_dtype dtype, const MatchArgs &a, const TileShape *shape, FiltPlan *out,
+                      bool batched = false) {
     if (dtype != NRR_F32 || shape || (a.block != 5 && a.block != 7 && a.block != 9)) return false;
+    if (!batched && a.window < (a.block == 5 ? 7 : a.block == 9 ? 4 : 0)) return false;
     TileShape sh;
     if (shape_from_env(&sh) || arith_preference() >= 0 || pinned_shape(dtype, a.block, a.window))
         return false;
@@ -1949,7 +1955,7 @@ static bool filt_plan(nrr_dtype dtype, const MatchArgs &a, const TileShape *shap
 bool plan_batch_filter(nrr_dtype dtype, const MatchArgs &a, FiltSizes *z, int32_t *cz,
                        size_t *lds) {
     FiltPlan fp;
-    if (!filt_plan(dtype, a, nullptr, &fp)) return false;
+    if (!filt_plan(dtype, a, nullptr, &fp, true)) return false;
     *z = fp.fa.z;
     *cz = fp.cz;
     *lds = fp.lds;

@@ -94,7 +94,7 @@ def centers_of(dims, b, seed, n=48):
     return np.array(c, dtype=np.int32)
 
 
-@pytest.mark.parametrize("b,w,dims", [(5, 4, (29, 26, 24)), (7, 5, (33, 30, 27)),
+@pytest.mark.parametrize("b,w,dims", [(5, 4, (29, 26, 24)), (5, 8, (31, 29, 26)), (7, 5, (33, 30, 27)),
                                       (9, 6, (37, 34, 31))])
 @pytest.mark.parametrize("kind", KINDS)
 def test_same_bits_as_the_fma_form(kind, b, w, dims):
