@@ -855,12 +855,9 @@ ExDirs ex_dirs(int connectivity) {
 // chip: bit t for pattern neighbour t, bit 31 for a candidate outside the
 // mask.  (In the one-workgroup kernel these reads, a few dependent ones per
 // candidate and 22 candidates per thread, were a third of its time.)
-__global__ __launch_bounds__(256) void k_ex_bits(const uint64_t *__restrict__ keys, int n,
-                                                 BoxGrid G, int nx, int ny,
-                                                 const uint8_t *__restrict__ mask, ExDirs D,
-                                                 uint32_t *__restrict__ above) {
-    const int g = blockIdx.x * 256 + threadIdx.x;
-    if (g >= n) return;
+__device__ inline uint32_t ex_bits(const uint64_t *__restrict__ keys, int g, const BoxGrid &G,
+                                   int nx, int ny, const uint8_t *__restrict__ mask,
+                                   const ExDirs &D) {
     const int gx = G.g[0], gy = G.g[1], gz = G.g[2], gxy = gx * gy;
     const int iz = g / gxy, r = g - iz * gxy, iy = r / gx, ix = r - iy * gx;
     bool in = true;
@@ -876,7 +873,15 @@ __global__ __launch_bounds__(256) void k_ex_bits(const uint64_t *__restrict__ ke
         const int q = real ? (z * gy + y) * gx + x : g;  // itself never ranks above itself
         if (ranks_above(keys[q], q, kg, g)) bits |= 1u << t;
     }
-    above[g] = bits;
+    return bits;
+}
+
+__global__ __launch_bounds__(256) void k_ex_bits(const uint64_t *__restrict__ keys, int n,
+                                                 BoxGrid G, int nx, int ny,
+                                                 const uint8_t *__restrict__ mask, ExDirs D,
+                                                 uint32_t *__restrict__ above) {
+    const int g = blockIdx.x * 256 + threadIdx.x;
+    if (g < n) above[g] = ex_bits(keys, g, G, nx, ny, mask, D);
 }
 
 // The rounds, the count and the selection of a small grid in one 1024-thread
@@ -888,7 +893,9 @@ __global__ __launch_bounds__(256) void k_ex_bits(const uint64_t *__restrict__ ke
 // over the keys in global memory and a serial compaction ran here.
 template <int NK>
 __global__ __launch_bounds__(1024) void k_select_ex(const uint64_t *__restrict__ keys, int n,
-                                                    BoxGrid G, ExDirs D, double fraction,
+                                                    BoxGrid G, int nx, int ny,
+                                                    const uint8_t *__restrict__ mask, ExDirs D,
+                                                    double fraction,
                                                     const uint32_t *__restrict__ above_g,
                                                     int32_t *__restrict__ centers,
                                                     int64_t *__restrict__ k_out) {
@@ -905,7 +912,13 @@ __global__ __launch_bounds__(1024) void k_select_ex(const uint64_t *__restrict__
     if (tid < 3) s_changed[tid] = 0;
     uint32_t a[NK];
 #pragma unroll
-    for (int j = 0; j < NK; ++j) a[j] = j * 1024 + tid < n ? above_g[j * 1024 + tid] : 1u << 31;
+    for (int j = 0; j < NK; ++j) {
+        const int g = j * 1024 + tid;
+        if constexpr (NK * 1024 <= kSmallSelect)
+            a[j] = g < n ? ex_bits(keys, g, G, nx, ny, mask, D) : 1u << 31;
+        else
+            a[j] = g < n ? above_g[g] : 1u << 31;
+    }
     uint32_t open = 0;  // bit j: candidate t + 1024 j is open
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
@@ -965,6 +978,32 @@ __global__ __launch_bounds__(1024) void k_select_ex(const uint64_t *__restrict__
     const int64_t want = k < n_taken ? k : n_taken;
     if (tid == 0) *k_out = want;
     __syncthreads();  // the rounds' masks make room for the select
+    if (NK * 1024 <= kSmallSelect && n <= 256) {
+        // a handful of candidates: ranks by counting (64 candidates: 27 us with
+        // the radix select's passes)
+        uint64_t *kk = reinterpret_cast<uint64_t *>(u.above);
+        const bool mine = tid < n && state[tid] == 1;
+        const uint64_t key = mine ? keys[tid] + 1 : 0;
+        if (tid < n) kk[tid] = key;
+        __syncthreads();
+        int rank = 0;
+        if (mine)
+            for (int i = 0; i < n; ++i) rank += ranks_above(kk[i], i, key, tid);
+        const bool keep = mine && rank < want;
+        const uint64_t kept = __ballot(keep);
+        if (lane == 0) s_count[0][w] = __popcll(kept);
+        __syncthreads();
+        int pos = __popcll(kept & ((1ull << lane) - 1));
+        for (int i = 0; i < w; ++i) pos += s_count[0][i];
+        if (keep) {
+            const int gxy = G.g[0] * G.g[1], iz = tid / gxy, r = tid - iz * gxy, iy = r / G.g[0],
+                      ix = r - iy * G.g[0];
+            centers[3 * pos + 0] = ix * G.s[0] + (G.b[0] - 1) / 2;
+            centers[3 * pos + 1] = iy * G.s[1] + (G.b[1] - 1) / 2;
+            centers[3 * pos + 2] = iz * G.s[2] + (G.b[2] - 1) / 2;
+        }
+        return;
+    }
     select_threshold_of<NK>(
         [&](int64_t i) { return state[i] == 1 ? keys[i] + 1 : (uint64_t)0; }, n, want, nullptr,
         nullptr, G, centers, u.thr);
@@ -1249,11 +1288,14 @@ hipError_t launch_select_ex(const void *vol, nrr_dtype dtype, const int32_t dims
     uint32_t *above = reinterpret_cast<uint32_t *>(ws + L.ex_above_off);
     const ExDirs D = ex_dirs(connectivity);
     launch_keys(vol, dtype, dims, G, n, keys, stream);
-    hipLaunchKernelGGL(k_ex_bits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, keys,
-                       (int)n, G, dims[0], dims[1], mask, D, above);
-    const auto fn = n <= kSmallSelect ? k_select_ex<4> : k_select_ex<kExCand / 1024>;
-    hipLaunchKernelGGL(fn, dim3(1), dim3(1024), 0, stream, keys, (int)n, G, D, fraction, above,
-                       centers, k_device);
+    // the masks of a few thousand candidates cost less than a launch
+    const bool small = n <= kSmallSelect;
+    if (!small)
+        hipLaunchKernelGGL(k_ex_bits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
+                           keys, (int)n, G, dims[0], dims[1], mask, D, above);
+    const auto fn = small ? k_select_ex<kSmallSelect / 1024> : k_select_ex<kExCand / 1024>;
+    hipLaunchKernelGGL(fn, dim3(1), dim3(1024), 0, stream, keys, (int)n, G, dims[0], dims[1], mask,
+                       D, fraction, above, centers, k_device);
     return hipGetLastError();
 }
 
