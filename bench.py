@@ -76,6 +76,7 @@ TRAFFIC_FILES = {
                                          "paper_2308_10868_amd/csrc/nrr_internal.h"]),
     ("mri_aniso_256x256x124_u16", "fma"): ("k_match_aniso_u16_mri_256x256x124_traffic.json",
                                            ["paper_2308_10868_amd/csrc/match_aniso.hip",
+                                            "paper_2308_10868_amd/csrc/mfma_filter.h",
                                             "paper_2308_10868_amd/csrc/nrr_internal.h"]),
 }
 

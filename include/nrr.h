@@ -84,8 +84,8 @@ nrr_status nrr_select_count(const int32_t dims[3], int32_t block, int32_t stride
                             int64_t *k);
 
 /* Device workspace bytes nrr_select_blocks and nrr_select_blocks_ex need
- * for these sizes (the variants on grids of more than 24576 candidates take
- * 5 bytes per candidate more than the plain selection). */
+ * for these sizes (the variants take 4 bytes per candidate more than the plain
+ * selection, 5 on grids of more than 24576 candidates). */
 nrr_status nrr_select_workspace_bytes(const int32_t dims[3], int32_t block, int32_t stride,
                                       size_t *bytes);
 
@@ -380,7 +380,10 @@ nrr_status nrr_clear_tuning(void);
  * and NRR_TILE overrides and tuned shapes taken into account.  arith 2 is
  * the fp16 matrix-core form (12-bit data, block edges 3-9, the window in
  * LDS; the default where it serves): products of exact 12-bit offsets with
- * FP32 sums, 256 threads; its rx, ry are 0 and pf -1.
+ * FP32 sums, 256 threads; its rx, ry are 0 and pf -1.  For float data and for
+ * 12-bit edges above 9 it is the vector form's shape: by default a matrix-core
+ * search with the same results runs before it or in its place, unless a shape
+ * was pinned or an override is set.
  *
  * nrr_match_shapes: the compiled shapes nrr_tune_match times for (dtype,
  * block, window), each with a z-chunk cz; *count receives how many there are
