@@ -32,8 +32,8 @@ struct SelectState {
     int64_t take_eq;  // how many candidates with key == kth are kept (lowest indices)
 };
 
-// One wavefront per candidate block (grids of more than 65535 candidate rows
-// along y or z): lanes take the
+// One wavefront per candidate block (edges above 15 whose tile region does not
+// fit, and grids of more than 65535 candidate rows along y or z): lanes take the
 // block's by*bz rows, sum them exactly in integers and reduce across the
 // wavefront.
 __global__ __launch_bounds__(256) void k_block_keys_u16(const uint16_t *__restrict__ vol, int nx,
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void k_block_keys_u16_rows(const uint16_t *__r
             vol + ((int64_t)iz * G.s[2] * ny + (int64_t)iy * G.s[1]) * nx + x0 + lane;
         for (int z = w; z < bz; z += 4) {
             const uint16_t *p = base + z * plane;
-            uint32_t v[15];  // block edges are at most 15
+            uint32_t v[15];  // the launch sends edges of at most 15
 #pragma unroll
             for (int y = 0; y < 15; ++y) v[y] = y < by ? p[(int64_t)y * nx] : 0u;
 #pragma unroll
@@ -120,8 +120,8 @@ __global__ __launch_bounds__(256) void k_block_keys_u16_rows(const uint16_t *__r
     }
 }
 
-// Tiled keys for many small overlapping candidates (tile regions up to 120
-// voxels a side): a workgroup takes 16 x 16 candidates in x and y at one candidate plane z.
+// Tiled keys for many small overlapping candidates, and for overlapping ones
+// with edges above 15 (tile regions up to 120 voxels a side): a workgroup takes 16 x 16 candidates in x and y at one candidate plane z.
 // For each of the block's bz voxel planes it stages the tile's region
 // ((15 sx + bx) x (15 sy + by) voxels, rows along x, coalesced) in LDS, forms
 // for every region row the sums over each candidate column's bx voxels, and
@@ -1355,7 +1355,9 @@ void launch_keys(const void *vol, nrr_dtype dtype, const int32_t dims[3], const 
     // 991, edge 9 stride 5 166 / 271, edge 9 stride 7 112 / 224)
     const int smin = G.s[0] < G.s[1] ? G.s[0] : G.s[1], bmax = G.b[0] > G.b[1] ? G.b[0] : G.b[1];
     const bool overlap = G.s[0] < G.b[0] || G.s[1] < G.b[1];
-    const bool tiles = overlap && (smin == 1 || (bmax <= 5 && smin <= 3));
+    // Edges above 15 (the selection variants take any) stay off the row kernel,
+    // which holds 15 rows of 64 columns: tiles, or a wavefront per candidate.
+    const bool tiles = overlap && (smin == 1 || (bmax <= 5 && smin <= 3) || bmax > 15);
     const int rx = ((KT - 1) * G.s[0] + G.b[0] + 1) & ~1, ry = (KT - 1) * G.s[1] + G.b[1];
     if (dtype == NRR_U16 && tiles && rx <= KT_MAXR && ry <= KT_MAXR)
         hipLaunchKernelGGL(k_block_keys_u16_tiled,
@@ -1363,7 +1365,7 @@ void launch_keys(const void *vol, nrr_dtype dtype, const int32_t dims[3], const 
                                 (unsigned)G.g[2]),
                            dim3(256), (size_t)rx * ry * 2 + (size_t)ry * KT * 12, stream,
                            static_cast<const uint16_t *>(vol), dims[0], dims[1], G, keys);
-    else if (dtype == NRR_U16 && G.g[1] <= 65535 && G.g[2] <= 65535) {
+    else if (dtype == NRR_U16 && bmax <= 15 && G.g[1] <= 65535 && G.g[2] <= 65535) {
         const int cx = (64 - G.b[0]) / G.s[0] + 1;  // candidates of a row per workgroup
         hipLaunchKernelGGL(k_block_keys_u16_rows,
                            dim3((unsigned)((G.g[0] + cx - 1) / cx), (unsigned)G.g[1],

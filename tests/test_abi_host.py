@@ -321,3 +321,27 @@ def test_select_and_window_stats_validation(lib):
     assert k.value == 146
     assert call(sbytes=16) == 2 and b"selection workspace" in lib.nrr_last_error()
     assert call(mbytes=16) == 2 and b"match workspace" in lib.nrr_last_error()
+
+
+@pytest.mark.parametrize("dims,b,s", [
+    ((100, 100, 100), 67, 3),  # a row of 64 columns holds no candidate of this edge
+    ((100, 100, 100), 65, 1), ((300, 200, 150), 129, 7), ((60, 60, 60), 17, 8),
+])
+def test_select_ex_with_a_large_edge_returns(lib, dims, b, s):
+    """Edges above 15 reach the launch and come back with a status: here, with
+    no device, the HIP error."""
+    import subprocess
+    import sys
+
+    import torch
+
+    if torch.cuda.device_count() > 0:
+        pytest.skip("the made-up pointers may reach no device")
+    code = """
+import ctypes, paper_2308_10868_amd as nrr
+lib, d = nrr.load(), (ctypes.c_int32 * 3)(*%r)
+p = ctypes.c_void_p(4096)
+print(lib.nrr_select_blocks_ex(p, nrr.U16, d, %d, %d, 0.5, None, 0, p, 1 << 40, p, p, 1 << 40, None))
+""" % (dims, b, s)
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.split() == ["3"], (r.returncode, r.stdout, r.stderr)

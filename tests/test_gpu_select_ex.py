@@ -205,3 +205,21 @@ def test_plain_selection_large_grid_with_ties(torch_dev, dtype):
         got = nrr.select_blocks(to_dev(small), 3, 2, f)
         torch.cuda.synchronize()
         assert np.array_equal(to_host(got), want), (dtype, "29,791", f)
+
+
+# Edges above 15, which the variants take (the plain selection does not):
+# overlapping by tiles and by a wavefront per candidate, and apart.
+@pytest.mark.parametrize("dims,b,s", [
+    ((75, 40, 33), 17, 8), ((90, 41, 34), 17, 17), ((90, 41, 34), 17, 19), ((70, 60, 45), 33, 5),
+    ((101, 69, 40), 33, 12), ((140, 70, 66), 33, 33), ((100, 83, 70), 67, 3),
+    ((110, 90, 69), 67, 9), ((140, 69, 68), 67, 71),
+])
+@pytest.mark.parametrize("dtype", ["u16", "f32"])
+def test_edges_above_fifteen(torch_dev, dtype, dims, b, s):
+    p = synth.gen_random(b + s, dims, dtype)
+    rng = np.random.default_rng(b)
+    for mask, conn in [(None, 0), ((rng.random(p.ref.shape) < 0.8).astype(np.uint8), 6)]:
+        say("select_ex edges above 15", dtype, dims, b, s, conn)
+        want, _ = oracle.select_ex(p.ref, b, s, 0.5, mask, conn)
+        got = gpu_ex(p.ref, b, s, 0.5, mask, conn)
+        assert np.array_equal(got, want), (dtype, dims, b, s, conn)
