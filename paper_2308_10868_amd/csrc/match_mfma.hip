@@ -78,6 +78,7 @@
 #include <utility>
 
 #include "nrr_internal.h"
+#include "record_planes.h"
 
 namespace nrr {
 namespace {
@@ -390,10 +391,10 @@ __device__ __attribute__((always_inline)) inline void build_bop(
 //
 // WIDE: volumes whose window spans more than 2 GiB of records; the records
 // are read through 64-bit addresses, clamped into the valid range.  Else
-// through a buffer descriptor of the table from the window's corner on: one
-// 32-bit offset per row, the plane added by the scalar offset, and reads past
-// the table's end (planes that are masked) return 0 by the descriptor's own
-// range check.
+// through a buffer descriptor of the table from the step's plane on
+// (record_planes.h): one 32-bit offset per row, the plane added to the
+// descriptor's base, and reads past the table's end (planes that are masked)
+// return 0 by its range check.
 template <int B, int NW, bool SURF, bool WIDE>
 __device__ __attribute__((always_inline)) inline void sweep_tiles(
     const MfParams &p, const BGeo &g, int64_t blk, const _Float16 *win, const uint32_t *rowtab,
@@ -409,10 +410,6 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
     const int plane_rec = p.oy * p.ox;
     const int64_t corner = ((int64_t)g.wz0 * p.oy + g.wy0) * p.ox + g.wx0;
     const StatU16 *srec = p.stats + corner;
-    const int64_t left = (p.nstat - corner) * (int64_t)sizeof(StatU16);
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<StatU16 *>(srec), 0, (int)(left < 0xffffffffll ? left : 0xffffffffll),
-        0x00020000);
     int kq[NQ];  // this lane's K group of each chunk, from its row's base
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -480,19 +477,24 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
         // registers allow three)
         constexpr int AHEAD = B == 7 ? 3 : B;
         StatU16 rec[B][4];
+        RecordPlanes at;  // of the plane fetched next (planes in order)
+        at.start(p.stats, p.nstat, corner, sizeof(StatU16));
         auto fetch = [&](int tau, StatU16 (&rec)[4]) __attribute__((always_inline)) {
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<unsigned char *>(at.base), 0, (int)at.bytes, 0x00020000);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if constexpr (WIDE) {
                     rec[i] = srec[rcur[i]];
                     rcur[i] += tau < lim3[i] ? plane_rec : 0;
                 } else {
-                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(
-                        rsrc, (int)roff[i], tau * plane_rec * (int)sizeof(StatU16), 0);
+                    const u32x2 v =
+                        __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)roff[i], 0, 0);
                     rec[i].s = (int)v[0];
                     rec[i].r = __uint_as_float(v[1]);
                 }
             }
+            at.next((uint32_t)plane_rec * (uint32_t)sizeof(StatU16));
         };
         // best key of each output row in this tile and its plane (-1: none).
         // Along a row the shift index grows with tau, so a strict comparison

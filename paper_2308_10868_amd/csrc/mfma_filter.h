@@ -40,6 +40,7 @@
 #include <utility>
 
 #include "nrr_internal.h"
+#include "record_planes.h"
 #include "wave64.h"
 
 namespace nrr {
@@ -485,11 +486,6 @@ __device__ __attribute__((always_inline)) inline int search(
         const int oa = n16 & 3, ob = n16 >> 2;
         const int plane_rec = p.oy * p.ox;
         const int64_t corner = ((int64_t)g.oz0 * p.oy + g.oy0) * p.ox + g.ox0;
-        const Rec *srec = static_cast<const Rec *>(p.stats) + corner;
-        const int64_t left = (p.nstat - corner) * (int64_t)sizeof(Rec);
-        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<Rec *>(srec), 0, (int)(left < 0xffffffffll ? left : 0xffffffffll),
-            0x00020000);
         int kq[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
@@ -536,11 +532,15 @@ __device__ __attribute__((always_inline)) inline int search(
             // r of each output row's record, AHEAD planes early: of a double the
             // high word (2^-20 of its value below it)
             uint32_t rec[BZ][4];
-            auto fetch = [&](int tau, uint32_t (&rc)[4]) __attribute__((always_inline)) {
-                const int so = tau * plane_rec * (int)sizeof(Rec);
+            RecordPlanes at_rec;  // of the plane fetched next (planes in order)
+            at_rec.start(p.stats, p.nstat, corner, sizeof(Rec));
+            auto fetch = [&](uint32_t (&rc)[4]) __attribute__((always_inline)) {
+                const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<unsigned char *>(at_rec.base), 0, (int)at_rec.bytes, 0x00020000);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    rc[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)roff[i], so, 0);
+                    rc[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)roff[i], 0, 0);
+                at_rec.next((uint32_t)plane_rec * (uint32_t)sizeof(Rec));
             };
             // largest upper bound of each row, its plane, and the second largest
             float top[4], second[4];
@@ -568,10 +568,10 @@ __device__ __attribute__((always_inline)) inline int search(
                     tp[i] = take ? tau : tp[i];
                     top[i] = take ? up : top[i];
                 }
-                fetch(tau + AHEAD, rec[(S + AHEAD) % BZ]);
+                fetch(rec[(S + AHEAD) % BZ]);
             };
             static_for<AHEAD>(
-                [&](auto k) { fetch(decltype(k)::value, rec[decltype(k)::value]); });
+                [&](auto k) { fetch(rec[decltype(k)::value]); });
             half8 aop[NQ];
             read_a(aop);
             sweep_block<BZ, NQ, 0>(0, acc, bop, aop, load_a, rank);

@@ -1,0 +1,105 @@
+"""The statistics records a matrix-core search loads, on the CPU: whatever
+plane a sweep runs to, the bytes its buffer descriptor lets through lie inside
+the table, and the records of the window's own planes are among them.  The
+descriptor arithmetic (csrc/record_planes.h) is compiled for the host and
+followed through the loads of windows all over a volume, the ones at its last
+planes among them."""
+
+import os
+import subprocess
+
+import pytest
+
+import paper_2308_10868_amd as nrr
+
+CSRC = os.path.join(os.path.dirname(nrr.library_path()), "csrc")
+
+PROGRAM = r"""
+#define NRR_HOST_DEVICE
+#include "record_planes.h"
+#include <algorithm>
+#include <cstdio>
+
+// the per-lane offset's range check, all the descriptor promises
+static bool readable(const nrr::RecordPlanes &r, int64_t off, int size) {
+    return off + size <= (int64_t)r.bytes;
+}
+
+int main(int argc, char **argv) {
+    int b, w, nx, ny, nz, size;
+    sscanf(argv[1], "%d,%d,%d,%d,%d,%d", &b, &w, &nx, &ny, &nz, &size);
+    const unsigned char *table = reinterpret_cast<const unsigned char *>(1ull << 40);
+    const int h = (b - 1) / 2, ox = nx - b + 1, oy = ny - b + 1, oz = nz - b + 1;
+    const int64_t nstat = (int64_t)ox * oy * oz, plane = (int64_t)ox * oy;
+    const unsigned char *end = table + nstat * size;
+    long loads = 0;
+    for (int cz = h; cz < nz - h; ++cz)
+        for (int cy : {h, ny / 2, ny - 1 - h})
+            for (int cx : {h, nx / 2, nx - 1 - h}) {
+                const int x0 = std::max(cx - h - w, 0), y0 = std::max(cy - h - w, 0),
+                          z0 = std::max(cz - h - w, 0);
+                const int dx = std::min(cx - h + w, ox - 1) - x0 + 1,
+                          dy = std::min(cy - h + w, oy - 1) - y0 + 1,
+                          dz = std::min(cz - h + w, oz - 1) - z0 + 1;
+                for (int tz = b; tz < dz + b; tz += b)  // every phase length
+                    for (int oph = 0; oph < dz; oph += tz) {
+                        nrr::RecordPlanes r;
+                        r.start(table, nstat, ((int64_t)z0 * oy + y0) * ox + x0, size);
+                        for (int tau = 0; tau < tz + b; ++tau, r.next((uint32_t)(plane * size)))
+                            for (int y = 0; y < dy; ++y)
+                                for (int x = 0; x < dx; ++x) {
+                                    const int64_t off = (oph * plane + y * ox + x) * size;
+                                    const unsigned char *at = r.base + off;
+                                    const bool in = readable(r, off, size);
+                                    ++loads;
+                                    if (in && (at < table || at + size > end)) {
+                                        printf("past the table: centre %d %d %d tau %d\n", cx, cy, cz, tau);
+                                        return 1;
+                                    }
+                                    const unsigned char *want =
+                                        table + (((z0 + oph + tau) * (int64_t)oy + y0 + y) * ox + x0 + x) * size;
+                                    if (oph + tau < dz && (!in || at != want)) {
+                                        printf("missed: centre %d %d %d tau %d\n", cx, cy, cz, tau);
+                                        return 1;
+                                    }
+                                }
+                    }
+            }
+    printf("%ld\n", loads);
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("records")
+    (d / "t.cpp").write_text(PROGRAM)
+    exe = str(d / "t")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", CSRC, str(d / "t.cpp"), "-o", exe], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("size", [8, 16])
+@pytest.mark.parametrize("b,w,dims", [
+    (7, 1, (16, 15, 14)),   # three valid planes at the most, fetches far past them
+    (3, 0, (9, 8, 7)), (5, 4, (17, 16, 19)), (7, 5, (19, 20, 23)), (9, 3, (17, 19, 12)),
+    (9, 8, (25, 11, 27)), (3, 4, (3, 3, 3)),
+])
+def test_loads_stay_in_the_table(program, b, w, dims, size):
+    arg = ",".join(str(v) for v in (b, w, *dims, size))
+    r = subprocess.run([program, arg], capture_output=True, text=True)
+    assert r.returncode == 0 and int(r.stdout) > 0, r.stdout
+
+
+@pytest.mark.parametrize("source", ["match_mfma.hip", "mfma_filter.h"])
+def test_record_loads_use_the_lane_offset_alone(source):
+    """No buffer load of the searches carries a scalar offset, which a
+    descriptor's range check does not cover."""
+    import re
+
+    text = open(os.path.join(CSRC, source)).read()
+    calls = re.findall(r"raw_buffer_load_b\d+\(\s*([^;]*?)\)\s*;", text, flags=re.S)
+    assert calls
+    for c in calls:
+        assert [a.strip() for a in c.split(",")[-2:]] == ["0", "0"], c
