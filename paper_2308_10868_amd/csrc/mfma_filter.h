@@ -22,7 +22,7 @@
 //   the FP32 search's own chain, at most 729 + 9 roundings: 738 2^-24;
 //   operands below fp16's normal range (2^-14 absolute, whether or not they
 //   are flushed), 2^-28 of Fmax;
-// which sum to 1.20e-3; 1.3e-3 is used.  So key / (N sT sF) lies in (C -+ ea) r
+// which sum to 1.20e-3; 1.3e-3 is used.  So key sT sF / N lies in (C -+ ea) r
 // with C the accumulated sum and ea = EPS sqrt(N) |T^| sT Fmax sF.  A
 // displacement whose upper end lies below the largest lower end cannot win.
 // (|F'| of each displacement would bound it more tightly, from the record's
@@ -72,9 +72,11 @@ __device__ __attribute__((always_inline)) inline void static_for(F &&f) {
     static_for_seq(f, std::make_integer_sequence<int, N>());
 }
 
-// Floats as integers of the same order (never 0 for a finite float).
+// Floats as integers of the same order (never 0 for a finite float).  The zeros
+// are one value, as in a comparison of floats: bounds of a record with r = 0 are
+// zeros of either sign, and their keys tie.
 __device__ inline uint32_t ordered(float f) {
-    const uint32_t b = __float_as_uint(f);
+    const uint32_t b = __float_as_uint(f + 0.0f);
     return b & 0x80000000u ? ~b : b | 0x80000000u;
 }
 __device__ inline float unordered(uint32_t u) {

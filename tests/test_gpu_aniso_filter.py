@@ -71,3 +71,29 @@ def test_same_bits_as_the_fma_form(monkeypatch, kind, b, w):
     want = [to_host(t) for t in nrr.block_match_aniso(r, f, c, b, w)]
     for a, e, name in zip(got, want, ("disp", "ncc", "conf")):
         assert np.array_equal(a.view(np.int32), e.view(np.int32)), (kind, b, w, name)
+
+
+@pytest.mark.parametrize("b,w", [((7, 7, 3), (10, 10, 4)), ((7, 7, 3), (5, 4, 4)),
+                                 ((9, 9, 5), (7, 9, 4))])
+def test_zero_keys_of_either_sign(monkeypatch, b, w):
+    """Float texture far below the common level: every key is a zero."""
+    import torch
+    from tests.test_gpu_f32_filter import level_pair
+
+    for v in ("NRR_ANISO_ARITH", "NRR_ANISO_TILE", "NRR_ANISO_CZ"):
+        monkeypatch.delenv(v, raising=False)
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    dims = tuple(2 * q + e + 6 for e, q in zip(b, w))
+    print("[gpu-case] per-axis filter zero keys", b, w, dims, flush=True)
+    sys.stdout.flush()
+    ref, flt = level_pair(dims, sum(b))
+    rng = np.random.default_rng(4)
+    h = [(e - 1) // 2 for e in b]
+    c = np.array([[int(rng.integers(k, d - k)) for k, d in zip(h, dims)] for _ in range(40)],
+                 dtype=np.int32)
+    r, f, c = to_dev(ref), to_dev(flt), torch.from_numpy(c).cuda()
+    got = [to_host(t) for t in nrr.block_match_aniso(r, f, c, b, w)]
+    monkeypatch.setenv("NRR_ANISO_TILE", "8")
+    want = [to_host(t) for t in nrr.block_match_aniso(r, f, c, b, w)]
+    for a, e, name in zip(got, want, ("disp", "ncc", "conf")):
+        assert np.array_equal(a.view(np.int32), e.view(np.int32)), (b, w, name)

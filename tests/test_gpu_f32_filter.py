@@ -118,3 +118,22 @@ def test_window_sizes(b, w):
     got, want = both(ref, flt, centers_of(dims, b, w, 10), b, w)
     for a, e in zip(got, want):
         assert np.array_equal(a.view(np.int32), e.view(np.int32))
+
+
+def level_pair(dims, seed, level=1e6, std=0.4):
+    """Texture far below the common level: every record is flagged flat (its
+    variance is below 1e-12 of its mean square), so every key is a zero, of
+    either sign, and the lowest shift index wins."""
+    rng = np.random.default_rng(seed)
+    return [(level + std * rng.normal(size=dims[::-1])).astype(np.float32) for _ in range(2)]
+
+
+@pytest.mark.parametrize("b,w", [(7, 1), (7, 2), (7, 3), (7, 6), (9, 4), (5, 7)])
+def test_zero_keys_of_either_sign(b, w):
+    dims = (2 * w + b + 8, 2 * w + b + 7, 2 * w + b + 5)
+    print("[gpu-case] f32 filter zero keys", b, w, dims, flush=True)
+    sys.stdout.flush()
+    ref, flt = level_pair(dims, b + w)
+    got, want = both(ref, flt, centers_of(dims, b, w), b, w)
+    for a, e, name in zip(got, want, ("disp", "ncc", "conf")):
+        assert np.array_equal(a.view(np.int32), e.view(np.int32)), (b, w, name)
