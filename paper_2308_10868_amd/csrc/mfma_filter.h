@@ -28,8 +28,8 @@
 // (|F'| of each displacement would bound it more tightly, from the record's
 // sum; it costs 16-byte records and a third of the sweep's registers.)
 // Blocks whose values do not scale (not finite, or magnitudes outside 2^-60 ..
-// 2^60), flat ones, and those that keep more candidates than the list holds
-// are left to the FP32 search itself.
+// 2^58: above, the FP32 search's sums may overflow), flat ones, and those that
+// keep more candidates than the list holds are left to the FP32 search itself.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -84,11 +84,11 @@ __device__ inline float unordered(uint32_t u) {
 }
 
 // Power of two that brings magnitude `bits` (of a positive float) into
-// [2^14, 2^15); false where the magnitude is outside 2^-60 .. 2^60, zero or
-// not finite.
+// [2^14, 2^15); false where the magnitude is outside 2^-60 .. 2^58, zero or
+// not finite.  (729 products of two magnitudes below 2^58 sum below 2^126.)
 __device__ inline bool scale_of(uint32_t bits, float &scale) {
     const int e = (int)(bits >> 23);
-    if (e < 127 - 60 || e > 127 + 60) return false;
+    if (e < 127 - 60 || e > 127 + 57) return false;
     scale = __uint_as_float((uint32_t)(127 + 14 - (e - 127)) << 23);
     return true;
 }

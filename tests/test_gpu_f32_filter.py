@@ -137,3 +137,20 @@ def test_zero_keys_of_either_sign(b, w):
     got, want = both(ref, flt, centers_of(dims, b, w), b, w)
     for a, e, name in zip(got, want, ("disp", "ncc", "conf")):
         assert np.array_equal(a.view(np.int32), e.view(np.int32)), (b, w, name)
+
+
+@pytest.mark.parametrize("top", [56.0, 57.9, 58.5, 59.9, 60.4])
+@pytest.mark.parametrize("b,w", [(7, 3), (9, 5)])
+def test_sums_past_the_float_range(b, w, top):
+    """Magnitudes whose FP32 cross terms overflow near a match: the FMA form's
+    keys tie at infinity there."""
+    dims = (2 * w + b + 8, 2 * w + b + 7, 2 * w + b + 5)
+    print("[gpu-case] f32 filter large magnitudes", b, w, top, flush=True)
+    sys.stdout.flush()
+    base = synth.gen_random(b + w, dims, "f32", smooth=2.5).ref.astype(np.float64)
+    base = np.tanh(4.0 * (base - base.mean()) / base.std())  # two levels, soft edges
+    base = (base * 2.0 ** top).astype(np.float32)
+    flt = np.ascontiguousarray(np.roll(base, (1, -1, 2), (0, 1, 2)))
+    got, want = both(base, flt, centers_of(dims, b, w), b, w)
+    for a, e, name in zip(got, want, ("disp", "ncc", "conf")):
+        assert np.array_equal(a.view(np.int32), e.view(np.int32)), (b, w, top, name)
