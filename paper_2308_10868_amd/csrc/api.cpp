@@ -231,12 +231,12 @@ nrr_status nrr_select_blocks_ex(const void *vol, nrr_dtype dtype, const int32_t 
         return fail(NRR_ERR_BUFFER_TOO_SMALL, "capacity %lld < %lld", (long long)capacity,
                     (long long)kmax);
     const nrr::SelectLayout L = nrr::select_layout(n, true);
-    if (workspace_bytes < L.total)
+    if (workspace_bytes < L.ex_min)
         return fail(NRR_ERR_BUFFER_TOO_SMALL, "workspace %zu < %zu bytes", workspace_bytes,
-                    L.total);
+                    L.ex_min);
     return hip_status(nrr::launch_select_ex(vol, dtype, dims, block, stride, g, fraction, mask,
                                             connectivity, centers, k_device, workspace,
-                                            static_cast<hipStream_t>(stream)),
+                                            workspace_bytes, static_cast<hipStream_t>(stream)),
                       "nrr_select_blocks_ex launch");
 }
 
@@ -753,11 +753,11 @@ nrr_status nrr_select_blocks_aniso_ex(const void *vol, nrr_dtype dtype, const in
         return fail(NRR_ERR_BUFFER_TOO_SMALL, "capacity %lld < %lld", (long long)capacity,
                     (long long)kmax);
     const nrr::SelectLayout L = nrr::select_layout(n, true);
-    if (workspace_bytes < L.total)
+    if (workspace_bytes < L.ex_min)
         return fail(NRR_ERR_BUFFER_TOO_SMALL, "workspace %zu < %zu bytes", workspace_bytes,
-                    L.total);
+                    L.ex_min);
     return hip_status(nrr::launch_select_ex(vol, dtype, dims, G, fraction, mask, connectivity,
-                                            centers, k_device, workspace,
+                                            centers, k_device, workspace, workspace_bytes,
                                             static_cast<hipStream_t>(stream)),
                       "nrr_select_blocks_aniso_ex launch");
 }

@@ -22,12 +22,13 @@ constexpr int kSelectTile = 2048;  // candidates per compaction workgroup
 struct SelectLayout {
     size_t keys_off, state_off, tiles_off, total;
     size_t radix_rows_off;                          // 0: one-workgroup radix select
-    size_t ex_ctr_off, ex_state_off, ex_above_off;  // selection variants, large grids
+    size_t ex_ctr_off, ex_state_off, ex_above_off;  // selection variants
+    size_t ex_min;                                  // smallest workspace they run in
     int64_t n_tiles;
 };
 // Grids of more candidates take the multi-workgroup radix select.
 constexpr int64_t kRadixMultiMin = 1 << 15;
-// variants: room for the selection variants on large grids as well
+// variants: room for the selection variants as well
 SelectLayout select_layout(int64_t n_candidates, bool variants = false);
 
 // Candidate grid: per-axis block edge b, stride s and candidate count g
@@ -55,11 +56,12 @@ constexpr int64_t kSelectExCand = 24576;
 hipError_t launch_select_ex(const void *vol, nrr_dtype dtype, const int32_t dims[3],
                             int32_t block, int32_t stride, const int32_t grid[3], double fraction,
                             const uint8_t *mask, int32_t connectivity, int32_t *centers,
-                            int64_t *k_device, void *workspace, hipStream_t stream);
+                            int64_t *k_device, void *workspace, size_t workspace_bytes,
+                            hipStream_t stream);
 hipError_t launch_select_ex(const void *vol, nrr_dtype dtype, const int32_t dims[3],
                             const BoxGrid &G, double fraction, const uint8_t *mask,
                             int32_t connectivity, int32_t *centers, int64_t *k_device,
-                            void *workspace, hipStream_t stream);
+                            void *workspace, size_t workspace_bytes, hipStream_t stream);
 hipError_t launch_select_ex_large(const void *vol, nrr_dtype dtype, const int32_t dims[3],
                                   const BoxGrid &G, double fraction, const uint8_t *mask,
                                   int32_t connectivity, int32_t *centers, int64_t *k_device,

@@ -891,7 +891,10 @@ __global__ __launch_bounds__(256) void k_ex_bits(const uint64_t *__restrict__ ke
 // registers (taken: key + 1, any other: 0).  256x256x124, 22,032 candidates,
 // 6-connectivity inside an ellipsoid: 205 us when the set-up, six radix passes
 // over the keys in global memory and a serial compaction ran here.
-template <int NK>
+// HERE: the masks are made here too: of a small grid in registers (cheaper than
+// a launch), of a larger one through LDS, for callers whose workspace has no
+// room for them (the selection above 146 us in all, 90 with the launch).
+template <int NK, bool HERE>
 __global__ __launch_bounds__(1024) void k_select_ex(const uint64_t *__restrict__ keys, int n,
                                                     BoxGrid G, int nx, int ny,
                                                     const uint8_t *__restrict__ mask, ExDirs D,
@@ -910,14 +913,18 @@ __global__ __launch_bounds__(1024) void k_select_ex(const uint64_t *__restrict__
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (tid < D.n) s_off[tid] = (D.dz[tid] * G.g[1] + D.dy[tid]) * G.g[0] + D.dx[tid];
     if (tid < 3) s_changed[tid] = 0;
+    if constexpr (HERE && NK * 1024 > kSmallSelect)  // a thread reads back its own only
+        for (int g = tid; g < n; g += 1024) u.above[g] = ex_bits(keys, g, G, nx, ny, mask, D);
     uint32_t a[NK];
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
         const int g = j * 1024 + tid;
-        if constexpr (NK * 1024 <= kSmallSelect)
+        if constexpr (!HERE)
+            a[j] = g < n ? above_g[g] : 1u << 31;
+        else if constexpr (NK * 1024 <= kSmallSelect)
             a[j] = g < n ? ex_bits(keys, g, G, nx, ny, mask, D) : 1u << 31;
         else
-            a[j] = g < n ? above_g[g] : 1u << 31;
+            a[j] = g < n ? u.above[g] : 1u << 31;
     }
     uint32_t open = 0;  // bit j: candidate t + 1024 j is open
 #pragma unroll
@@ -1269,15 +1276,16 @@ hipError_t launch_select_batch(const void *vol, nrr_dtype dtype, const int32_t d
 hipError_t launch_select_ex(const void *vol, nrr_dtype dtype, const int32_t dims[3],
                             int32_t block, int32_t stride, const int32_t grid[3], double fraction,
                             const uint8_t *mask, int32_t connectivity, int32_t *centers,
-                            int64_t *k_device, void *workspace, hipStream_t stream) {
+                            int64_t *k_device, void *workspace, size_t workspace_bytes,
+                            hipStream_t stream) {
     return launch_select_ex(vol, dtype, dims, cubic_grid(block, stride, grid), fraction, mask,
-                            connectivity, centers, k_device, workspace, stream);
+                            connectivity, centers, k_device, workspace, workspace_bytes, stream);
 }
 
 hipError_t launch_select_ex(const void *vol, nrr_dtype dtype, const int32_t dims[3],
                             const BoxGrid &G, double fraction, const uint8_t *mask,
                             int32_t connectivity, int32_t *centers, int64_t *k_device,
-                            void *workspace, hipStream_t stream) {
+                            void *workspace, size_t workspace_bytes, hipStream_t stream) {
     const int64_t n = (int64_t)G.g[0] * G.g[1] * G.g[2];
     if (n > kSelectExCand)
         return launch_select_ex_large(vol, dtype, dims, G, fraction, mask, connectivity, centers,
@@ -1289,11 +1297,13 @@ hipError_t launch_select_ex(const void *vol, nrr_dtype dtype, const int32_t dims
     const ExDirs D = ex_dirs(connectivity);
     launch_keys(vol, dtype, dims, G, n, keys, stream);
     // the masks of a few thousand candidates cost less than a launch
-    const bool small = n <= kSmallSelect;
-    if (!small)
+    const bool small = n <= kSmallSelect, here = small || workspace_bytes < L.total;
+    if (!here)
         hipLaunchKernelGGL(k_ex_bits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
                            keys, (int)n, G, dims[0], dims[1], mask, D, above);
-    const auto fn = small ? k_select_ex<kSmallSelect / 1024> : k_select_ex<kExCand / 1024>;
+    const auto fn = small  ? k_select_ex<kSmallSelect / 1024, true>
+                    : here ? k_select_ex<kExCand / 1024, true>
+                           : k_select_ex<kExCand / 1024, false>;
     hipLaunchKernelGGL(fn, dim3(1), dim3(1024), 0, stream, keys, (int)n, G, dims[0], dims[1], mask,
                        D, fraction, above, centers, k_device);
     return hipGetLastError();
@@ -1398,9 +1408,13 @@ SelectLayout select_layout(int64_t n_candidates, bool variants) {
     L.ex_ctr_off = L.total;
     L.ex_state_off = L.ex_ctr_off + 256;
     L.ex_above_off = L.ex_state_off + align_up((size_t)n_candidates, 256);
-    // (small grids: the masks alone)
+    // (grids in one workgroup: the masks alone, and none below kSmallSelect; such a
+    // selection runs in the plain size too)
     if (n_candidates <= kSelectExCand) L.ex_above_off = L.ex_ctr_off;
-    if (variants) L.total = L.ex_above_off + align_up((size_t)n_candidates * 4, 256);
+    L.ex_min = L.total;
+    if (variants && n_candidates > kSmallSelect)
+        L.total = L.ex_above_off + align_up((size_t)n_candidates * 4, 256);
+    if (n_candidates > kSelectExCand) L.ex_min = L.total;
     return L;
 }
 

@@ -223,3 +223,48 @@ def test_edges_above_fifteen(torch_dev, dtype, dims, b, s):
         want, _ = oracle.select_ex(p.ref, b, s, 0.5, mask, conn)
         got = gpu_ex(p.ref, b, s, 0.5, mask, conn)
         assert np.array_equal(got, want), (dtype, dims, b, s, conn)
+
+
+# Grids one workgroup serves also run in the plain selection's workspace: the
+# masks of ranked-above neighbours are then made in that workgroup.
+@pytest.mark.parametrize("conn", [0, 6, 26])
+@pytest.mark.parametrize("dims", [(84, 84, 81), (60, 50, 43), (48, 46, 90), (51, 45, 30)])
+@pytest.mark.parametrize("axes", [False, True])
+def test_in_the_plain_workspace(torch_dev, dims, conn, axes):
+    import ctypes
+
+    torch, lib = torch_dev, nrr.load()
+    b, s = (3, 3) if dims[0] == 84 else (3, 2) if dims[0] == 60 else (5, 3)
+    p = synth.gen_random(sum(dims), dims, "u16", smooth=1.0)
+    mask = (np.random.default_rng(2).random(p.ref.shape) < 0.85).astype(np.uint8)
+    n = int(np.prod(nrr.grid_shape(dims, b, s)))
+    assert n <= 24576
+
+    def up(v):
+        return (v + 255) // 256 * 256
+
+    plain = up(8 * n) + 256 + up(16 * ((n + 2047) // 2048))
+    say("select_ex in the plain workspace", dims, b, s, conn, axes, n)
+    ws = torch.full((plain + 4096,), 171, dtype=torch.uint8, device="cuda")
+    c = torch.zeros((n, 3), dtype=torch.int32, device="cuda")
+    k = torch.zeros(1, dtype=torch.int64, device="cuda")
+    vol, m = to_dev(p.ref), to_dev(mask)
+    d3 = (ctypes.c_int32 * 3)(*dims)
+    b3, s3 = (ctypes.c_int32 * 3)(b, b, b), (ctypes.c_int32 * 3)(s, s, s)
+
+    def ptr(t):
+        return ctypes.c_void_p(t.data_ptr())
+
+    if axes:
+        call = lambda size: lib.nrr_select_blocks_aniso_ex(
+            ptr(vol), nrr.U16, d3, b3, s3, 0.6, ptr(m), conn, ptr(c), n, ptr(k), ptr(ws), size,
+            None)
+    else:
+        call = lambda size: lib.nrr_select_blocks_ex(
+            ptr(vol), nrr.U16, d3, b, s, 0.6, ptr(m), conn, ptr(c), n, ptr(k), ptr(ws), size, None)
+    assert call(plain) == 0, lib.nrr_last_error()
+    torch.cuda.synchronize()
+    want, _ = oracle.select_ex(p.ref, b, s, 0.6, mask, conn)
+    assert int(k.item()) == len(want) and np.array_equal(to_host(c)[: len(want)], want)
+    assert bool((ws[plain:] == 171).all())  # nothing written past the size given
+    assert call(plain - 1) == 2  # still refused below it
