@@ -98,9 +98,9 @@ struct Geom {
 
 __device__ inline Geom make_geom(const Params &p, int64_t blk, int h) {
     Geom g;
-    g.cx = p.centers[3 * blk];
-    g.cy = p.centers[3 * blk + 1];
-    g.cz = p.centers[3 * blk + 2];
+    g.cx = __builtin_amdgcn_readfirstlane(p.centers[3 * blk]);  // one block: uniform
+    g.cy = __builtin_amdgcn_readfirstlane(p.centers[3 * blk + 1]);
+    g.cz = __builtin_amdgcn_readfirstlane(p.centers[3 * blk + 2]);
     g.inside = g.cx - h >= 0 && g.cy - h >= 0 && g.cz - h >= 0 && g.cx + h <= p.nx - 1 &&
                g.cy + h <= p.ny - 1 && g.cz + h <= p.nz - 1;
     g.lox = max(-p.w, h - g.cx);
@@ -881,6 +881,8 @@ struct FiltShape {
     static constexpr int KREG = B == 5 ? 20 : B == 7 ? 24 : 40;  // window chunks held per thread
     static constexpr int AHEAD = B == 7 ? 3 : B == 5 ? 5 : 5;    // planes between a record's load and its use
     static constexpr int WAVES = B == 9 ? 1 : 2;   // wavefronts per SIMD the registers allow
+    // candidates above which sweeping broad peaks again costs less than ranking all
+    static constexpr int FEW = B == 5 ? 256 : 128;
 };
 
 template <int B>
@@ -951,8 +953,8 @@ __device__ __attribute__((always_inline)) inline void match_one_filtered(
         fs.tmax[tid >> 6] = tmx;
     }
     wg_sum<NT, double, 1>(sd, sm.redd);  // its barrier publishes the extremes too
-    const double tmean = sd[0] / (double)N;
-    const float c = (float)tmean;
+    const double tmean = uniform(sd[0] / (double)N);
+    const float c = uniform((float)tmean);
     float sT = 0.0f;
     bool scales = filt::block_scale(fs, tmean, sT);
     double ctr[2] = {0.0, 0.0};
@@ -972,25 +974,51 @@ __device__ __attribute__((always_inline)) inline void match_one_filtered(
         return;
     }
     const float *tf = reinterpret_cast<const float *>(lds + fa.z.t_off);
-    const double dN = (double)N, tsum = ctr[0];
+    const double dN = (double)N, tsum = uniform(ctr[0]);
     const int side = 2 * p.w + 1;
     const StatF32 *table = static_cast<const StatF32 *>(p.stats);
-    int ncand = scales ? filt::search<float, B, S::NQ, S::KREG, S::AHEAD>(
-                             fa, fg, lds, fs, w, walk0, at, c, (float)sqrt(ctr[1]), sT)
+    int ncand = scales ? filt::search<float, B, S::NQ, S::KREG, S::AHEAD, true>(
+                             fa, fg, lds, fs, w, walk0, at, c, uniform((float)sqrt(ctr[1])), sT,
+                             S::FEW)
                        : 0;
     const int *cand = filt::candidates(fa, lds);
     int best = cand[0];
-    if (ncand > 1) {
+    constexpr int PER = 64 / B;  // candidates per wavefront step
+    int picked = -1;
+    if (ncand > 2 * filt::NW * PER)  // two turns of the loop below
+        picked = filt::pick_in_box<float, double>(
+            fa, fg, lds, fs, ncand, c,
+            [&](const float *f, int pitch, int plane, const int (&i)[3]) {
+                // the FMA form's key: plane sums, added in order
+                float x = 0.0f;
+#pragma unroll 1  // (a plane's T^ in registers, not the block's)
+                for (int oz = 0; oz < B; ++oz) {
+                    float acc = 0.0f;
+#pragma unroll
+                    for (int oy = 0; oy < B; ++oy)
+#pragma unroll
+                        for (int ox = 0; ox < B; ++ox)
+                            acc = __builtin_fmaf(f[oz * plane + oy * pitch + ox],
+                                                 tf[(oz * B + oy) * B + ox], acc);
+                    x += acc;
+                }
+                const int64_t x0 = g.cx - H + i[0] - p.w, y0 = g.cy - H + i[1] - p.w,
+                              z0 = g.cz - H + i[2] - p.w;
+                return key_f32_of(dN, x, tsum, table[(z0 * p.oy + y0) * p.ox + x0], c);
+            });
+    if (picked >= 0) {
+        best = picked;
+    } else if (ncand > filt::SPREAD) {
+        ncand = 0;
+    } else if (ncand > 1) {
         // the FMA form's key of each candidate: lane oz sums block plane oz, the
         // plane sums are added in order
-        double *keys = reinterpret_cast<double *>(lds + fa.z.l_off + filt::LIST * 8 +
-                                                  filt::CAND * 4);
-        constexpr int PER = 64 / B;  // candidates per wavefront step
+        double *keys = filt::candidate_keys<double>(fa, lds);
         const int lane = tid & 63, sub = lane / B, oz = lane - sub * B;
         for (int k0 = (tid >> 6) * PER; k0 < ncand; k0 += filt::NW * PER) {
             const int k = k0 + sub;
             const bool on = sub < PER && k < ncand;
-            const int id = on ? cand[k] : 0;
+            const int id = on ? cand[-k] : 0;
             const int iz = id / (side * side), ir = id - iz * side * side, iy = ir / side,
                       ix = ir - iy * side;
             const int x0 = g.cx - H + ix - p.w, y0 = g.cy - H + iy - p.w, z0 = g.cz - H + iz - p.w;
@@ -1013,8 +1041,8 @@ __device__ __attribute__((always_inline)) inline void match_one_filtered(
         }
         __syncthreads();
         best = filt::pick(cand, keys, ncand);
-        if (best == INT_MAX) ncand = 0;
     }
+    if (best == INT_MAX) ncand = 0;
     // an opaque copy of the thread index: what follows recomputes its
     // addresses instead of holding them in registers through the sweep
     int t2 = tid;
@@ -1507,7 +1535,7 @@ __global__ __launch_bounds__(256, FiltShape<B>::WAVES) void k_match_batch_filter
         s += __popcll(__ballot(at));
     }
     s = __builtin_amdgcn_readfirstlane(s);
-    const BatchSet &S = sets[s];
+    const BatchSet S = uniform_copy(sets[s]);
     Params p;
     p.ref = S.a.ref;
     p.flt = S.a.flt;
@@ -1915,15 +1943,24 @@ struct FiltPlan {
 // fits in LDS, by default: a shape asked for by the caller (a tuner's trial, a
 // pinned shape, an environment override) runs as the FMA form itself.  At
 // edge 3 the FMA form's 27 products per displacement cost less than the
-// bounds, as do small windows' products at the other edges (192x192x96, 4000
-// blocks, FMA form / filter, us: edge 5 W = 5 77 / 90, W = 7 112 / 103; edge 9
-// W = 3 233 / 256, W = 4 422 / 265; edge 7 gains from W = 1, 144 / 106); sets of
-// a batch share their launch, whatever their window.  Record and voxel offsets
-// from the window's corner are 32-bit.
+// bounds, as do small windows' products at the other edges, unless nearly all
+// blocks are in flight at once (two or one a CU), where the FMA form's latency is
+// the longer one.  The search alone, FMA form / filter in us, on
+// tissue with noise (1,500-15,000 blocks) and on smooth blobs, whose broad
+// peaks cost the filter a second look:
+//   edge 5  W = 7 128 / 145, 133 / 178   W = 8 201 / 172, 202 / 216
+//   edge 7  W = 5 167 / 174, 175 / 233   W = 6 238 / 176, 249 / 244
+//   edge 9  W = 6 203 / 192, 237 / 304   W = 7 247 / 194, 284 / 302
+// and in one round (64^3): edge 7, W = 5, 365 blocks 28.6 / 21.2, 28.6 / 32.5;
+// edge 9, W = 5, 172 blocks 38.7 / 20.5, 38.6 / 37.5.  Sets of a batch share
+// their launch, whatever their window.  Record and voxel offsets from the
+// window's corner are 32-bit.
 static bool filt_plan(nrr_dtype dtype, const MatchArgs &a, const TileShape *shape, FiltPlan *out,
                       bool batched = false) {
     if (dtype != NRR_F32 || shape || (a.block != 5 && a.block != 7 && a.block != 9)) return false;
-    if (!batched && a.window < (a.block == 5 ? 7 : a.block == 9 ? 4 : 0)) return false;
+    const bool few = a.n <= 512;
+    const int least = a.block == 5 ? 8 : a.block == 7 ? (few ? 0 : 6) : (few ? 4 : 7);
+    if (!batched && a.window < least) return false;
     TileShape sh;
     if (shape_from_env(&sh) || arith_preference() >= 0 || pinned_shape(dtype, a.block, a.window))
         return false;

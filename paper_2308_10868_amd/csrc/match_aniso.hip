@@ -85,11 +85,11 @@ struct AGeom {
     bool inside;
 };
 
-__device__ inline AGeom aniso_geom(const AnisoArgs &p, int64_t blk) {
+__device__ inline AGeom aniso_geom_at(const AnisoArgs &p, int cx, int cy, int cz) {
     AGeom g;
     g.bx = p.b[0], g.by = p.b[1], g.bz = p.b[2];
     g.hx = (g.bx - 1) / 2, g.hy = (g.by - 1) / 2, g.hz = (g.bz - 1) / 2;
-    g.cx = p.centers[3 * blk], g.cy = p.centers[3 * blk + 1], g.cz = p.centers[3 * blk + 2];
+    g.cx = cx, g.cy = cy, g.cz = cz;
     g.inside = g.cx - g.hx >= 0 && g.cy - g.hy >= 0 && g.cz - g.hz >= 0 &&
                g.cx + g.hx <= p.nx - 1 && g.cy + g.hy <= p.ny - 1 && g.cz + g.hz <= p.nz - 1;
     // displacements that keep the block inside the volume
@@ -104,6 +104,12 @@ __device__ inline AGeom aniso_geom(const AnisoArgs &p, int64_t blk) {
     g.rbase = (g.cz - g.hz) * g.sz + (int64_t)(g.cy - g.hy) * g.sy + (g.cx - g.hx);
     g.nb = g.bx * g.by * g.bz;
     return g;
+}
+
+__device__ inline AGeom aniso_geom(const AnisoArgs &p, int64_t blk) {  // one block: uniform
+    return aniso_geom_at(p, __builtin_amdgcn_readfirstlane(p.centers[3 * blk]),
+                         __builtin_amdgcn_readfirstlane(p.centers[3 * blk + 1]),
+                         __builtin_amdgcn_readfirstlane(p.centers[3 * blk + 2]));
 }
 
 __device__ inline void write_outside(const AnisoArgs &p, int64_t blk) {
@@ -358,23 +364,23 @@ __global__ __launch_bounds__(NT, BZ * NQ <= 15 ? 3 : BZ * NQ <= 28 ? 2 : 1) void
     const int tid = threadIdx.x;
     const Vox *ref = static_cast<const Vox *>(p.ref);
     const Vox *flt = static_cast<const Vox *>(p.flt);
-    const AGeom g = aniso_geom(p, blk);
-    if (!g.inside) {
+    const AGeom g0 = aniso_geom(p, blk);
+    if (!g0.inside) {
         if (tid == 0) write_outside(p, blk);
         return;
     }
     // the block's voxels (at most 3 per thread), then the window's chunks
     constexpr int TPT = (filt::MAXN + NT - 1) / NT;
     Vox tv[TPT];
-    const int bxy = g.bx * g.by;
-    auto voxel = [&](int o) {
-        const int z = quotient(o, bxy), r = o - z * bxy, y = quotient(r, g.bx);
-        return z * g.sz + (int64_t)y * g.sy + (r - y * g.bx);
+    const int bxy = g0.bx * g0.by;
+    auto voxel0 = [&](int o) {
+        const int z = quotient(o, bxy), r = o - z * bxy, y = quotient(r, g0.bx);
+        return z * g0.sz + (int64_t)y * g0.sy + (r - y * g0.bx);
     };
 #pragma unroll
     for (int k = 0; k < TPT; ++k)
-        if (k * NT < g.nb) tv[k] = ref[g.rbase + voxel(min(tid + k * NT, g.nb - 1))];
-    filt::Geo fg = filt::geometry<Vox>(fa, g.cx, g.cy, g.cz);
+        if (k * NT < g0.nb) tv[k] = ref[g0.rbase + voxel0(min(tid + k * NT, g0.nb - 1))];
+    filt::Geo fg = filt::geometry<Vox>(fa, g0.cx, g0.cy, g0.cz);
     filt::Walk<Vox> walk0;
     walk0.start(fa, fg);
     filt::Walk<Vox> at = walk0;
@@ -393,7 +399,7 @@ __global__ __launch_bounds__(NT, BZ * NQ <= 15 ? 3 : BZ * NQ <= 28 ? 2 : 1) void
     uint32_t tmn = 0xffffffffu, tmx = 0;
 #pragma unroll
     for (int k = 0; k < TPT; ++k)
-        if (tid + k * NT < g.nb) {
+        if (tid + k * NT < g0.nb) {
             st += (double)tv[k];
             tmn = min(tmn, filt::ordered((float)tv[k]));
             tmx = max(tmx, filt::ordered((float)tv[k]));
@@ -404,70 +410,165 @@ __global__ __launch_bounds__(NT, BZ * NQ <= 15 ? 3 : BZ * NQ <= 28 ? 2 : 1) void
         fs.tmin[tid >> 6] = tmn;
         fs.tmax[tid >> 6] = tmx;
     }
-    const double mt = wg_sum(st, sm.red) / g.nb;  // its barrier publishes the extremes too
-    const float cf = (float)mt;
+    const double mt = uniform(wg_sum(st, sm.red) / g0.nb);  // its barrier publishes the extremes too
+    const float cf = uniform((float)mt);
     float sT = 0.0f, sq = 0.0f;
     const bool scales = filt::block_scale(fs, mt, sT);
 #pragma unroll
     for (int k = 0; k < TPT; ++k)
-        if (tid + k * NT < g.nb) {
+        if (tid + k * NT < g0.nb) {
             const float v = (float)((double)tv[k] - mt);
             const int o = tid + k * NT, z = quotient(o, bxy), r = o - z * bxy,
-                      y = quotient(r, g.bx);
-            filt::put_voxel(fa, ldsb, r - y * g.bx, y, z, v, sT);
+                      y = quotient(r, g0.bx);
+            filt::put_voxel(fa, ldsb, r - y * g0.bx, y, z, v, sT);
             sq = fmaf(v, v, sq);
         }
     sq = wave_xor_sum(sq);
     if ((tid & 63) == 63) s_sq[tid >> 6] = sq;
     __syncthreads();  // T^, the sums
     const float *tf = reinterpret_cast<const float *>(ldsb + fa.z.t_off);
-    int ncand = scales ? filt::search<Vox, BZ, NQ, KREG, AHEAD>(
+    int ncand = scales ? filt::search<Vox, BZ, NQ, KREG, AHEAD, false>(
                              fa, fg, ldsb, fs, w, walk0, at, cf,
-                             sqrtf((s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3])), sT)
+                             uniform(sqrtf((s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3]))), sT,
+                             filt::NT)
                        : 0;
+    // the geometry again, and an opaque copy of the thread index: what follows
+    // recomputes its addresses instead of holding them in registers through the
+    // sweep
+    int cx = g0.cx, cy = g0.cy, cz = g0.cz, t2 = tid;
+    asm volatile("" : "+s"(cx), "+s"(cy), "+s"(cz), "+v"(t2));
+    const AGeom g = aniso_geom_at(p, cx, cy, cz);
+    auto voxel = [&](int o) {
+        const int z = quotient(o, g.bx * g.by), r = o - z * g.bx * g.by, y = quotient(r, g.bx);
+        return z * g.sz + (int64_t)y * g.sy + (r - y * g.bx);
+    };
     const int *cand = filt::candidates(fa, ldsb);
     int best = cand[0];
     const int sxn = 2 * p.w[0] + 1, syn = 2 * p.w[1] + 1;
-    if (ncand > 1) {
-        // the candidates' windows as F - mean(T) in the window's place (an odd
-        // pitch: one candidate per lane reads without conflicts), as many as fit
-        Key *keys = reinterpret_cast<Key *>(ldsb + fa.z.l_off + filt::LIST * 8 + filt::CAND * 4);
-        float *fw = reinterpret_cast<float *>(ldsb);
-        const int pitch = g.nb | 1, fit = min(fa.z.t_off / (4 * pitch), NT);
-        for (int k0 = 0; k0 < ncand; k0 += fit) {
-            const int n = min(fit, ncand - k0);
-            for (int e = tid; e < n * g.nb; e += NT) {
-                const int k = quotient(e, g.nb), o = e - k * g.nb, id = cand[k0 + k];
-                const int iz = quotient(id, sxn * syn), ir = id - iz * sxn * syn,
-                          iy = quotient(ir, sxn);
-                const int64_t d = (iz - p.w[2]) * g.sz + (int64_t)(iy - p.w[1]) * g.sy +
-                                  (ir - iy * sxn - p.w[0]);
-                fw[k * pitch + o] = (float)flt[g.rbase + d + voxel(o)] - cf;
+    // records of the displacement (ix, iy, iz)
+    auto record = [&](int ix, int iy, int iz) {
+        return Rec<Vox>::r(p.stats, ((int64_t)(g.cz - g.hz + iz - p.w[2]) * p.oy +
+                                     (g.cy - g.hy + iy - p.w[1])) * p.ox + g.cx - g.hx + ix - p.w[0]);
+    };
+    // The FMA form's key of a displacement by one thread (z, y, x in one chain):
+    // row(z, y, v) reads the row's voxels less the block's mean.  Four rows are in
+    // flight while four are summed.
+    auto chain = [&](int ix, int iy, int iz, auto row) __attribute__((always_inline)) {
+        constexpr int AT = 4;
+        const int rows = g.by * BZ;
+        float v[AT][9];
+        int y = 0, z = 0;
+        auto fetch = [&] {
+#pragma unroll
+            for (int i = 0; i < AT; ++i) {
+                row(z, y, v[i]);
+                const bool end = y + 1 == g.by, last = end && z + 1 == BZ;
+                y = last ? y : end ? 0 : y + 1;
+                z += end && !last;
             }
-            __syncthreads();
-            if (tid < n) {  // the FMA form's chain: z, y, x
-                const float *f = fw + tid * pitch;
-                float acc = 0.0f;
+        };
+        fetch();
+        float acc = 0.0f;
+#pragma unroll 1
+        for (int r = 0; r < rows; r += AT) {
+            float u[AT][9];
+#pragma unroll
+            for (int i = 0; i < AT; ++i)
+#pragma unroll
+                for (int x = 0; x < 9; ++x) u[i][x] = v[i][x];
+            fetch();
+#pragma unroll
+            for (int i = 0; i < AT; ++i)
+#pragma unroll
+                for (int x = 0; x < 9; ++x) {
+                    const bool in = x < g.bx && r + i < rows;
+                    const float t = tf[in ? (r + i) * g.bx + x : 0];
+                    acc = in ? fmaf(t, u[i][x], acc) : acc;
+                }
+        }
+        const Key key = (Key)acc * record(ix, iy, iz);
+        return key != key ? (Key)-INFINITY : key;  // as the FMA form ranks them: last
+    };
+    // candidates whose windows fit in LDS at once
+    const int pitch = g.nb | 1, fit = min(fa.z.t_off / (4 * pitch), NT);
+    int picked = -1;
+    // A displacement costs a thread here what five to eight cost the FMA form: above
+    // an eighth of the window the block is the FMA form's.  Up to four turns of
+    // windows staged one by one, the voxels around a close peak, and beyond both
+    // each thread's own reads (9x9x5, 25x13x9, 97 blocks: 31 us in turns, 39 with
+    // own reads; 9x9x7, 25x9x5, 165 blocks of smooth volumes: 712 us with every
+    // candidate in turns, 59 now).
+    const int most = max(sxn * syn * (2 * p.w[2] + 1) / 8, 128);
+    if (ncand > 4 * fit && ncand <= most)
+        picked = filt::pick_in_box<Vox, Key>(
+            fa, filt::geometry<Vox>(fa, cx, cy, cz), ldsb, fs, ncand, cf,
+            [&](const float *f, int bp, int plane, const int (&i)[3]) {
+                return chain(i[0], i[1], i[2], [&](int z, int y, float (&v)[9]) {
+#pragma unroll
+                    for (int x = 0; x < 9; ++x) v[x] = f[z * plane + y * bp + min(x, g.bx - 1)];
+                });
+            });
+    if (picked >= 0) {
+        best = picked;
+    } else if (ncand > min(filt::SPREAD, most)) {
+        ncand = 0;
+    } else if (ncand > 1) {
+        Key *keys = filt::candidate_keys<Key>(fa, ldsb);
+        if (ncand <= 4 * fit) {
+            // the candidates' windows as F - mean(T) in the window's place (an odd
+            // pitch: one candidate per lane reads without conflicts), as many as fit
+            float *fw = reinterpret_cast<float *>(ldsb);
+            for (int k0 = 0; k0 < ncand; k0 += fit) {
+                const int n = min(fit, ncand - k0);
+                for (int e0 = t2; e0 < n * g.nb; e0 += 4 * NT) {  // four voxels in flight
+                    Vox v[4];
+                    int to[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int e = min(e0 + u * NT, n * g.nb - 1), k = quotient(e, g.nb),
+                                  o = e - k * g.nb, id = cand[-(k0 + k)];
+                        const int iz = quotient(id, sxn * syn), ir = id - iz * sxn * syn,
+                                  iy = quotient(ir, sxn);
+                        const int64_t d = (iz - p.w[2]) * g.sz + (int64_t)(iy - p.w[1]) * g.sy +
+                                          (ir - iy * sxn - p.w[0]);
+                        to[u] = k * pitch + o;
+                        v[u] = flt[g.rbase + d + voxel(o)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) fw[to[u]] = (float)v[u] - cf;
+                }
+                __syncthreads();
+                if (t2 < n) {  // the FMA form's chain: z, y, x
+                    const float *f = fw + t2 * pitch;
+                    float acc = 0.0f;
 #pragma unroll 8
-                for (int o = 0; o < g.nb; ++o) acc = fmaf(tf[o], f[o], acc);
-                const int id = cand[k0 + tid];
+                    for (int o = 0; o < g.nb; ++o) acc = fmaf(tf[o], f[o], acc);
+                    const int id = cand[-(k0 + t2)];
+                    const int iz = quotient(id, sxn * syn), ir = id - iz * sxn * syn,
+                              iy = quotient(ir, sxn), ix = ir - iy * sxn;
+                    Key key = (Key)acc * record(ix, iy, iz);
+                    if (key != key) key = -INFINITY;  // as the FMA form ranks them: last
+                    keys[k0 + t2] = key;
+                }
+                __syncthreads();
+            }
+        } else {  // each thread reads its candidate's rows itself
+            for (int k = t2; k < ncand; k += NT) {
+                const int id = cand[-k];
                 const int iz = quotient(id, sxn * syn), ir = id - iz * sxn * syn,
                           iy = quotient(ir, sxn), ix = ir - iy * sxn;
-                const Key r = Rec<Vox>::r(
-                    p.stats, ((int64_t)(g.cz - g.hz + iz - p.w[2]) * p.oy +
-                              (g.cy - g.hy + iy - p.w[1])) * p.ox + g.cx - g.hx + ix - p.w[0]);
-                Key key = (Key)acc * r;
-                if (key != key) key = -INFINITY;  // as the FMA form ranks them: last
-                keys[k0 + tid] = key;
+                const Vox *f = flt + g.rbase + (iz - p.w[2]) * g.sz +
+                               (int64_t)(iy - p.w[1]) * g.sy + (ix - p.w[0]);
+                keys[k] = chain(ix, iy, iz, [&](int z, int y, float (&v)[9]) {
+#pragma unroll
+                    for (int x = 0; x < 9; ++x)
+                        v[x] = (float)f[z * g.sz + y * g.sy + min(x, g.bx - 1)] - cf;
+                });
             }
-            __syncthreads();
         }
+        __syncthreads();
         best = filt::pick(cand, keys, ncand);
     }
-    // an opaque copy of the thread index: what follows recomputes its addresses
-    // instead of holding them in registers through the sweep
-    int t2 = tid;
-    asm volatile("" : "+v"(t2));
     if (ncand == 0) {  // uniform
         __syncthreads();
         aniso_one<Vox, 8>(p, blk, reinterpret_cast<float *>(ldsb), sm, t2);
@@ -734,11 +835,13 @@ const Filtered kFiltered[] = {FILTERED(3, 2), FILTERED(3, 4), FILTERED(3, 5), FI
 
 // Where the filter pays: it costs a block about the same whatever its window
 // (its phases wait for memory, and its tiles take whole block-deep runs of
-// planes), the FMA form its products per thread.  Measured over 107 random
-// sizes (edges 5-9, z 3 or 5; whole calls, FMA form / filter): all 40 of 3300
-// and more gain, 1.08 to 2.4x (9x9x5, window 11x21x11: 491 / 203 us); below,
-// thin blocks with many planes still do (7x7x3, 11x21x9: 75 / 47), the others
-// go either way, down to 0.7x (7x9x3, 13x9x3: 40 / 54).
+// planes), the FMA form its products per thread.  Whole calls on tissue with
+// noise, FMA form / filter, over 70 random sizes (edges 5-9, z 3 to 9): from 3300
+// products per thread 1.6x on average (9x9x5, 9x21x13: 211 / 56 us; where two
+// rounds of one workgroup a CU meet one of three, 9x9x9, 13x11x7, 440 blocks: 56 /
+// 82); below, thin blocks with many planes still gain (7x5x3, 13x11x13: 85 / 72,
+// at 1344 products 67 / 73), the others go either way.  Volumes as smooth as the
+// window cost the FMA form behind the filter: 0.75x on average there.
 bool filter_pays(const AnisoArgs &a) {
     AnisoPlan pl;
     if (!aniso_plan(a.b, a.w, &pl)) return false;
@@ -747,7 +850,7 @@ bool filter_pays(const AnisoArgs &a) {
     const int64_t rows = (int64_t)a.b[2] * a.b[1] * ((a.b[0] + TU - 1) / TU * TU);
     // (wavefronts of 64 tiles, four of them a workgroup's turn)
     const int64_t per = (tiles + 63) / 64 * rx * rows / 4 * std::min<int64_t>(dz, a.b[2]) / a.b[2];
-    return per >= 3300 || (a.b[2] == 3 && dz >= 9 && per >= 1200);
+    return per >= 3300 || (a.b[2] == 3 && dz >= 9 && per >= 1500);
 }
 
 // The filter serves block edges up to 9 (z: 3 to 9) whose window fits in LDS

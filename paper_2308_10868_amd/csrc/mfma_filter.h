@@ -25,11 +25,22 @@
 // which sum to 1.20e-3; 1.3e-3 is used.  So key sT sF / N lies in (C -+ ea) r
 // with C the accumulated sum and ea = EPS sqrt(N) |T^| sT Fmax sF.  A
 // displacement whose upper end lies below the largest lower end cannot win.
-// (|F'| of each displacement would bound it more tightly, from the record's
-// sum; it costs 16-byte records and a third of the sweep's registers.)
+// (|F'| of each displacement bounds it more tightly, from the record's sum; in
+// the sweep it would cost 16-byte records and a third of the registers, so only
+// listed displacements get it.)
+//
+// Broad peaks.  EPS separates displacements by about 0.003 in NCC: on tissue with
+// noise most blocks keep one, on smooth volumes hundreds lie that close.  Those
+// cost the FP32 chain of each, one displacement per thread, where the FP32 search
+// reads eight from the same registers; so the cubic search sweeps the tiles that
+// still matter a second time against the bound found (fewer whole rows), the
+// voxels around the peak are staged once for all candidates, and the per-axis
+// search leaves the block early.  64^3 blobs with noise of 0.02, 32 sets in one
+// batch: 0.94 ms with all candidates' windows staged one by one, 0.67 now (1.20
+// in the FP32 form).
 // Blocks whose values do not scale (not finite, or magnitudes outside 2^-60 ..
 // 2^58: above, the FP32 search's sums may overflow), flat ones, and those that
-// keep more candidates than the list holds are left to the FP32 search itself.
+// keep more candidates than is worth ranking are left to the FP32 search itself.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -57,8 +68,10 @@ typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));
 constexpr int NT = 256, NW = 4;  // threads and wavefronts of a workgroup
 constexpr int OFF = 3;           // zero rows above a plane of the T tables
 constexpr float EPS = 1.3e-3f;
-constexpr int LIST = 256;   // rows that may hold a winner, pushed while tiles are swept
-constexpr int CAND = 512;   // displacements re-ranked
+constexpr int LIST = 896;   // list of displacements and rows that may win: at least,
+constexpr int LIST_MAX = 4096;  // and at most, where a CU's LDS has room beside its workgroups
+constexpr int SPREAD = 512;  // candidates re-ranked one by one, wherever they lie
+constexpr int TILES = 64;   // 16-row tiles of a window at most
 constexpr int MAXN = 729;   // block voxels served (the bound's terms above)
 
 // f(0) .. f(N - 1) with the index as a compile-time constant.
@@ -136,9 +149,17 @@ inline bool plan(const int32_t b[3], const int32_t w[3], size_t limit, Sizes *s)
     const size_t t_off = ((win > tables ? win : tables) + 15) & ~(size_t)15;
     const size_t tab_off = (t_off + (size_t)b[0] * b[1] * b[2] * 4 + 15) & ~(size_t)15;
     const size_t nrows = (size_t)nbx * nby * ((dz + b[2] - 1) / b[2]);
+    if (nrows > 16 * TILES) return false;
     const size_t l_off = tab_off + (nrows + 15) / 16 * 16 * 4;
-    const size_t lds = l_off + LIST * 8 + CAND * 12 + 16;
-    if (lds > limit) return false;
+    if (l_off + LIST * 8 > limit) return false;
+    // the list takes what is left of the CU's LDS by the workgroups that share it
+    // (at most three: registers)
+    const size_t shared = limit / (l_off + LIST * 8), groups = shared < 3 ? shared : 3;
+    size_t room = (limit / groups - (groups > 1 ? 2048 : 0)) / 8 * 8;
+    room = room < l_off + LIST * 8 ? l_off + LIST * 8 : room;
+    const size_t list = (room - l_off) / 8 < LIST_MAX ? (room - l_off) / 8 : LIST_MAX;
+    const size_t lds = l_off + list * 8;
+    s->list = (int)list;
     s->t_off = (int)t_off;
     s->tab_off = (int)tab_off;
     s->l_off = (int)l_off;
@@ -151,7 +172,11 @@ struct Small {
     uint32_t wmax[NW];  // largest |F'| bits per wavefront
     uint32_t tmin[NW], tmax[NW];  // smallest and largest block voxel (ordered) per wavefront
     uint32_t low;       // largest lower bound (ordered)
-    int nlist, ncand, overflow;
+    uint32_t top[TILES];  // largest upper bound of each tile
+    int nlist, ncand, rows;
+    uint32_t box[6];    // of the candidates: largest x, y, z, and complements of the smallest
+    double key[NW];
+    int idx[NW];
 };
 
 // The block's scale from its extremes and mean; false where it does not scale.
@@ -240,7 +265,8 @@ __device__ __attribute__((always_inline)) inline void open_block(const Args &p, 
         *reinterpret_cast<u32x4 *>(lds + 16 * i) = u32x4{0, 0, 0, 0};
     if (tid == 0) {
         sm.low = 0;
-        sm.nlist = sm.ncand = sm.overflow = 0;
+        sm.nlist = sm.ncand = sm.rows = 0;
+        for (int i = 0; i < 6; ++i) sm.box[i] = 0;
     }
 }
 
@@ -387,9 +413,14 @@ __device__ __attribute__((always_inline)) inline void sweep_block(
     });
 }
 
-// The candidates' shift indices, and behind them their keys.
+// The candidates' shift indices (candidate k at [-k], down from the list's end),
+// and room for SPREAD keys (at its start).
 __device__ inline int *candidates(const Args &p, unsigned char *lds) {
-    return reinterpret_cast<int *>(lds + p.z.l_off + LIST * 8);
+    return reinterpret_cast<int *>(lds + p.z.l_off + 8 * p.z.list) - 1;
+}
+template <typename Key>
+__device__ inline Key *candidate_keys(const Args &p, unsigned char *lds) {
+    return reinterpret_cast<Key *>(lds + p.z.l_off);
 }
 
 template <typename Vox>
@@ -403,16 +434,99 @@ struct Record<uint16_t> {
     using Type = StatU16;
 };
 
+// One tile's sweep: take(i, tau, hi, lo) with the upper and lower end of the
+// key of output row i of the lane in plane tau of the row's phase (valid where tau
+// < lim[i]; lim and ents: the valid planes and table entries of the four rows).
+template <typename Rec, int BZ, int NQ, int AHEAD, typename Take>
+__device__ __attribute__((always_inline)) inline void sweep_tile(
+    const Args &p, const Geo &g, const _Float16 *win, const uint32_t *rowtab,
+    const half8 (&bop)[BZ][NQ], const int (&kq)[NQ], int64_t corner, float ea, int tile, int lane,
+    int (&lim)[4], uint32_t (&ents)[4], Take take) {
+    const int n16 = lane & 15, grp = lane >> 4;
+    const int oa = n16 & 3, ob = n16 >> 2;
+    const int plane_rec = p.oy * p.ox;
+    int abase, alim;
+    {
+        const uint32_t e = rowtab[16 * tile + n16];
+        const int aph = (int)(e >> 16 & 0xff) * g.tz;
+        abase = min(aph, g.ez - 1) * g.pl + (int)(e >> 8 & 0xff) * 2 * p.z.rp2 +
+                (int)(e & 0xff) * 8;
+        alim = g.ez - 1 - aph;
+    }
+    uint32_t roff[4];
+    const uint4 ent = *reinterpret_cast<const uint4 *>(rowtab + 16 * tile + 4 * grp);
+    ents[0] = ent.x, ents[1] = ent.y, ents[2] = ent.z, ents[3] = ent.w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t e = ents[i];
+        const int odx = 4 * (int)(e & 0xff) + oa, ody = 4 * (int)(e >> 8 & 0xff) + ob;
+        const int oph = (int)(e >> 16 & 0xff) * g.tz;
+        roff[i] = (uint32_t)(min(ody, g.dyn - 1) * p.ox + min(odx, g.dxn - 1) +
+                             min(oph, g.dzn - 1) * plane_rec) *
+                      (uint32_t)sizeof(Rec) +
+                  (uint32_t)(sizeof(Rec) - 4);  // r, or its high word
+        lim[i] = (e >> 24) && odx < g.dxn && ody < g.dyn ? g.dzn - oph : -1;
+    }
+    float4v acc[BZ];
+#pragma unroll
+    for (int k = 0; k < BZ; ++k) acc[k] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+    auto read_a = [&](half8 (&aop)[NQ]) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            aop[q] = *reinterpret_cast<const half8 *>(win + abase + kq[q]);
+    };
+    auto load_a = [&](int t, half8 (&aop)[NQ]) {
+        abase += t <= alim ? g.pl : 0;
+        read_a(aop);
+    };
+    // r of each output row's record, AHEAD planes early: of a double the high
+    // word (2^-20 of its value below it)
+    uint32_t rec[BZ][4];
+    RecordPlanes at_rec;  // of the plane fetched next (planes in order)
+    at_rec.start(p.stats, p.nstat, corner, sizeof(Rec));
+    auto fetch = [&](uint32_t (&rc)[4]) __attribute__((always_inline)) {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<unsigned char *>(at_rec.base), 0, (int)at_rec.bytes, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            rc[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)roff[i], 0, 0);
+        at_rec.next((uint32_t)plane_rec * (uint32_t)sizeof(Rec));
+    };
+    auto rank = [&](const float4v &c4, int tau, auto slot) __attribute__((always_inline)) {
+        constexpr int S = decltype(slot)::value;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // (the clamp keeps the ends finite: beyond 2^86 the distance between
+            // them exceeds any key)
+            float r = sizeof(Rec) == 16 ? (float)__hiloint2double((int)rec[S][i], 0)
+                                        : __uint_as_float(rec[S][i]);
+            r = r > 0x1p86f ? 0x1p86f : r;
+            const float hi = (c4[i] + ea) * r, lo = (c4[i] - ea) * r;
+            take(i, tau, hi, lo);
+        }
+        fetch(rec[(S + AHEAD) % BZ]);
+    };
+    static_for<AHEAD>([&](auto k) { fetch(rec[decltype(k)::value]); });
+    half8 aop[NQ];
+    read_a(aop);
+    sweep_block<BZ, NQ, 0>(0, acc, bop, aop, load_a, rank);
+    for (int t0 = BZ; t0 < g.tz; t0 += BZ)
+        sweep_block<BZ, NQ, 1>(t0, acc, bop, aop, load_a, rank);
+    sweep_block<BZ, NQ, 2>(g.tz, acc, bop, aop, load_a, rank);
+}
+
 // Everything after the caller's T^ (put_voxel, after open_block's clears, and
 // published by a barrier): w[] holds the first KREG chunks
 // of `walk0`'s walk, and `at` the walk behind them.  Returns the number of
 // displacements that can win (shift indices in candidates(), with repeats), or
-// 0 where the block is left to the FP32 search.  Uniform; the window in LDS is
+// 0 where the block is left to the FP32 search.  `few`: with AGAIN the candidates
+// above which broad peaks are swept a second time; without, the list's entries
+// above which the block is left.  Uniform; the window in LDS is
 // free for reuse, and the list published, on return.
-template <typename Vox, int BZ, int NQ, int KREG, int AHEAD>
+template <typename Vox, int BZ, int NQ, int KREG, int AHEAD, bool AGAIN>
 __device__ __attribute__((always_inline)) inline int search(
     const Args &p, const Geo &g, unsigned char *lds, Small &sm, u32x4 (&w)[KREG],
-    const Walk<Vox> &walk0, Walk<Vox> at, float c, float tnorm, float sT) {
+    const Walk<Vox> &walk0, Walk<Vox> at, float c, float tnorm, float sT, int few) {
     using Rec = typename Record<Vox>::Type;
     constexpr int C = Chunk<Vox>::C;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -477,179 +591,255 @@ __device__ __attribute__((always_inline)) inline int search(
     }
     __syncthreads();
 
-    // ---- sweep: bounds of every displacement; rows that may hold the winner
-    // go to the list
+    // ---- sweep: bounds of every displacement.  Of each row of displacements
+    // along z the one with the largest upper end goes to the list if it may win,
+    // and the row itself if its second largest may.
     const uint32_t *rowtab = reinterpret_cast<const uint32_t *>(lds + p.z.tab_off);
     u32x2 *list = reinterpret_cast<u32x2 *>(lds + p.z.l_off);
     const int sx = 2 * p.w[0] + 1, sxy = sx * (2 * p.w[1] + 1);
-    const float ea = EPS * sqrtf((float)N) * (tnorm * sT) * (__uint_as_float(fmax) * sF);
-    {
-        const int n16 = lane & 15, grp = lane >> 4;
-        const int oa = n16 & 3, ob = n16 >> 2;
-        const int plane_rec = p.oy * p.ox;
-        const int64_t corner = ((int64_t)g.oz0 * p.oy + g.oy0) * p.ox + g.ox0;
-        int kq[NQ];
+    const float ea = uniform(EPS * sqrtf((float)N) * (tnorm * sT) * (__uint_as_float(fmax) * sF));
+    const int64_t corner = ((int64_t)g.oz0 * p.oy + g.oy0) * p.ox + g.ox0;
+    int kq[NQ];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int gg = 4 * q + grp, gy = quotient(gg, p.z.gx);
-            kq[q] = gy < p.z.gyp ? gy * p.z.rp2 + (gg - gy * p.z.gx) * 8 : 0;
+    for (int q = 0; q < NQ; ++q) {
+        const int gg = 4 * q + (lane >> 4), gy = quotient(gg, p.z.gx);
+        kq[q] = gy < p.z.gyp ? gy * p.z.rp2 + (gg - gy * p.z.gx) * 8 : 0;
+    }
+    int lim[4];
+    uint32_t ents[4];
+    // shift index of plane 0 of the lane's row i
+    auto row_index = [&](int i) {
+        const uint32_t e = ents[i];
+        const int odx = 4 * (int)(e & 0xff) + (lane & 3);
+        const int ody = 4 * (int)(e >> 8 & 0xff) + (lane >> 2 & 3);
+        return (g.loz + (int)(e >> 16 & 0xff) * g.tz + p.w[2]) * sxy + (g.loy + ody + p.w[1]) * sx +
+               (g.lox + odx + p.w[0]);
+    };
+    auto push = [&](uint32_t key, uint32_t what) {
+        const int k = atomicAdd(&sm.nlist, 1);
+        if (k < p.z.list) list[k] = u32x2{key, what};
+    };
+    float low = -INFINITY;
+    for (int tile = wave; tile < g.ntiles; tile += NW) {
+        // largest upper bound of each row, its plane, and the second largest
+        float top[4], second[4];
+        int tp[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            top[i] = second[i] = -INFINITY;
+            tp[i] = 0;
         }
-        float low = -INFINITY;
-        for (int tile = wave; tile < g.ntiles; tile += NW) {
-            int abase, alim;
-            {
-                const uint32_t e = rowtab[16 * tile + n16];
-                const int aph = (int)(e >> 16 & 0xff) * g.tz;
-                abase = min(aph, g.ez - 1) * g.pl + (int)(e >> 8 & 0xff) * 2 * p.z.rp2 +
-                        (int)(e & 0xff) * 8;
-                alim = g.ez - 1 - aph;
-            }
-            int lim[4];
-            uint32_t roff[4];
-            const uint4 ent = *reinterpret_cast<const uint4 *>(rowtab + 16 * tile + 4 * grp);
-            const uint32_t ents[4] = {ent.x, ent.y, ent.z, ent.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t e = ents[i];
-                const int odx = 4 * (int)(e & 0xff) + oa, ody = 4 * (int)(e >> 8 & 0xff) + ob;
-                const int oph = (int)(e >> 16 & 0xff) * g.tz;
-                roff[i] = (uint32_t)(min(ody, g.dyn - 1) * p.ox + min(odx, g.dxn - 1) +
-                                     min(oph, g.dzn - 1) * plane_rec) *
-                              (uint32_t)sizeof(Rec) +
-                          (uint32_t)(sizeof(Rec) - 4);  // r, or its high word
-                lim[i] = (e >> 24) && odx < g.dxn && ody < g.dyn ? g.dzn - oph : -1;
-            }
-            float4v acc[BZ];
-#pragma unroll
-            for (int k = 0; k < BZ; ++k) acc[k] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-            auto read_a = [&](half8 (&aop)[NQ]) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q)
-                    aop[q] = *reinterpret_cast<const half8 *>(win + abase + kq[q]);
-            };
-            auto load_a = [&](int t, half8 (&aop)[NQ]) {
-                abase += t <= alim ? g.pl : 0;
-                read_a(aop);
-            };
-            // r of each output row's record, AHEAD planes early: of a double the
-            // high word (2^-20 of its value below it)
-            uint32_t rec[BZ][4];
-            RecordPlanes at_rec;  // of the plane fetched next (planes in order)
-            at_rec.start(p.stats, p.nstat, corner, sizeof(Rec));
-            auto fetch = [&](uint32_t (&rc)[4]) __attribute__((always_inline)) {
-                const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                    const_cast<unsigned char *>(at_rec.base), 0, (int)at_rec.bytes, 0x00020000);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    rc[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)roff[i], 0, 0);
-                at_rec.next((uint32_t)plane_rec * (uint32_t)sizeof(Rec));
-            };
-            // largest upper bound of each row, its plane, and the second largest
-            float top[4], second[4];
-            int tp[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                top[i] = second[i] = -INFINITY;
-                tp[i] = 0;
-            }
-            auto rank = [&](const float4v &c4, int tau, auto slot) __attribute__((always_inline)) {
-                constexpr int S = decltype(slot)::value;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    // (the clamp keeps the ends finite: beyond 2^86 the distance
-                    // between them exceeds any key)
-                    float r = sizeof(Rec) == 16 ? (float)__hiloint2double((int)rec[S][i], 0)
-                                                : __uint_as_float(rec[S][i]);
-                    r = r > 0x1p86f ? 0x1p86f : r;
-                    const float hi = (c4[i] + ea) * r, lo = (c4[i] - ea) * r;
-                    const bool in = tau < lim[i];
-                    const float up = in ? hi : -INFINITY;
-                    low = in & (lo > low) ? lo : low;
-                    second[i] = __builtin_amdgcn_fmed3f(up, top[i], second[i]);
-                    const bool take = up > top[i];
-                    tp[i] = take ? tau : tp[i];
-                    top[i] = take ? up : top[i];
-                }
-                fetch(rec[(S + AHEAD) % BZ]);
-            };
-            static_for<AHEAD>(
-                [&](auto k) { fetch(rec[decltype(k)::value]); });
-            half8 aop[NQ];
-            read_a(aop);
-            sweep_block<BZ, NQ, 0>(0, acc, bop, aop, load_a, rank);
-            for (int t0 = BZ; t0 < g.tz; t0 += BZ)
-                sweep_block<BZ, NQ, 1>(t0, acc, bop, aop, load_a, rank);
-            sweep_block<BZ, NQ, 2>(g.tz, acc, bop, aop, load_a, rank);
-            // the workgroup's largest lower bound so far, then this tile's rows
-            const uint32_t wl = wave_max(ordered(low));
-            if (lane == 63) atomicMax(&sm.low, wl);
-            // (this wavefront's own maximum is among them: LDS operations of a
-            // wavefront complete in order)
-            const uint32_t all = *(volatile uint32_t *)&sm.low;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (lim[i] > 0 && ordered(top[i]) >= all) {
-                    const uint32_t e = ents[i];
-                    const int odx = 4 * (int)(e & 0xff) + oa, ody = 4 * (int)(e >> 8 & 0xff) + ob;
-                    const int oph = (int)(e >> 16 & 0xff) * g.tz;
-                    const int idx = (g.loz + oph + p.w[2]) * sxy + (g.loy + ody + p.w[1]) * sx +
-                                    (g.lox + odx + p.w[0]);
-                    const bool more = ordered(second[i]) >= all;
-                    const int at0 = atomicAdd(&sm.nlist, more ? 2 : 1);
-                    if (at0 < LIST)
-                        list[at0] = u32x2{ordered(top[i]), (uint32_t)(idx + tp[i] * sxy)};
-                    if (more && at0 + 1 < LIST)  // the row's other planes: all of them
-                        list[at0 + 1] = u32x2{ordered(second[i]),
-                                              (uint32_t)idx | (uint32_t)min(lim[i], g.tz) << 24};
-                }
-            }
+        sweep_tile<Rec, BZ, NQ, AHEAD>(
+            p, g, win, rowtab, bop, kq, corner, ea, tile, lane, lim, ents,
+            [&](int i, int tau, float hi, float lo) __attribute__((always_inline)) {
+                const bool in = tau < lim[i];
+                const float up = in ? hi : -INFINITY;
+                low = in & (lo > low) ? lo : low;
+                second[i] = __builtin_amdgcn_fmed3f(up, top[i], second[i]);
+                const bool take = up > top[i];
+                tp[i] = take ? tau : tp[i];
+                top[i] = take ? up : top[i];
+            });
+        // the workgroup's largest lower bound so far, then this tile's rows
+        const uint32_t wl = wave_max(ordered(low));
+        if (lane == 63) atomicMax(&sm.low, wl);
+        if constexpr (AGAIN) {
+            const uint32_t wt =
+                wave_max(ordered(fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3]))));
+            if (lane == 63) sm.top[tile] = wt;
         }
+        // (this wavefront's own maximum is among them: LDS operations of a
+        // wavefront complete in order)
+        const uint32_t all = *(volatile uint32_t *)&sm.low;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (lim[i] > 0 && ordered(top[i]) >= all) {
+                const int idx = row_index(i);
+                push(ordered(top[i]), (uint32_t)(idx + tp[i] * sxy));
+                if (ordered(second[i]) >= all)
+                    push(ordered(second[i]), (uint32_t)idx | (uint32_t)min(lim[i], g.tz) << 24);
+            }
     }
     __syncthreads();
 
-    // ---- candidates: of the list entries that still reach the largest lower
-    // end, the single displacements get their own bound, with |F'| from their
+    // ---- the listed displacements get their own bound, with |F'| from their
     // record: sqrt(N) |F'| r = sqrt(1 + m^2), m = (sum F - N c) r, and 2^-17 of
     // the window's bound (2^-28 of Fmax for operands below fp16's range).  It is a
     // third to a twentieth of the window's: most blocks keep one displacement.
+    auto own_bounds = [&](int n) {
+        for (int k = tid; k < n; k += NT) {
+            const u32x2 e = list[k];
+            const uint32_t top = e[0];
+            const int idx = (int)e[1];
+            if (e[1] >> 24 || top < *(volatile uint32_t *)&sm.low) continue;
+            const int iz = quotient(idx, sxy), ir = idx - iz * sxy, iy = quotient(ir, sx);
+            const int64_t at_rec = ((int64_t)(g.oz0 + iz - p.w[2] - g.loz) * p.oy +
+                                    (g.oy0 + iy - p.w[1] - g.loy)) * p.ox +
+                                   (g.ox0 + ir - iy * sx - p.w[0] - g.lox);
+            const Rec rec = static_cast<const Rec *>(p.stats)[at_rec];
+            float m;
+            if constexpr (sizeof(Rec) == 16)
+                m = (float)((rec.s - (double)N * (double)c) * rec.r);
+            else  // sums of F - 2048
+                m = ((float)rec.s + (float)N * (2048.0f - c)) * rec.r;
+            const float r = (float)rec.r;
+            const float t = unordered(top) - ea * r;  // C r, to 2^-20 of its size and of ea r
+            const float own = EPS * (tnorm * sT) * sF * rsqrtf((float)N) * (1.0f + fabsf(m)) +
+                              0x1p-17f * (ea * r) + 0x1p-19f * fabsf(t);
+            if (r < 0x1p86f && own < ea * r) {  // (also not taken where a term is not a number)
+                atomicMax(&sm.low, ordered(t - own));
+                list[k][0] = ordered(t + own);
+            }
+        }
+    };
+    // the listed displacements that reach the largest lower end, and the rows with
+    // all their planes, behind the n entries of the list; false where they do not fit
     int *cand = candidates(p, lds);
-    uint32_t all = sm.low;
-    const int nlist = sm.nlist;
-    if (nlist > LIST) return 0;  // uniform
-    const u32x2 e = tid < nlist ? list[tid] : u32x2{0, 0};
-    const int planes = (int)(e[1] >> 24), idx = (int)(e[1] & 0xffffffu);
-    uint32_t top = e[0];
-    if (top >= all && planes == 0) {
-        const int iz = quotient(idx, sxy), ir = idx - iz * sxy, iy = quotient(ir, sx);
-        const int64_t at_rec =
-            ((int64_t)(g.oz0 + iz - p.w[2] - g.loz) * p.oy + (g.oy0 + iy - p.w[1] - g.loy)) * p.ox +
-            (g.ox0 + ir - iy * sx - p.w[0] - g.lox);
-        const Rec rec = static_cast<const Rec *>(p.stats)[at_rec];
-        float m;
-        if constexpr (sizeof(Rec) == 16)
-            m = (float)((rec.s - (double)N * (double)c) * rec.r);
-        else  // sums of F - 2048
-            m = ((float)rec.s + (float)N * (2048.0f - c)) * rec.r;
-        const float r = (float)rec.r;
-        const float t = unordered(top) - ea * r;  // C r, to 2^-20 of its size and of ea r
-        const float own = EPS * (tnorm * sT) * sF * rsqrtf((float)N) * (1.0f + fabsf(m)) +
-                          0x1p-17f * (ea * r) + 0x1p-19f * fabsf(t);
-        if (r < 0x1p86f && own < ea * r) {  // (also not taken where a term is not a number)
-            atomicMax(&sm.low, ordered(t - own));
-            top = ordered(t + own);
+    auto collect = [&](int n) {
+        const uint32_t all = sm.low;
+        const int room = 2 * (p.z.list - n);
+        for (int k = tid; k < n; k += NT) {
+            const u32x2 e = list[k];
+            if (e[0] < all) continue;
+            const int m = max((int)(e[1] >> 24), 1), idx = (int)(e[1] & 0xffffffu);
+            const int at = atomicAdd(&sm.ncand, m);
+            if (m > 1) sm.rows = 1;
+            for (int j = 0; j < m; ++j)
+                if (at + j < room) cand[-(at + j)] = idx + j * sxy;
+        }
+        __syncthreads();
+        return sm.ncand <= room;
+    };
+    int nlist = sm.nlist;
+    if (!AGAIN && nlist > few) return 0;  // uniform
+    own_bounds(min(nlist, p.z.list));
+    __syncthreads();
+    bool fits = collect(min(nlist, p.z.list));
+
+    // ---- broad peaks: where whole rows make more than `few` candidates, or the
+    // list overflowed, the tiles that may hold the winner are swept again against
+    // the bound that stands now, and every displacement that reaches it is listed
+    // and bounded by itself
+    if (!AGAIN) {
+        if (nlist > few) return 0;  // uniform
+    } else if (nlist > p.z.list || !fits || (sm.ncand > few && sm.rows)) {  // uniform
+        const uint32_t all = sm.low;
+        const uint64_t again = __ballot(lane < g.ntiles && sm.top[lane] >= all);
+        const float cut = unordered(all);
+        __syncthreads();
+        if (tid == 0) sm.nlist = sm.ncand = 0;
+        __syncthreads();
+        int turn = 0;
+        for (uint64_t left = again; left; left &= left - 1) {
+            if ((turn++ & (NW - 1)) != wave) continue;
+            const int tile = __ffsll((unsigned long long)left) - 1;
+            sweep_tile<Rec, BZ, NQ, AHEAD>(
+                p, g, win, rowtab, bop, kq, corner, ea, tile, lane, lim, ents,
+                [&](int i, int tau, float hi, float) __attribute__((always_inline)) {
+                    if (tau < lim[i] && hi >= cut)
+                        push(ordered(hi), (uint32_t)(row_index(i) + tau * sxy));
+                });
+        }
+        __syncthreads();
+        nlist = sm.nlist;
+        if (nlist > p.z.list) return 0;  // uniform
+        own_bounds(nlist);
+        __syncthreads();
+        fits = collect(nlist);
+    }
+    return fits ? __builtin_amdgcn_readfirstlane(sm.ncand) : 0;
+}
+
+// The best of candidates that lie close together (a broad peak): the voxels of
+// their common box are staged as F' in the window's place and every thread runs
+// the FP32 search's chain for a candidate of its own.  chain(f, pitch, plane, idx)
+// is the key of the displacement whose block starts at f.  Returns the shift index
+// of the largest key (the smallest among equal ones; INT_MAX where every key is a
+// NaN), or -1 where the box does not fit.  Uniform.
+template <typename Vox, typename Key, typename Chain>
+__device__ __attribute__((always_inline)) inline int pick_in_box(const Args &p, const Geo &g,
+                                                                 unsigned char *lds, Small &sm,
+                                                                 int ncand, float c, Chain chain) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int *cand = candidates(p, lds);
+    const int sx = 2 * p.w[0] + 1, sxy = sx * (2 * p.w[1] + 1);
+    auto split = [&](int idx, int (&i)[3]) {
+        i[2] = quotient(idx, sxy);
+        const int r = idx - i[2] * sxy;
+        i[1] = quotient(r, sx);
+        i[0] = r - i[1] * sx;
+    };
+    uint32_t top[6] = {0, 0, 0, 0, 0, 0};
+    for (int k = tid; k < ncand; k += NT) {
+        int i[3];
+        split(cand[-k], i);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            top[a] = max(top[a], (uint32_t)i[a]);
+            top[3 + a] = max(top[3 + a], 0xffffu - (uint32_t)i[a]);
         }
     }
-    __syncthreads();
-    all = sm.low;
-    if (tid < nlist && top >= all) {
-        const int n = max(planes, 1);
-        const int k = atomicAdd(&sm.ncand, n);
-        for (int j = 0; j < n; ++j)
-            if (k + j < CAND) cand[k + j] = idx + j * sxy;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        top[a] = wave_max(top[a]);
+        if (lane == 63) atomicMax(&sm.box[a], top[a]);
     }
     __syncthreads();
-    const int ncand = __builtin_amdgcn_readfirstlane(sm.ncand);
-    return ncand <= CAND ? ncand : 0;
+    int lo[3], e[3];  // the box: first displacement, voxels per axis
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = (int)(0xffffu - sm.box[3 + a]);
+        e[a] = (int)sm.box[a] - lo[a] + p.b[a];
+    }
+    const int pitch = e[0] | 1, plane = e[1] * pitch, rows = e[1] * e[2];
+    if (plane * e[2] * 4 > p.z.t_off) return -1;  // uniform
+    float *box = reinterpret_cast<float *>(lds);
+    const int64_t sy = p.nx, sz = (int64_t)p.nx * p.ny;
+    const Vox *src = static_cast<const Vox *>(p.flt) + (g.oz0 + lo[2] - p.w[2] - g.loz) * sz +
+                     (g.oy0 + lo[1] - p.w[1] - g.loy) * sy + (g.ox0 + lo[0] - p.w[0] - g.lox);
+    const int n = rows * e[0];
+    for (int i0 = tid; i0 < n; i0 += 4 * NT) {
+        float v[4];
+        int at[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = min(i0 + u * NT, n - 1), r = quotient(i, e[0]), x = i - r * e[0];
+            const int z = quotient(r, e[1]), y = r - z * e[1];
+            at[u] = r * pitch + x;
+            v[u] = (float)src[z * sz + y * sy + x] - c;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) box[at[u]] = v[u];
+    }
+    __syncthreads();
+    Key bk = -INFINITY;
+    int bi = INT_MAX;
+    for (int k = tid; k < ncand; k += NT) {
+        const int idx = cand[-k];
+        int i[3];
+        split(idx, i);
+        const Key key = chain(box + (i[2] - lo[2]) * plane + (i[1] - lo[1]) * pitch + (i[0] - lo[0]),
+                              pitch, plane, i);
+        if (key > bk || (key == bk && idx < bi)) {
+            bk = key;
+            bi = idx;
+        }
+    }
+    wave_best(bk, bi);
+    if (lane == 63) {
+        sm.key[tid >> 6] = (double)bk;
+        sm.idx[tid >> 6] = bi;
+    }
+    __syncthreads();
+    double best = sm.key[0];
+    bi = sm.idx[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w)
+        if (sm.key[w] > best || (sm.key[w] == best && sm.idx[w] < bi)) {
+            best = sm.key[w];
+            bi = sm.idx[w];
+        }
+    return __builtin_amdgcn_readfirstlane(bi);
 }
 
 // The best of the re-ranked candidates (keys in LDS beside them, published):
@@ -660,7 +850,7 @@ __device__ inline int pick(const int *cand, const Key *keys, int ncand) {
     int bi = INT_MAX;
     for (int k = threadIdx.x & 63; k < ncand; k += 64) {
         const Key key = keys[k];
-        const int i = cand[k];
+        const int i = cand[-k];
         if (key > bk || (key == bk && i < bi)) {
             bk = key;
             bi = i;

@@ -180,7 +180,8 @@ struct FiltSizes {
     int gx, gyp, nq;            // x groups, y row pairs, 32-wide K chunks per plane
     int txw, tyw, tcopy;        // T table row width, rows per plane, halves per copy
     int rp2;                    // window pitch of a row pair (halves)
-    int t_off, tab_off, l_off;  // bytes: T^ floats, tile rows, candidates
+    int t_off, tab_off, l_off;  // bytes: T^ floats, tile rows, list
+    int list;                   // entries of the list
     int lds;                    // total bytes
     int tz;                     // phase length of an unclipped window
 };

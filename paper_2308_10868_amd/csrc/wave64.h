@@ -15,6 +15,30 @@ __device__ inline int quotient(int a, int b) {
     return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
 }
 
+// A value that every lane of the wavefront holds, in scalar registers.
+__device__ inline float uniform(float v) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
+}
+__device__ inline double uniform(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u),
+                   hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, hi << 32 | lo);
+}
+
+// A struct in memory that the wavefront shares, in scalar registers.
+template <typename T>
+__device__ inline T uniform_copy(const T &v) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    struct Words {
+        uint32_t w[sizeof(T) / 4];
+    } s = __builtin_bit_cast(Words, v);
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i)
+        s.w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.w[i]);
+    return __builtin_bit_cast(T, s);
+}
+
 template <int CTRL>
 __device__ inline uint32_t dpp_move(uint32_t old, uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, 0xf, 0xf, false);

@@ -97,3 +97,34 @@ def test_zero_keys_of_either_sign(monkeypatch, b, w):
     want = [to_host(t) for t in nrr.block_match_aniso(r, f, c, b, w)]
     for a, e, name in zip(got, want, ("disp", "ncc", "conf")):
         assert np.array_equal(a.view(np.int32), e.view(np.int32)), (b, w, name)
+
+
+@pytest.mark.parametrize("dtype", ["u16", "f32"])
+@pytest.mark.parametrize("noise", [0.0, 0.005, 0.02])
+@pytest.mark.parametrize("b,w", [((7, 7, 3), (10, 10, 4)), ((5, 7, 3), (8, 12, 5)),
+                                 ((5, 7, 5), (12, 4, 6)), ((9, 9, 5), (7, 9, 4)),
+                                 ((7, 9, 7), (7, 9, 4)), ((9, 5, 9), (9, 8, 5))])
+def test_broad_peaks(monkeypatch, b, w, noise, dtype):
+    """Smooth blobs: many displacements within the filter's bound, ranked in
+    turns, around the peak, one by one or by the FMA form."""
+    import torch
+
+    for v in ("NRR_ANISO_ARITH", "NRR_ANISO_TILE", "NRR_ANISO_CZ"):
+        monkeypatch.delenv(v, raising=False)
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    print("[gpu-case] per-axis filter broad peaks", b, w, noise, dtype, flush=True)
+    sys.stdout.flush()
+    p = synth.gen_translation_f32(seed=sum(b) + sum(w), n=48, n_blobs=17, noise=noise)
+    ref, flt = p.ref, p.flt
+    if dtype == "u16":
+        lo, hi = min(ref.min(), flt.min()), max(ref.max(), flt.max())
+        ref, flt = [np.round((v - lo) * (4095 / (hi - lo))).astype(np.uint16) for v in (ref, flt)]
+    rng = np.random.default_rng(5)
+    h = [(e - 1) // 2 for e in b]
+    c = np.array([[int(rng.integers(k, 48 - k)) for k in h] for _ in range(60)], dtype=np.int32)
+    r, f, c = to_dev(ref), to_dev(flt), torch.from_numpy(c).cuda()
+    got = [to_host(t) for t in nrr.block_match_aniso(r, f, c, b, w)]
+    monkeypatch.setenv("NRR_ANISO_TILE", "8")
+    want = [to_host(t) for t in nrr.block_match_aniso(r, f, c, b, w)]
+    for a, e, name in zip(got, want, ("disp", "ncc", "conf")):
+        assert np.array_equal(a.view(np.int32), e.view(np.int32)), (b, w, name)

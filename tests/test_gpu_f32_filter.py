@@ -154,3 +154,16 @@ def test_sums_past_the_float_range(b, w, top):
     got, want = both(base, flt, centers_of(dims, b, w), b, w)
     for a, e, name in zip(got, want, ("disp", "ncc", "conf")):
         assert np.array_equal(a.view(np.int32), e.view(np.int32)), (b, w, top, name)
+
+
+@pytest.mark.parametrize("noise", [0.0, 0.005, 0.02])
+@pytest.mark.parametrize("b,w", [(5, 8), (5, 12), (7, 3), (7, 6), (7, 10), (9, 5), (9, 11)])
+def test_broad_peaks(b, w, noise):
+    """Smooth blobs: hundreds of displacements within the filter's bound, which
+    are swept again, ranked around the peak, one by one or by the FMA form."""
+    print("[gpu-case] f32 filter broad peaks", b, w, noise, flush=True)
+    sys.stdout.flush()
+    p = synth.gen_translation_f32(seed=b + w, n=48, n_blobs=17, noise=noise)
+    got, want = both(p.ref, p.flt, centers_of((48, 48, 48), b, w), b, w)
+    for a, e, name in zip(got, want, ("disp", "ncc", "conf")):
+        assert np.array_equal(a.view(np.int32), e.view(np.int32)), (b, w, name)
