@@ -233,9 +233,10 @@ nrr_status nrr_select_and_window_stats(const void *ref, const void *flt, nrr_dty
                                        size_t match_workspace_bytes, void *stream);
 
 /* nrr_window_stats_for: as nrr_window_stats, for the search that nrr_block_match_prepared will run
- * with this window under the current plan (nrr_match_plan): the plane-pair
- * volume of 12-bit data is written only when that search reads it (the
- * dot2 form).  If the plan changes before the search (tuning, NRR_ARITH),
+ * with this window under the current plan: the plane-pair volume of 12-bit
+ * data is written only when the shape that nrr_match_plan reports reads it (the
+ * dot2 form; for edges 11 to 15 also where the 8-bit matrix cores, which do
+ * not read it, run in that shape's place).  If the plan changes before the search (tuning, NRR_ARITH),
  * the prepared search adds the missing part itself. */
 nrr_status nrr_window_stats_for(const void *flt, nrr_dtype dtype, const int32_t dims[3],
                                 int32_t block, int32_t window, void *workspace,
@@ -347,6 +348,12 @@ nrr_status nrr_structure_confidence(const void *ref, nrr_dtype dtype, const int3
  * every later search in this process with that (dtype, block, window):
  * nrr_block_match, nrr_block_match_prepared and the batched search.
  *
+ * Two searches take no shape: float data behind the matrix-core filter (edges
+ * 5, 7 and 9) and 12-bit edges 11 to 15 on the 8-bit matrix cores, both by
+ * default.  Where one of them serves, the tuner times it too: later plain and
+ * prepared searches run the fastest shape where that is the faster, else stay
+ * with it.  The batched search's float sets stay with the filter either way.
+ *
  *  A shape: arith 0 = dot2 (12-bit data), 1 = FMA, 2 = fp16 matrix cores
  *  (12-bit data, see nrr_match_plan); rx x ry displacements
  *  per thread; nt threads; pf 1 = records prefetched; cz displacement planes
@@ -356,8 +363,8 @@ nrr_status nrr_structure_confidence(const void *ref, nrr_dtype dtype, const int3
  * prepared by nrr_window_stats); the outputs hold the results of the last
  * trial (every shape computes the same results).  reps >= 1 timed launches
  * per shape after one warm-up.  It synchronises `stream`.  best (host,
- * optional) receives the chosen shape, best_us (host, optional) its mean
- * time in microseconds.  Errors as nrr_block_match_prepared, INVALID_ARG for
+ * optional) receives the fastest shape, best_us (host, optional) its mean
+ * time in microseconds (also where a search that takes no shape is faster).  Errors as nrr_block_match_prepared, INVALID_ARG for
  * reps < 1. */
 typedef struct {
     int32_t arith, rx, ry, nt, pf, cz;
@@ -383,21 +390,25 @@ nrr_status nrr_clear_tuning(void);
  * LDS; the default where it serves): products of exact 12-bit offsets with
  * FP32 sums, 256 threads; its rx, ry are 0 and pf -1.  For float data and for
  * 12-bit edges above 9 it is the vector form's shape: by default a matrix-core
- * search with the same results runs before it or in its place, unless a shape
- * was pinned or an override is set.
+ * search that takes no shape, with the same results, runs in its place, unless
+ * a shape was pinned, the tuner found one faster, or an override is set.
  *
  * nrr_match_shapes: the compiled shapes nrr_tune_match times for (dtype,
  * block, window), each with a z-chunk cz; *count receives how many there are
  * (at most cap written to out).
  *
  * nrr_set_tuned_shape: pins `shape` for every later search of (dtype,
- * block, window) in this process, as nrr_tune_match does with the fastest;
+ * block, window) in this process, batched ones included and also where a
+ * search that takes no shape would serve and be faster (so handing the
+ * tuner's `best` back here is not the same as having tuned);
  * cz 0 = as planned, else a cap on the z-chunk.  UNSUPPORTED if the shape is
  * not compiled for that block size (a shape of the batched search is
  * accepted and used there).
  *
  * nrr_batch_shapes: the shape each parameter set of a batched plan over
- * `sets` would run with (out[nsets]); errors as nrr_batch_layout.
+ * `sets` would run with (out[nsets]) in the vector form (float sets of edges
+ * 5, 7 and 9 run behind the filter unless a shape was pinned); errors as
+ * nrr_batch_layout.
  *
  * Errors: as nrr_match_supported, INVALID_ARG for NULL pointers. */
 nrr_status nrr_match_plan(nrr_dtype dtype, const int32_t dims[3], int32_t block, int32_t window,
@@ -417,9 +428,10 @@ nrr_status nrr_set_tuned_shape(nrr_dtype dtype, int32_t block, int32_t window,
  *
  * The batch runs as one selection launch (a workgroup per set; each set's
  * candidate grid must have at most 4096 blocks), the window statistics of
- * each distinct block size, and ONE persistent search launch over the blocks
- * of every set (the sets of largest cost first, the tile shape of each set
- * from the tuned table or the cost model).  With use_graph the launches are
+ * each distinct block size, and the search of the blocks of every set: ONE
+ * persistent launch (the sets of largest cost first, the tile shape of each set
+ * from the tuned table or the cost model), and for float sets with edges 5, 7
+ * and 9 one launch per edge behind the matrix-core filter instead.  With use_graph the launches are
  * captured once into a HIP graph and each run replays it.
  *
  * nrr_batch_layout (host only): offsets[0..nsets] - set s owns output rows

@@ -252,7 +252,8 @@ def match_shapes(dtype: int, block: int, window: int) -> list:
 
 
 def set_tuned_shape(dtype: int, block: int, window: int, shape: dict):
-    """Pin a compiled shape for later searches of (dtype, block, window)."""
+    """Pin a compiled shape for later searches of (dtype, block, window), also
+    where a matrix-core search that takes no shape would serve and be faster."""
     t = TileShape(*[int(shape.get(k, 0)) for k, _ in TileShape._fields_])
     _check(load().nrr_set_tuned_shape(dtype, block, window, ctypes.byref(t)))
 
@@ -598,7 +599,8 @@ def structure_confidence(ref, centers, block: int, conf):
 
 def tune_match(ref, flt, centers, block: int, window: int, workspace=None, reps: int = 3):
     """Time every compiled search shape for (dtype, block, window) on these
-    inputs and keep the fastest for later searches in this process.
+    inputs and keep the fastest for later searches in this process (where a
+    matrix-core search that takes no shape serves and is faster, that one stays).
     Returns (shape dict, mean microseconds).  Synchronises the stream."""
     torch = _torch()
     lib = load()

@@ -926,21 +926,38 @@ nrr_status nrr_tune_match(const void *ref, const void *flt, nrr_dtype dtype,
         hipEventDestroy(e0);
         return hip_status(e, "tuner event");
     }
+    // mean time of a launch as `shape`, or of the default launch
+    auto timed = [&](const nrr::TileShape *shape, double *us) -> hipError_t {
+        hipError_t r = nrr::launch_match(dtype, a, st, shape);  // warm-up
+        if (r == hipSuccess) r = hipEventRecord(e0, st);
+        for (int i = 0; i < reps && r == hipSuccess; ++i) r = nrr::launch_match(dtype, a, st, shape);
+        if (r == hipSuccess) r = hipEventRecord(e1, st);
+        if (r == hipSuccess) r = hipEventSynchronize(e1);
+        float ms = 0.0f;
+        if (r == hipSuccess) r = hipEventElapsedTime(&ms, e0, e1);
+        *us = 1000.0 * ms / reps;
+        return r;
+    };
     double bt = std::numeric_limits<double>::infinity();
     int bi = -1;
     for (int i = 0; i < ns && e == hipSuccess; ++i) {
-        if ((e = nrr::launch_match(dtype, a, st, &shapes[i])) != hipSuccess) break;  // warm-up
-        if ((e = hipEventRecord(e0, st)) != hipSuccess) break;
-        for (int r = 0; r < reps && e == hipSuccess; ++r) e = nrr::launch_match(dtype, a, st, &shapes[i]);
-        if (e != hipSuccess) break;
-        if ((e = hipEventRecord(e1, st)) != hipSuccess) break;
-        if ((e = hipEventSynchronize(e1)) != hipSuccess) break;
-        float ms = 0.0f;
-        if ((e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess) break;
-        const double us = 1000.0 * ms / reps;
-        if (us < bt) {
+        double us = 0.0;
+        e = timed(&shapes[i], &us);
+        if (e == hipSuccess && us < bt) {
             bt = us;
             bi = i;
+        }
+    }
+    if (e == hipSuccess && bi >= 0) {
+        // against the matrix-core search that takes no shape, where one serves: the
+        // shape has to be faster by more than two trials of one launch differ
+        nrr::set_tuned_shape(dtype, block, window, shapes[bi], nrr::ShapeFrom::Tuner);
+        if (nrr::match_takes_no_shape(dtype, a)) {
+            double us = 0.0;
+            e = timed(nullptr, &us);
+            if (e == hipSuccess && bt < 0.97 * us)
+                nrr::set_tuned_shape(dtype, block, window, shapes[bi],
+                                     nrr::ShapeFrom::TunerFastest);
         }
     }
     hipEventDestroy(e0);
@@ -949,7 +966,6 @@ nrr_status nrr_tune_match(const void *ref, const void *flt, nrr_dtype dtype,
     if (bi < 0) return fail(NRR_ERR_UNSUPPORTED, "no compiled shape for block %d window %d", block,
                             window);
     // leave the outputs as the chosen shape computes them
-    nrr::set_tuned_shape(dtype, block, window, shapes[bi], false);
     if ((e = nrr::launch_match(dtype, a, st, &shapes[bi])) != hipSuccess)
         return hip_status(e, "block match launch");
     if (best) {
@@ -1001,7 +1017,7 @@ nrr_status nrr_set_tuned_shape(nrr_dtype dtype, int32_t block, int32_t window,
         return fail(NRR_ERR_UNSUPPORTED,
                     "shape (arith %d, %dx%d, %d threads, pf %d) is not compiled for block %d "
                     "window %d", t.arith, t.rx, t.ry, t.nt, t.pf, block, window);
-    nrr::set_tuned_shape(dtype, block, window, t, true);
+    nrr::set_tuned_shape(dtype, block, window, t, nrr::ShapeFrom::Caller);
     return ok();
 }
 

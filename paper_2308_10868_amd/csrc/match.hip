@@ -1707,7 +1707,7 @@ struct TunedEntry {
     nrr_dtype dtype;
     int b, w;
     TileShape sh;
-    bool pinned;  // set by the caller, not by the tuner
+    ShapeFrom from;
 };
 std::mutex g_tuned_mu;
 std::vector<TunedEntry> g_tuned;
@@ -1874,21 +1874,25 @@ bool tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, TileShape *sh) 
 }
 
 void set_tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, const TileShape &sh,
-                     bool pinned) {
+                     ShapeFrom from) {
     std::lock_guard<std::mutex> lk(g_tuned_mu);
     for (TunedEntry &t : g_tuned)
         if (t.dtype == dtype && t.b == block && t.w == window) {
             t.sh = sh;
-            t.pinned = pinned;
+            t.from = from;
             return;
         }
-    g_tuned.push_back(TunedEntry{dtype, block, window, sh, pinned});
+    g_tuned.push_back(TunedEntry{dtype, block, window, sh, from});
 }
 
-bool pinned_shape(nrr_dtype dtype, int32_t block, int32_t window) {
+// Does the table's shape run in place of the matrix-core searches that take no
+// shape?  A pinned one does; one the tuner timed against them where it was the
+// faster, in the search it timed (a batch shares their launch among its sets).
+static bool shape_replaces(nrr_dtype dtype, int32_t block, int32_t window, bool batched) {
     std::lock_guard<std::mutex> lk(g_tuned_mu);
     for (const TunedEntry &t : g_tuned)
-        if (t.dtype == dtype && t.b == block && t.w == window) return t.pinned;
+        if (t.dtype == dtype && t.b == block && t.w == window)
+            return t.from == ShapeFrom::Caller || (t.from == ShapeFrom::TunerFastest && !batched);
     return false;
 }
 
@@ -1919,7 +1923,8 @@ static kernel_wide_t wide_plan(nrr_dtype dtype, const MatchArgs &a, const TileSh
                                WideSizes *z) {
     if (dtype != NRR_U16 || shape || a.block < 11 || a.block > 15) return nullptr;
     TileShape sh;
-    if (shape_from_env(&sh) || arith_preference() >= 0 || pinned_shape(dtype, a.block, a.window))
+    if (shape_from_env(&sh) || arith_preference() >= 0 ||
+        shape_replaces(dtype, a.block, a.window, false))
         return nullptr;
     const int e = 2 * a.window + a.block;
     if ((int64_t)a.nx * a.ny * e >= (1ll << 31) || (int64_t)e * e * (e / 8 + 2) >= (1 << 20))
@@ -1962,7 +1967,8 @@ static bool filt_plan(nrr_dtype dtype, const MatchArgs &a, const TileShape *shap
     const int least = a.block == 5 ? 8 : a.block == 7 ? (few ? 0 : 6) : (few ? 4 : 7);
     if (!batched && a.window < least) return false;
     TileShape sh;
-    if (shape_from_env(&sh) || arith_preference() >= 0 || pinned_shape(dtype, a.block, a.window))
+    if (shape_from_env(&sh) || arith_preference() >= 0 ||
+        shape_replaces(dtype, a.block, a.window, batched))
         return false;
     const int d = 2 * a.window + 1;
     if ((int64_t)a.nx * a.ny * 16 * (2 * d + 3 * a.block) >= (1ll << 31)) return false;
@@ -2036,6 +2042,12 @@ int match_shapes(nrr_dtype dtype, int32_t block, int32_t window, TileShape *out,
         }
     }
     return n < cap ? n : cap;
+}
+
+bool match_takes_no_shape(nrr_dtype dtype, const MatchArgs &a) {
+    FiltPlan fp;
+    WideSizes z;
+    return filt_plan(dtype, a, nullptr, &fp) || wide_plan(dtype, a, nullptr, &z);
 }
 
 bool match_reads_pairs(nrr_dtype dtype, const MatchArgs &a) {

@@ -222,6 +222,9 @@ hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t stream);
 // The shape launch_match would use now (arith 0 dot2, 1 FMA, 2 MFMA); false
 // when no compiled shape serves.
 bool match_plan(nrr_dtype dtype, const MatchArgs &a, TileShape *out);
+// Would a matrix-core search that takes no shape serve this launch now (float
+// data behind the filter, 12-bit edges 11-15)?
+bool match_takes_no_shape(nrr_dtype dtype, const MatchArgs &a);
 // Does the default search of these sizes read the plane-pair volume?
 bool match_reads_pairs(nrr_dtype dtype, const MatchArgs &a);
 // Whether `sh` (cz ignored) is a compiled plain or batched shape for
@@ -236,11 +239,12 @@ hipError_t launch_match(nrr_dtype dtype, const MatchArgs &a, hipStream_t stream,
 int match_shapes(nrr_dtype dtype, int32_t block, int32_t window, TileShape *out, int cap);
 // Process-wide table of tuned shapes used by every later launch.
 bool tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, TileShape *sh);
-// `pinned`: asked for by the caller (the float search then runs as that shape);
-// a tuner's result serves the vector form only.
+// A shape of the caller's, and one of the tuner's that was the fastest of all,
+// run in place of the matrix-core searches that take no shape; another shape of
+// the tuner's serves the sizes they do not.
+enum class ShapeFrom { Tuner, TunerFastest, Caller };
 void set_tuned_shape(nrr_dtype dtype, int32_t block, int32_t window, const TileShape &sh,
-                     bool pinned);
-bool pinned_shape(nrr_dtype dtype, int32_t block, int32_t window);
+                     ShapeFrom from);
 void clear_tuned_shapes();
 
 // The matrix-core form of the search (12-bit data, block edges 3-9, whole

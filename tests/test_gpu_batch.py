@@ -197,3 +197,24 @@ def test_tuner_keeps_results_and_records_shape(torch_dev, u16_pair):
     check_match(p.ref, p.flt, to_host(c), 7, 6, to_host(d1), to_host(n1), to_host(f1), "tuned")
     nrr.clear_tuning()
     assert nrr.tuned_shape(nrr.U16, 7, 6) is None
+
+
+@pytest.mark.parametrize("dtype,b,w", [(nrr.F32, 7, 8), (nrr.F32, 7, 1), (nrr.F32, 9, 8),
+                                       (nrr.U16, 13, 4)])
+def test_tuner_beside_searches_without_a_shape(torch_dev, dtype, b, w):
+    """The tuner times them too: whichever it keeps, the results are theirs, and
+    a shape pinned before is forgotten."""
+    p = synth.gen_random(b + w, (40, 36, 34), "f32" if dtype == nrr.F32 else "u16", smooth=1.5)
+    ref_d, flt_d = to_dev(p.ref), to_dev(p.flt)
+    nrr.clear_tuning()
+    c = nrr.select_blocks(ref_d, b, b, 0.5)
+    ws = nrr.window_stats(flt_d, b)
+    say("tuner beside the default search", dtype, b, w)
+    want = [to_host(t) for t in nrr.block_match(ref_d, flt_d, c, b, w, workspace=ws, prepared=True)]
+    nrr.set_tuned_shape(dtype, b, w, nrr.match_shapes(dtype, b, w)[0])
+    shape, us = nrr.tune_match(ref_d, flt_d, c, b, w, workspace=ws, reps=2)
+    assert us > 0 and nrr.tuned_shape(dtype, b, w) == shape
+    got = [to_host(t) for t in nrr.block_match(ref_d, flt_d, c, b, w, workspace=ws, prepared=True)]
+    nrr.clear_tuning()
+    same_or_tied(got[0], got[1], want[0], want[1])
+    check_match(p.ref, p.flt, to_host(c), b, w, got[0], got[1], got[2], "tuned")
