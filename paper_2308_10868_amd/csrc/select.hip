@@ -985,6 +985,55 @@ __global__ __launch_bounds__(1024) void k_select_ex(const uint64_t *__restrict__
     const int64_t want = k < n_taken ? k : n_taken;
     if (tid == 0) *k_out = want;
     __syncthreads();  // the rounds' masks make room for the select
+    auto put = [&](int g, int pos) {
+        const int gxy = G.g[0] * G.g[1], iz = g / gxy, r = g - iz * gxy, iy = r / G.g[0],
+                  ix = r - iy * G.g[0];
+        centers[3 * pos + 0] = ix * G.s[0] + (G.b[0] - 1) / 2;
+        centers[3 * pos + 1] = iy * G.s[1] + (G.b[1] - 1) / 2;
+        centers[3 * pos + 2] = iz * G.s[2] + (G.b[2] - 1) / 2;
+    };
+    if (want == n_taken) {  // uniform
+        // a pattern often takes fewer than the fraction asks for: all of them, in
+        // grid order, without ranking (187x127x126, edge 15, 616 candidates, 18
+        // neighbours: 66.4 us a call with the select, 61.0 without)
+        uint32_t *before = u.above;  // candidates taken before each wavefront's turn
+#pragma unroll
+        for (int j = 0; j < NK; ++j) {
+            const int c = __popcll(__ballot(taken >> j & 1));
+            if (lane == 0) before[j * 16 + w] = c;
+        }
+        __syncthreads();
+        if (w == 0) {
+            constexpr int PER = (NK * 16 + 63) / 64;
+            uint32_t c[PER], sum = 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                c[i] = lane * PER + i < NK * 16 ? before[lane * PER + i] : 0;
+                sum += c[i];
+            }
+            uint32_t incl = sum;
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t v = __shfl_up(incl, off);
+                incl += lane >= off ? v : 0;
+            }
+            uint32_t at = incl - sum;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                if (lane * PER + i < NK * 16) before[lane * PER + i] = at;
+                at += c[i];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NK; ++j) {
+            const bool mine = taken >> j & 1;
+            const uint64_t all = __ballot(mine);
+            if (mine)
+                put(j * 1024 + tid,
+                    (int)before[j * 16 + w] + __popcll(all & ((1ull << lane) - 1)));
+        }
+        return;
+    }
     if (NK * 1024 <= kSmallSelect && n <= 256) {
         // a handful of candidates: ranks by counting (64 candidates: 27 us with
         // the radix select's passes)
@@ -1002,13 +1051,7 @@ __global__ __launch_bounds__(1024) void k_select_ex(const uint64_t *__restrict__
         __syncthreads();
         int pos = __popcll(kept & ((1ull << lane) - 1));
         for (int i = 0; i < w; ++i) pos += s_count[0][i];
-        if (keep) {
-            const int gxy = G.g[0] * G.g[1], iz = tid / gxy, r = tid - iz * gxy, iy = r / G.g[0],
-                      ix = r - iy * G.g[0];
-            centers[3 * pos + 0] = ix * G.s[0] + (G.b[0] - 1) / 2;
-            centers[3 * pos + 1] = iy * G.s[1] + (G.b[1] - 1) / 2;
-            centers[3 * pos + 2] = iz * G.s[2] + (G.b[2] - 1) / 2;
-        }
+        if (keep) put(tid, pos);
         return;
     }
     select_threshold_of<NK>(

@@ -268,3 +268,23 @@ def test_in_the_plain_workspace(torch_dev, dims, conn, axes):
     assert int(k.item()) == len(want) and np.array_equal(to_host(c)[: len(want)], want)
     assert bool((ws[plain:] == 171).all())  # nothing written past the size given
     assert call(plain - 1) == 2  # still refused below it
+
+
+@pytest.mark.parametrize("dims,b,s", [((3, 3, 3), 3, 3), ((18, 18, 21), 3, 3),      # 1, 252
+                                      ((33, 33, 27), 3, 3), ((48, 48, 48), 3, 3),   # 1089, 4096
+                                      ((51, 51, 45), 3, 3), ((84, 84, 81), 3, 3)])  # 4335, 21168
+@pytest.mark.parametrize("conn", [0, 6, 26])
+def test_everything_taken_and_one_less(torch_dev, dims, b, s, conn):
+    """The count reaches what the pattern takes, passes it, and stays one below."""
+    p = synth.gen_random(sum(dims) + conn, dims, "u16", smooth=0.7)
+    rng = np.random.default_rng(conn)
+    mask = (rng.random(p.ref.shape) < 0.9).astype(np.uint8)
+    full, _ = oracle.select_ex(p.ref, b, s, 1.0, mask, conn)
+    h = b // 2
+    n_in = int(mask[h::s, h::s, h::s][:dims[2] // s, :dims[1] // s, :dims[0] // s].sum())
+    for k in {len(full) - 1, len(full), n_in} - {0, -1}:  # (a fraction is above 0)
+        f = k / n_in
+        say("select_ex all taken", dims, conn, k, n_in)
+        want, _ = oracle.select_ex(p.ref, b, s, f, mask, conn)
+        got = gpu_ex(p.ref, b, s, f, mask, conn)
+        assert np.array_equal(got, want), (dims, conn, k)
