@@ -96,11 +96,17 @@ struct Geom {
     bool inside;
 };
 
+// UNIFORM: in scalar registers (the filtered search, short of vector ones).
+template <bool UNIFORM = false>
 __device__ inline Geom make_geom(const Params &p, int64_t blk, int h) {
+    auto coord = [&](int i) {
+        const int v = p.centers[3 * blk + i];
+        return UNIFORM ? __builtin_amdgcn_readfirstlane(v) : v;
+    };
     Geom g;
-    g.cx = __builtin_amdgcn_readfirstlane(p.centers[3 * blk]);  // one block: uniform
-    g.cy = __builtin_amdgcn_readfirstlane(p.centers[3 * blk + 1]);
-    g.cz = __builtin_amdgcn_readfirstlane(p.centers[3 * blk + 2]);
+    g.cx = coord(0);
+    g.cy = coord(1);
+    g.cz = coord(2);
     g.inside = g.cx - h >= 0 && g.cy - h >= 0 && g.cz - h >= 0 && g.cx + h <= p.nx - 1 &&
                g.cy + h <= p.ny - 1 && g.cz + h <= p.nz - 1;
     g.lox = max(-p.w, h - g.cx);
@@ -893,7 +899,7 @@ __device__ __attribute__((always_inline)) inline void match_one_filtered(
     constexpr int H = (B - 1) / 2, N = B * B * B, BP = (B + 3) & ~3, NT = 256;
     constexpr int TP_WORDS = B * B * BP;
     constexpr int TPT = (N + NT - 1) / NT, TPI = (TP_WORDS + NT - 1) / NT;
-    const Geom g = make_geom(p, blk, H);
+    const Geom g = make_geom<true>(p, blk, H);
     const int tid = threadIdx.x;
     if (!g.inside) {
         if (tid == 0) write_result(p, blk, 0, 0, 0, NAN);
