@@ -447,7 +447,7 @@ def main() -> int:
 def bench_batched(args) -> int:
     """32 parameter sets (block, window, fraction; stride = block) over the
     64^3 float pair: one step = one batch (window statistics per block size,
-    one selection launch, one persistent search launch) replayed from a HIP
+    one selection launch, one search launch per block edge) replayed from a HIP
     graph, against the same 32 sets as 32 sequential plain calls
     (select_blocks + block_match each)."""
     import torch
