@@ -1371,9 +1371,9 @@ __global__ __launch_bounds__(256, WideShape<B>::WAVES) void k_match_wide(Params 
         int at = abase + min(tau0, alim) * plane;
         read(at, std::integral_constant<int, 0>(), ah, al);
         for (int u0 = 0; u0 < tz + TW - 1; u0 += TW) {
-            filt::static_for<TW>([&](auto uc) __attribute__((always_inline)) {
+            static_for<TW>([&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
-                filt::static_for<NS>([&](auto sc) __attribute__((always_inline)) {
+                static_for<NS>([&](auto sc) __attribute__((always_inline)) {
                     constexpr int s = decltype(sc)::value;
                     int4v nh, nl;
                     if constexpr (s == NS - 1) at = abase + min(tau0 + u0 + u + 1, alim) * plane;

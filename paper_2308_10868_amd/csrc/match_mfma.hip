@@ -79,6 +79,7 @@
 
 #include "nrr_internal.h"
 #include "record_planes.h"
+#include "wave64.h"
 
 namespace nrr {
 namespace {
@@ -151,40 +152,17 @@ __device__ inline void put(const MfParams &p, int64_t blk, int dx, int dy, int d
     p.conf[blk] = v > 0.0f ? v : 0.0f;
 }
 
-// Wavefront reductions by data-parallel-primitive moves (row shifts, then
-// row broadcasts): lane 63 ends with the result of all 64 lanes.  A step
-// costs a few cycles; a shuffle goes through LDS and waits ~100.
-template <int CTRL>
-__device__ inline int dpp(int old, int v) {
-    return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xf, 0xf, false);
-}
-template <typename F>
-__device__ inline void dpp_steps(F &&f) {
-    f(std::integral_constant<int, 0x111>());  // row_shr:1
-    f(std::integral_constant<int, 0x112>());
-    f(std::integral_constant<int, 0x114>());
-    f(std::integral_constant<int, 0x118>());
-    f(std::integral_constant<int, 0x142>());  // row_bcast:15
-    f(std::integral_constant<int, 0x143>());  // row_bcast:31
-}
+// Of the wavefront (valid in lane 63).
 __device__ inline int wave_sum(int v) {  // 32-bit sums, wrapping
-    dpp_steps([&](auto c) { v += dpp<decltype(c)::value>(0, v); });
+    dpp_steps([&](auto move) { v += (int)move(0u, (uint32_t)v); });
     return v;
 }
 __device__ inline u16x2 wave_min(u16x2 v) {
-    dpp_steps([&](auto c) {
-        const int o = dpp<decltype(c)::value>(-1, __builtin_bit_cast(int, v));
+    dpp_steps([&](auto move) {
+        const uint32_t o = move(0xffffffffu, __builtin_bit_cast(uint32_t, v));
         v = __builtin_elementwise_min(v, __builtin_bit_cast(u16x2, o));
     });
     return v;
-}
-__device__ inline void wave_best(float &bk, int &bi) {
-    dpp_steps([&](auto c) {
-        constexpr int C = decltype(c)::value;
-        const float ok = __int_as_float(dpp<C>(__float_as_int(bk), __float_as_int(bk)));
-        const int oi = dpp<C>(bi, bi);
-        keep_best(bk, bi, ok, oi);
-    });
 }
 
 constexpr int MAX_NW = 4;  // wavefronts per workgroup
@@ -283,12 +261,6 @@ __device__ inline void block_tiles(const MfParams &p, BGeo &g) {
     g.ntiles = (g.nrows + 15) / 16;
 }
 
-// a / b for 0 <= a < 65536, b > 0: (a + 1/2) / b is at least 1 / (2 b) away
-// from the next integer, beyond the rounding of the reciprocal.
-__device__ inline int quotient(int a, int b) {
-    return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
-}
-
 // Tile rows as packed table entries: x base index, y base index, phase, and
 // whether the row exists (rows past the last repeat row 0, masked).
 __device__ inline uint32_t row_entry(const BGeo &g, int r) {
@@ -308,17 +280,6 @@ __device__ inline u32x4 shift_chunk(u32x4 v, int sh) {
     for (int j = 0; j < 4; ++j) v[j] = sh & 1 ? h[j] : v[j];
     v = sh & 2 ? u32x4{v[1], v[2], v[3], v[3]} : v;
     return sh & 4 ? u32x4{v[2], v[3], v[3], v[3]} : v;
-}
-
-// f(0) .. f(N - 1) with the index as a compile-time constant.
-template <typename F, int... I>
-__device__ __attribute__((always_inline)) inline void static_for_seq(
-    F &&f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>()), ...);
-}
-template <int N, typename F>
-__device__ __attribute__((always_inline)) inline void static_for(F &&f) {
-    static_for_seq(f, std::make_integer_sequence<int, N>());
 }
 
 // One unrolled block of B sweep steps t0 .. t0 + B - 1 (t0 a multiple of B):

@@ -74,17 +74,6 @@ constexpr int SPREAD = 512;  // candidates re-ranked one by one, wherever they l
 constexpr int TILES = 64;   // 16-row tiles of a window at most
 constexpr int MAXN = 729;   // block voxels served (the bound's terms above)
 
-// f(0) .. f(N - 1) with the index as a compile-time constant.
-template <typename F, int... I>
-__device__ __attribute__((always_inline)) inline void static_for_seq(
-    F &&f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>()), ...);
-}
-template <int N, typename F>
-__device__ __attribute__((always_inline)) inline void static_for(F &&f) {
-    static_for_seq(f, std::make_integer_sequence<int, N>());
-}
-
 // Floats as integers of the same order (never 0 for a finite float).  The zeros
 // are one value, as in a comparison of floats: bounds of a record with r = 0 are
 // zeros of either sign, and their keys tie.

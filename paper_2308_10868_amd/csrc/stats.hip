@@ -60,17 +60,6 @@ __device__ inline void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// f(0) .. f(N - 1) with the index as a compile-time constant.
-template <typename F, int... I>
-__device__ __attribute__((always_inline)) inline void static_for_seq(
-    F &&f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>()), ...);
-}
-template <int N, typename F>
-__device__ __attribute__((always_inline)) inline void static_for(F &&f) {
-    static_for_seq(f, std::make_integer_sequence<int, N>());
-}
-
 // Body of the float statistics kernel.  V: staged voxel type, A/AQ: row and
 // plane sums of F and F^2, AS/AQQ: block sums, re-added from the ring of the
 // last bz plane sums.  Global loads run two planes ahead of the plane being

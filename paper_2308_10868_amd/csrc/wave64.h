@@ -6,8 +6,21 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
+#include <utility>
 
 namespace nrr {
+
+// f(0) .. f(N - 1) with the index as a compile-time constant.
+template <typename F, int... I>
+__device__ __attribute__((always_inline)) inline void static_for_seq(
+    F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ __attribute__((always_inline)) inline void static_for(F &&f) {
+    static_for_seq(f, std::make_integer_sequence<int, N>());
+}
 
 // a / b for 0 <= a < 2^20, 0 < b: (a + 1/2) / b is at least 1 / (2 b) away from
 // the next integer, beyond the rounding of the reciprocal and the product.
