@@ -438,24 +438,30 @@ __device__ __attribute__((always_inline)) inline void sweep_tiles(
         // registers allow three)
         constexpr int AHEAD = B == 7 ? 3 : B;
         StatU16 rec[B][4];
-        RecordPlanes at;  // of the plane fetched next (planes in order)
+        RecordPlanes at;
         at.start(p.stats, p.nstat, corner, sizeof(StatU16));
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<unsigned char *>(at.base), 0, (int)at.bytes, 0x00020000);
+        // of the plane fetched next (planes in order), added to the lanes' offsets
+        // load by load: a descriptor per plane cost the steps' scalar issue (b = 7 208
+        // us against 204, dense b = 9 31.3 ms against 31.0), sums kept ahead by the
+        // compiler registers (13 spilled at b = 7: 213 us)
+        uint32_t plane_off = 0;
         auto fetch = [&](int tau, StatU16 (&rec)[4]) __attribute__((always_inline)) {
-            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<unsigned char *>(at.base), 0, (int)at.bytes, 0x00020000);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if constexpr (WIDE) {
                     rec[i] = srec[rcur[i]];
                     rcur[i] += tau < lim3[i] ? plane_rec : 0;
                 } else {
-                    const u32x2 v =
-                        __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)roff[i], 0, 0);
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(
+                        rsrc, (int)(roff[i] + plane_off), 0, 0);
                     rec[i].s = (int)v[0];
                     rec[i].r = __uint_as_float(v[1]);
                 }
             }
-            at.next((uint32_t)plane_rec * (uint32_t)sizeof(StatU16));
+            plane_off += (uint32_t)plane_rec * (uint32_t)sizeof(StatU16);
+            asm volatile("" : "+s"(plane_off));
         };
         // best key of each output row in this tile and its plane (-1: none).
         // Along a row the shift index grows with tau, so a strict comparison

@@ -23,7 +23,7 @@ struct RecordPlanes {
     uint32_t bytes;             // readable from there (0 behind the last plane)
 
     // `table`: nstat records of `size` bytes; `corner`: the window's first one.
-    // Offsets from a step's base must lie below 2^31.
+    // Offsets from the base, planes added to them included, must lie below 2^31.
     NRR_HOST_DEVICE inline void start(const void *table, int64_t nstat, int64_t corner, int size) {
         base = static_cast<const unsigned char *>(table) + corner * size;
         const int64_t left = (nstat - corner) * size;

@@ -92,6 +92,27 @@ def test_loads_stay_in_the_table(program, b, w, dims, size):
     assert r.returncode == 0 and int(r.stdout) > 0, r.stdout
 
 
+# the sweep that keeps one descriptor and adds each plane to the lanes' offsets
+KEPT = PROGRAM.replace("r.next((uint32_t)(plane * size))", "off0 += plane * size") \
+    .replace("for (int tau = 0;", "int64_t off0 = 0;\n                        for (int tau = 0;") \
+    .replace("(oph * plane + y * ox + x) * size;", "off0 + (oph * plane + y * ox + x) * size;")
+
+
+@pytest.mark.parametrize("b,w,dims", [
+    (7, 1, (16, 15, 14)), (3, 0, (9, 8, 7)), (5, 4, (17, 16, 19)), (7, 5, (19, 20, 23)),
+    (9, 3, (17, 19, 12)), (9, 8, (25, 11, 27)), (3, 4, (3, 3, 3)),
+])
+def test_kept_descriptor_stays_in_the_table(tmp_path, b, w, dims):
+    assert KEPT.count("off0") == 3
+    (tmp_path / "t.cpp").write_text(KEPT)
+    exe = str(tmp_path / "t")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", CSRC, str(tmp_path / "t.cpp"), "-o", exe],
+                   check=True)
+    arg = ",".join(str(v) for v in (b, w, *dims, 8))
+    r = subprocess.run([exe, arg], capture_output=True, text=True)
+    assert r.returncode == 0 and int(r.stdout) > 0, r.stdout
+
+
 @pytest.mark.parametrize("source", ["match_mfma.hip", "mfma_filter.h"])
 def test_record_loads_use_the_lane_offset_alone(source):
     """No buffer load of the searches carries a scalar offset, which a
